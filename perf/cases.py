@@ -82,11 +82,10 @@ def _log_int(rng, lo, hi):
 def draw(rng):
     kind = rng.choice(["step", "step", "step", "upstream", "autograd", "view", "track", "manage", "select",
                        "update"])
-    w = _log_int(rng, 120, 1300)
+    w = _log_int(rng, 240 if kind == "track" else 120, 1300)
     h = max(64, int(w * rng.uniform(0.5, 0.8)))
     if kind == "track":
-        w = max(w, 240)
-        return _case(kind, 0, 1, w, max(h, 160))
+        return _case(kind, 0, 1, w, h)
     if kind == "select":
         return _case(kind, 0, rng.randint(1, 16), w, h)
     if kind == "manage":
