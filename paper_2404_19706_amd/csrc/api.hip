@@ -1006,37 +1006,51 @@ rtg_status rtg_icp(const rtg_intrinsics* intr, const rtg_icp_params* prm, const 
     const float* D[3] = {depth_in, nullptr, nullptr};
     const float* Dm[3] = {depth_model, nullptr, nullptr};
     const float* Nm[3] = {normal_model, nullptr, nullptr};
+    float *d[3] = {}, *dm[3] = {}, *nm[3] = {};
     for (int l = 1; l < prm->levels; ++l) {
-        float* d = reinterpret_cast<float*>(b + L.off_d[l]);
-        float* dm = reinterpret_cast<float*>(b + L.off_dm[l]);
-        float* nm = reinterpret_cast<float*>(b + L.off_nm[l]);
-        const unsigned g = grid_for((int64_t)L.W[l] * L.H[l], 256);
-        hipLaunchKernelGGL(k_icp_down_depth, dim3(g), dim3(256), 0, S(stream), D[l - 1], L.W[l - 1], d, L.W[l],
-                           L.H[l]);
-        hipLaunchKernelGGL(k_icp_down_depth, dim3(g), dim3(256), 0, S(stream), Dm[l - 1], L.W[l - 1], dm, L.W[l],
-                           L.H[l]);
-        hipLaunchKernelGGL(k_icp_down_normal, dim3(g), dim3(256), 0, S(stream), Dm[l - 1], Nm[l - 1], L.W[l - 1],
-                           nm, L.W[l], L.H[l]);
-        D[l] = d;
-        Dm[l] = dm;
-        Nm[l] = nm;
+        D[l] = d[l] = reinterpret_cast<float*>(b + L.off_d[l]);
+        Dm[l] = dm[l] = reinterpret_cast<float*>(b + L.off_dm[l]);
+        Nm[l] = nm[l] = reinterpret_cast<float*>(b + L.off_nm[l]);
     }
-    if (pose_out != pose_init)
-        hipLaunchKernelGGL(k_icp_copy_pose, dim3(1), dim3(64), 0, S(stream), pose_init, pose_out);
+    if (prm->levels > 1) {
+        const bool two = prm->levels > 2;
+        const IcpPyr P{depth_in, depth_model, normal_model, d[1],   dm[1],  nm[1],           d[2],
+                       dm[2],    nm[2],       L.W[0],       L.W[1], L.H[1], two ? L.W[2] : 0, two ? L.H[2] : 0};
+        const int64_t cells = (int64_t)((L.W[1] + 1) / 2) * ((L.H[1] + 1) / 2);
+        hipLaunchKernelGGL(k_icp_pyramid, dim3(grid_for(cells, 256)), dim3(256), 0, S(stream), P);
+    }
+    // The partial rows take the space of one row per 256 level-0 pixels: two
+    // sets of up to max_rows rows, then one pose; the other place of a pose
+    // is pose_out, the first pass writing the workspace's (pose_out may be
+    // pose_init, which that pass reads).  An image too small for that takes
+    // one workgroup, which may overwrite what it has read.
     double* part = reinterpret_cast<double*>(b + L.off_part);
+    const int max_rows = std::min(256, std::max(1, (kIcpTerms * L.nblk0 - 12) / (2 * kIcpTerms)));
+    const bool one = max_rows == 1;
+    double* part_of[2] = {part, one ? part : part + (int64_t)max_rows * kIcpTerms};
+    double* pose_of[2] = {one ? pose_out : part + 2 * (int64_t)max_rows * kIcpTerms, pose_out};
+    IcpPrev prev{nullptr, 0, pose_init, nullptr};
     int row = 0;
     for (int l = prm->levels - 1; l >= 0; --l) {
         const double s = (double)(1 << l);
-        IcpLevel lv{L.W[l], L.H[l], intr->fx / s, intr->fy / s, intr->cx / s, intr->cy / s, D[l], Dm[l], Nm[l]};
-        // at most 512 workgroups, each striding over the level's pixels
-        const int nblk = (int)std::min<unsigned>(grid_for((int64_t)L.W[l] * L.H[l], 256), 512u);
+        const IcpLevel lv{L.W[l], L.H[l], intr->fx / s, intr->fy / s, intr->cx / s, intr->cy / s, D[l], Dm[l], Nm[l]};
+        // rows of strips of 64 columns, at least one per wave
+        const int strips = (L.W[l] - 1 + 63) / 64;
+        const int64_t units = (int64_t)strips * (L.H[l] - 1), per = kIcpThreads / 64;
+        const int nblk = (int)std::min<int64_t>(max_rows, (units + per - 1) / per);
         for (int it = 0; it < prm->iters[l]; ++it, ++row) {
-            hipLaunchKernelGGL(k_icp_reduce, dim3(nblk), dim3(256), 0, S(stream), lv, (const double*)pose_out,
-                               pose_model, prm->dist, prm->sin_angle, part);
-            hipLaunchKernelGGL(k_icp_solve, dim3(1), dim3(256), 0, S(stream), (const double*)part, nblk, pose_out,
-                               trace_out ? trace_out + (int64_t)kIcpTrace * row : nullptr);
+            double* Tk = pose_of[row & 1];
+            double* pk = part_of[row & 1];
+            if (L.W[l] + L.H[l] <= kIcpTable)
+                hipLaunchKernelGGL(k_icp_pass<true>, dim3(nblk), dim3(kIcpThreads), 8 * (size_t)(L.W[l] + L.H[l]),
+                                   S(stream), lv, prev, pose_model, prm->dist, prm->sin_angle, strips, Tk, pk);
+            else
+                hipLaunchKernelGGL(k_icp_pass<false>, dim3(nblk), dim3(kIcpThreads), 0, S(stream), lv, prev,
+                                   pose_model, prm->dist, prm->sin_angle, strips, Tk, pk);
+            prev = IcpPrev{pk, nblk, Tk, trace_out ? trace_out + (int64_t)kIcpTrace * row : nullptr};
         }
     }
+    hipLaunchKernelGGL(k_icp_finish, dim3(1), dim3(kIcpThreads), 0, S(stream), prev, pose_out);
     return launched();
 }
 

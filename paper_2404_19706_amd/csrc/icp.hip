@@ -3,13 +3,14 @@
 // Gaussian's normal per pixel) and a multi-level projective point-to-plane
 // ICP of an input depth frame against the rendered depth and normals.
 //
-// Per level and iteration: one thread per input pixel forms the pair of
-// Eq. 10 (binary64, a fixed operation sequence), its residual and Jacobian,
-// and the workgroup sums the 29 terms of the normal equations (A upper
-// triangle, b, r^2, count) in a fixed tree; one workgroup then adds the
-// partial sums in a fixed order, solves the 6x6 system by Cholesky and
-// applies the SE(3) update to the pose held in device memory, so the whole
-// iteration schedule is enqueued without a host round trip.
+// One launch per iteration: each workgroup first adds the partial normal
+// equations of the iteration before in a fixed order, solves the 6x6 system
+// by Cholesky and applies the SE(3) update; then its lanes form the pairs of
+// Eq. 10 for their input pixels (binary64, a fixed operation sequence), their
+// residuals and Jacobians, and the workgroup sums the 29 terms of the normal
+// equations (A upper triangle, b, r^2, count) in a fixed tree.  A last launch
+// solves for the result, so the whole iteration schedule is enqueued without
+// a host round trip.
 #include "rtg_common.h"
 
 namespace rtg {
@@ -44,48 +45,76 @@ __global__ __launch_bounds__(256) void k_render_normals(Dims d, WS w, float* __r
     out_n[3 * pix + 2] = n2;
 }
 
-// Depth of level l+1: the binary32 mean of the valid (> 0) depths of the
-// 2 x 2 block, ((d00 + d01) + d10) + d11 over the valid ones / their count.
-__global__ __launch_bounds__(256) void k_icp_down_depth(const float* __restrict__ Df, int Wf, float* __restrict__ Dc,
-                                                        int Wc, int Hc) {
-    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (p >= (int64_t)Wc * Hc) return;
-    const int x = (int)(p % Wc), y = (int)(p / Wc);
-    const float* r0 = Df + (int64_t)(2 * y) * Wf + 2 * x;
-    const float* r1 = r0 + Wf;
-    const float q[4] = {r0[0], r0[1], r1[0], r1[1]};
+// Pyramid levels 1 and 2 of the input depth, the model depth and the model
+// normals in one launch.  Depth of a coarser pixel: the binary32 mean of the
+// valid (> 0) depths of its 2 x 2 block, ((d00 + d01) + d10) + d11 over the
+// valid ones / their count; model normal: that of the block's first pixel
+// (raster order) with a valid depth.  A thread makes a 2 x 2 block of level-1
+// pixels (fewer at an odd edge) and the level-2 pixel they form, so level 2
+// is built from registers; the six single-map launches this replaces were
+// bound by their launches (28 us together at 1200x680 against 6 us).
+struct IcpPyr {
+    const float *D, *Dm, *Nm;            // level 0
+    float *D1, *Dm1, *Nm1;               // level 1
+    float *D2, *Dm2, *Nm2;               // level 2 (unused with two levels)
+    int W, W1, H1, W2, H2;               // W2 = H2 = 0 with two levels
+};
+
+__device__ __forceinline__ float mean_valid(const float (&q)[4]) {
     float s = 0.f, c = 0.f;
+#pragma unroll
     for (int k = 0; k < 4; ++k)
         if (q[k] > 0.f) {
             s = s + q[k];
             c = c + 1.f;
         }
-    Dc[p] = c > 0.f ? s / c : 0.f;
+    return c > 0.f ? s / c : 0.f;
 }
 
-// Model normal of level l+1: that of the block's first pixel (raster order)
-// with a valid depth.
-__global__ __launch_bounds__(256) void k_icp_down_normal(const float* __restrict__ Df, const float* __restrict__ Nf,
-                                                         int Wf, float* __restrict__ Nc, int Wc, int Hc) {
-    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (p >= (int64_t)Wc * Hc) return;
-    const int x = (int)(p % Wc), y = (int)(p / Wc);
-    float n0 = 0.f, n1 = 0.f, n2 = 0.f;
-    for (int k = 3; k >= 0; --k) {
-        const int64_t q = (int64_t)(2 * y + (k >> 1)) * Wf + 2 * x + (k & 1);
-        if (Df[q] > 0.f) {
-            n0 = Nf[3 * q];
-            n1 = Nf[3 * q + 1];
-            n2 = Nf[3 * q + 2];
+__global__ __launch_bounds__(256) void k_icp_pyramid(IcpPyr P) {
+    const int cw = (P.W1 + 1) >> 1, ch = (P.H1 + 1) >> 1;
+    const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (c >= (int64_t)cw * ch) return;
+    const int bx = (int)(c % cw), by = (int)(c / cw);
+    float d1[4] = {0.f, 0.f, 0.f, 0.f}, m1[4] = {0.f, 0.f, 0.f, 0.f}, n1[4][3];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int x = 2 * bx + (k & 1), y = 2 * by + (k >> 1);
+        n1[k][0] = n1[k][1] = n1[k][2] = 0.f;
+        if (x >= P.W1 || y >= P.H1) continue;
+        const int64_t q = (int64_t)(2 * y) * P.W + 2 * x;
+        const float d[4] = {P.D[q], P.D[q + 1], P.D[q + P.W], P.D[q + P.W + 1]};
+        const float m[4] = {P.Dm[q], P.Dm[q + 1], P.Dm[q + P.W], P.Dm[q + P.W + 1]};
+        d1[k] = mean_valid(d);
+        m1[k] = mean_valid(m);
+        const int64_t qn = m[0] > 0.f ? q : m[1] > 0.f ? q + 1 : m[2] > 0.f ? q + P.W : q + P.W + 1;
+        if (m[0] > 0.f || m[1] > 0.f || m[2] > 0.f || m[3] > 0.f) {
+            n1[k][0] = P.Nm[3 * qn];
+            n1[k][1] = P.Nm[3 * qn + 1];
+            n1[k][2] = P.Nm[3 * qn + 2];
         }
+        const int64_t o = (int64_t)y * P.W1 + x;
+        P.D1[o] = d1[k];
+        P.Dm1[o] = m1[k];
+        P.Nm1[3 * o] = n1[k][0];
+        P.Nm1[3 * o + 1] = n1[k][1];
+        P.Nm1[3 * o + 2] = n1[k][2];
     }
-    Nc[3 * p] = n0;
-    Nc[3 * p + 1] = n1;
-    Nc[3 * p + 2] = n2;
-}
-
-__global__ void k_icp_copy_pose(const double* __restrict__ src, double* __restrict__ dst) {
-    if (threadIdx.x < 12) dst[threadIdx.x] = src[threadIdx.x];
+    if (bx >= P.W2 || by >= P.H2) return;
+    const int64_t o = (int64_t)by * P.W2 + bx;
+    P.D2[o] = mean_valid(d1);
+    P.Dm2[o] = mean_valid(m1);
+    float n0 = 0.f, nx = 0.f, nz = 0.f;
+#pragma unroll
+    for (int k = 3; k >= 0; --k)
+        if (m1[k] > 0.f) {
+            n0 = n1[k][0];
+            nx = n1[k][1];
+            nz = n1[k][2];
+        }
+    P.Nm2[3 * o] = n0;
+    P.Nm2[3 * o + 1] = nx;
+    P.Nm2[3 * o + 2] = nz;
 }
 
 struct IcpLevel {
@@ -96,11 +125,9 @@ struct IcpLevel {
     const float* Nm;   // model normals (camera frame of the model pose)
 };
 
-__device__ __forceinline__ void vtx(const IcpLevel& L, int x, int y, double D, double* v) {
-    v[0] = D * ((((double)x + 0.5) - L.cx) / L.fx);
-    v[1] = D * ((((double)y + 0.5) - L.cy) / L.fy);
-    v[2] = D;
-}
+// Ray of a pixel column / row: vertex = D * (ray_x, ray_y, 1).
+__device__ __forceinline__ double ray_x(const IcpLevel& L, int x) { return (((double)x + 0.5) - L.cx) / L.fx; }
+__device__ __forceinline__ double ray_y(const IcpLevel& L, int y) { return (((double)y + 0.5) - L.cy) / L.fy; }
 
 __device__ __forceinline__ void mat_vec(const double* R, const double* v, double* o) {
     for (int i = 0; i < 3; ++i) o[i] = (R[3 * i] * v[0] + R[3 * i + 1] * v[1]) + R[3 * i + 2] * v[2];
@@ -114,106 +141,6 @@ __device__ __forceinline__ void cross3(const double* a, const double* b, double*
 
 __device__ __forceinline__ double dot3(const double* a, const double* b) {
     return (a[0] * b[0] + a[1] * b[1]) + a[2] * b[2];
-}
-
-// The input pixels' pairs (Eq. 10, projective association) under the
-// estimate T of the input frame's camera-to-world pose against the model
-// rendered at Tm; each thread strides over the pixels and adds the 29 terms
-// of its kept pairs, in pixel order.
-__global__ __launch_bounds__(256) void k_icp_reduce(IcpLevel L, const double* __restrict__ Tdev,
-                                                    const double* __restrict__ Tm, double dist, double sin_a,
-                                                    double* __restrict__ partials) {
-    __shared__ double red[4][kIcpTerms];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    double t[kIcpTerms];
-    for (int k = 0; k < kIcpTerms; ++k) t[k] = 0.0;
-    for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < (int64_t)L.W * L.H;
-         p += (int64_t)gridDim.x * 256) {
-        const int x = (int)(p % L.W), y = (int)(p / L.W);
-        bool ok = x < L.W - 1 && y < L.H - 1;
-        double D = 0.0, Dr = 0.0, Dd = 0.0;
-        if (ok) {
-            D = L.D[p];
-            Dr = L.D[p + 1];
-            Dd = L.D[p + L.W];
-            ok = D > 0.0 && Dr > 0.0 && Dd > 0.0;
-        }
-        if (ok) {
-            double T[12], M[12];
-            for (int k = 0; k < 12; ++k) {
-                T[k] = Tdev[k];
-                M[k] = Tm[k];
-            }
-            double V[3], Vr[3], Vd[3], a[3], b[3], Nn[3];
-            vtx(L, x, y, D, V);
-            vtx(L, x + 1, y, Dr, Vr);
-            vtx(L, x, y + 1, Dd, Vd);
-            for (int i = 0; i < 3; ++i) {
-                a[i] = Vr[i] - V[i];
-                b[i] = Vd[i] - V[i];
-            }
-            cross3(a, b, Nn);
-            double P[3], dm[3], pm[3];
-            mat_vec(T, V, P);
-            for (int i = 0; i < 3; ++i) P[i] = P[i] + T[9 + i];
-            for (int i = 0; i < 3; ++i) dm[i] = P[i] - M[9 + i];
-            for (int i = 0; i < 3; ++i) pm[i] = (M[i] * dm[0] + M[3 + i] * dm[1]) + M[6 + i] * dm[2];
-            ok = pm[2] > 0.0;
-            int ui = 0, vi = 0;
-            if (ok) {
-                const double u = floor(L.fx * pm[0] / pm[2] + L.cx);
-                const double v = floor(L.fy * pm[1] / pm[2] + L.cy);
-                ok = u >= 0.0 && u < (double)L.W && v >= 0.0 && v < (double)L.H;
-                ui = ok ? (int)u : 0;
-                vi = ok ? (int)v : 0;
-            }
-            const int64_t q = (int64_t)vi * L.W + ui;
-            double Dmq = 0.0, nm[3] = {0.0, 0.0, 0.0};
-            if (ok) {
-                Dmq = L.Dm[q];
-                nm[0] = L.Nm[3 * q];
-                nm[1] = L.Nm[3 * q + 1];
-                nm[2] = L.Nm[3 * q + 2];
-                ok = Dmq > 0.0 && dot3(nm, nm) > 0.0;
-            }
-            if (ok) {
-                double Vm[3], Q[3], n[3], m[3], dd[3], cr[3];
-                vtx(L, ui, vi, Dmq, Vm);
-                mat_vec(M, Vm, Q);
-                for (int i = 0; i < 3; ++i) Q[i] = Q[i] + M[9 + i];
-                mat_vec(M, nm, n);
-                mat_vec(T, Nn, m);
-                for (int i = 0; i < 3; ++i) dd[i] = P[i] - Q[i];
-                cross3(m, n, cr);
-                ok = dot3(dd, dd) <= dist * dist && dot3(cr, cr) <= (sin_a * sin_a) * (dot3(m, m) * dot3(n, n));
-                if (ok) {
-                    const double r = dot3(dd, n);
-                    double J[6];
-                    cross3(P, n, J);
-                    J[3] = n[0];
-                    J[4] = n[1];
-                    J[5] = n[2];
-                    int k = 0;
-                    for (int i = 0; i < 6; ++i)
-                        for (int j = i; j < 6; ++j) t[k++] += J[i] * J[j];
-                    for (int i = 0; i < 6; ++i) t[21 + i] += J[i] * r;
-                    t[27] += r * r;
-                    t[28] += 1.0;
-                }
-            }
-        }
-    }
-    // fixed-order reduction: wave butterflies, then the four waves in order
-    for (int k = 0; k < kIcpTerms; ++k) {
-        double v = t[k];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if (lane == 0) red[wv][k] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x < kIcpTerms) {
-        const int k = threadIdx.x;
-        partials[(int64_t)blockIdx.x * kIcpTerms + k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
-    }
 }
 
 // SE(3) exponential of xi = (omega, v): R = I + a [w] + b [w]^2,
@@ -247,81 +174,346 @@ __device__ void se3_exp(const double* xi, double* R, double* t) {
     for (int i = 0; i < 3; ++i) t[i] = (Vm[3 * i] * xi[3] + Vm[3 * i + 1] * xi[4]) + Vm[3 * i + 2] * xi[5];
 }
 
-// One workgroup: the partial sums in a fixed order, the 6x6 solve (no
-// update with fewer than 6 pairs or a non-positive pivot), the pose update
-// T <- exp(xi) T and the trace row (pose used, r^2, count, A, b).
-__global__ __launch_bounds__(256) void k_icp_solve(const double* __restrict__ partials, int nblk,
-                                                   double* __restrict__ T, double* __restrict__ trace) {
-    __shared__ double red[4][kIcpTerms];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    double s[kIcpTerms];
-    for (int k = 0; k < kIcpTerms; ++k) s[k] = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += 256)
-        for (int k = 0; k < kIcpTerms; ++k) s[k] += partials[(int64_t)b * kIcpTerms + k];
-    for (int k = 0; k < kIcpTerms; ++k) {
-        double v = s[k];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if (lane == 0) red[wv][k] = v;
+// Reduce-scatter of 32 binary64 values over the wave: every lane returns the
+// wave total of slot icp_slot(lane).  Lane bits 5 and 4 by the permlane
+// swaps (each half keeps its own slot's partial sum after one add), bits 3
+// and 2 by the row mirrors (partners that agree on the bits already reduced),
+// bit 1 within the quads, then the pair sum over bit 0: 31 exchanges
+// where a butterfly per value takes 174 for the 29 terms.
+__device__ __forceinline__ double f64_of(uint32_t lo, uint32_t hi) {
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ void f64_to(double v, uint32_t& lo, uint32_t& hi) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    lo = (uint32_t)b;
+    hi = (uint32_t)(b >> 32);
+}
+__device__ __forceinline__ double swap32_sum64(double a, double b) {
+    uint32_t al, ah, bl, bh;
+    f64_to(a, al, ah);
+    f64_to(b, bl, bh);
+    auto l = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+    auto h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+    return f64_of(l[0], h[0]) + f64_of(l[1], h[1]);
+}
+__device__ __forceinline__ double swap16_sum64(double a, double b) {
+    uint32_t al, ah, bl, bh;
+    f64_to(a, al, ah);
+    f64_to(b, bl, bh);
+    auto l = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+    auto h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+    return f64_of(l[0], h[0]) + f64_of(l[1], h[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov64(double v) {
+    uint32_t lo, hi;
+    f64_to(v, lo, hi);
+    lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, CTRL, 0xf, 0xf, false);
+    hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, CTRL, 0xf, 0xf, false);
+    return f64_of(lo, hi);
+}
+template <int CTRL>
+__device__ __forceinline__ double pair_sum64(double a, double b, bool hi) {
+    const double send = hi ? a : b, keep = hi ? b : a;
+    return keep + dpp_mov64<CTRL>(send);
+}
+__device__ __forceinline__ double reduce_scatter32(double (&t)[32], int lane) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) t[j] = swap32_sum64(t[2 * j], t[2 * j + 1]);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t[j] = swap16_sum64(t[2 * j], t[2 * j + 1]);
+    const bool b3 = (lane >> 3) & 1, b2 = (lane >> 2) & 1, b1 = (lane >> 1) & 1;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t[j] = pair_sum64<0x140>(t[2 * j], t[2 * j + 1], b3);   // row mirror
+#pragma unroll
+    for (int j = 0; j < 2; ++j) t[j] = pair_sum64<0x141>(t[2 * j], t[2 * j + 1], b2);   // half-row mirror
+    const double r = pair_sum64<0x4E>(t[0], t[1], b1);                                  // quad [2,3,0,1]
+    return r + dpp_mov64<0xB1>(r);                                                      // quad [1,0,3,2]
+}
+__device__ __forceinline__ int icp_slot(int lane) {
+    return ((lane >> 5) & 1) + 2 * ((lane >> 4) & 1) + 4 * ((lane >> 3) & 1) + 8 * ((lane >> 2) & 1) +
+           16 * ((lane >> 1) & 1);
+}
+
+// What a pass starts from: the normal equations of the pass before it (as
+// per-workgroup partial rows) and the pose that pass used, or, for the first
+// one (part == nullptr), the initial pose itself.
+struct IcpPrev {
+    const double* part;
+    int rows;
+    const double* T;
+    double* trace;   // trace row of the pass before, or nullptr
+};
+
+// The pose after the previous pass, into T (LDS) for the whole workgroup of
+// kIcpThreads: the partial rows added in a fixed order (every workgroup
+// gets the same bits), the 6x6 solve by Cholesky (no update with fewer than
+// 6 pairs or a non-positive pivot) and T <- exp(xi) T.  `write`: this workgroup
+// also writes the trace row (pose used, r^2, count, A, b).
+constexpr int kIcpThreads = 768;
+
+__device__ void icp_next_pose(const IcpPrev& v, bool write, double (&red)[kIcpThreads / 64][32], double (&T)[12]) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (!v.part) {
+        if (tid < 12) T[tid] = v.T[tid];
+        __syncthreads();
+        return;
+    }
+    // thread (row group tid / 32, term tid % 32)
+    const int k = tid & 31;
+    double s = 0.0;
+    if (k < kIcpTerms)
+        for (int b = tid >> 5; b < v.rows; b += kIcpThreads / 32) s += v.part[(int64_t)b * kIcpTerms + k];
+    s += __shfl_xor(s, 32);
+    if (lane < 32) red[wv][lane] = s;
+    __syncthreads();
+    if (wv == 0) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < kIcpThreads / 64; ++w) t += red[w][lane & 31];
+        double tot[kIcpTerms];
+#pragma unroll
+        for (int i = 0; i < kIcpTerms; ++i) tot[i] = __shfl(t, i);
+        double T0[12];
+#pragma unroll
+        for (int i = 0; i < 12; ++i) T0[i] = v.T[i];
+        if (write && v.trace && lane < kIcpTrace) {
+            double o = 0.0;
+            if (lane < 12) o = v.T[lane];
+            const int src = lane == 12 ? 27 : lane == 13 ? 28 : lane - 14;
+            const double ts = __shfl(t, src & 31);
+            if (lane >= 12 && lane < 41) o = ts;
+            v.trace[lane] = o;
+        }
+        // Cholesky A = L L^T; the upper triangle of A is tot[0..20] row by row
+        double Lc[6][6], yv[6], xi[6];
+        bool good = tot[28] >= 6.0;
+#pragma unroll
+        for (int j = 0; j < 6; ++j)
+#pragma unroll
+            for (int i = j; i < 6; ++i) {
+                double acc = tot[j * 6 - (j * (j - 1)) / 2 + (i - j)];
+#pragma unroll
+                for (int m = 0; m < j; ++m) acc -= Lc[i][m] * Lc[j][m];
+                if (i == j) {
+                    good = good && acc > 0.0;
+                    Lc[j][j] = sqrt(acc);
+                } else {
+                    Lc[i][j] = acc / Lc[j][j];
+                }
+            }
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            double acc = tot[21 + i];
+#pragma unroll
+            for (int m = 0; m < i; ++m) acc -= Lc[i][m] * yv[m];
+            yv[i] = acc / Lc[i][i];
+        }
+#pragma unroll
+        for (int i = 5; i >= 0; --i) {
+            double acc = yv[i];
+#pragma unroll
+            for (int m = i + 1; m < 6; ++m) acc -= Lc[m][i] * xi[m];
+            xi[i] = acc / Lc[i][i];
+        }
+#pragma unroll
+        for (int i = 0; i < 6; ++i) xi[i] = -xi[i];
+        double dR[9], dt[3], Tn[12];
+        se3_exp(xi, dR, dt);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                Tn[3 * i + j] = (dR[3 * i] * T0[j] + dR[3 * i + 1] * T0[3 + j]) + dR[3 * i + 2] * T0[6 + j];
+            Tn[9 + i] = ((dR[3 * i] * T0[9] + dR[3 * i + 1] * T0[10]) + dR[3 * i + 2] * T0[11]) + dt[i];
+        }
+        if (lane == 0)
+#pragma unroll
+            for (int i = 0; i < 12; ++i) T[i] = good ? Tn[i] : T0[i];
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    double tot[kIcpTerms];
-    for (int k = 0; k < kIcpTerms; ++k) tot[k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
-    double A[36], bb[6];
-    int k = 0;
-    for (int i = 0; i < 6; ++i)
-        for (int j = i; j < 6; ++j) {
-            A[6 * i + j] = tot[k];
-            A[6 * j + i] = tot[k];
-            ++k;
+}
+
+// The same value on every lane, held in scalar registers.
+__device__ __forceinline__ double uniform64(double v) {
+    uint32_t lo, hi;
+    f64_to(v, lo, hi);
+    return f64_of((uint32_t)readfirstlane((int)lo), (uint32_t)readfirstlane((int)hi));
+}
+
+// Rays of the level's columns and rows, from a table in LDS (TAB) or formed
+// where they are needed.
+constexpr int kIcpTable = 7168;   // entries (56 KB of the 64 KB a workgroup has by default): columns, then rows
+
+template <bool TAB>
+struct IcpRays {
+    const double* tab;
+    __device__ __forceinline__ double x(const IcpLevel& L, int i) const {
+        if constexpr (TAB) return tab[i];
+        else return ray_x(L, i);
+    }
+    __device__ __forceinline__ double y(const IcpLevel& L, int i) const {
+        if constexpr (TAB) return tab[L.W + i];
+        else return ray_y(L, i);
+    }
+};
+
+// The pair of one input pixel up to the model's depth and normal (in flight
+// while the pixel before it is summed).
+struct IcpCand {
+    double P[3], Nn[3];   // world point, input normal (camera frame, not normalised)
+    float Dm, n0, n1, n2;
+    int ui, vi;
+    bool ok;
+};
+
+// One pass: the pose from the pass before (each workgroup solves for it
+// itself: about 2 us once the rows are there, where a launch of its own cost
+// 19 us, most of it one thread working from scratch memory), then the
+// input pixels' pairs (Eq. 10, projective association) under that estimate
+// T of the input frame's camera-to-world pose against the model rendered at
+// Tm.  The image is cut into strips of 64 columns; numbered strip by strip,
+// the rows of the strips are dealt to the waves in equal contiguous shares,
+// and the lanes take their pixels two at a time, staggered: the depths of
+// the row after next and the model's entries of the next pixel are loaded
+// while the present one is summed (three waves per SIMD, all the 29 binary64
+// sums allow, do not hide those two dependent loads).  The rays come from a
+// table in LDS where image width + height fit it, which takes the binary64
+// divisions per pixel from ten to two; the sums are fused multiply-adds, the
+// decisions keep their unfused sequence.  Bound by binary64 issue (344
+// instructions per pixel); a level-0 pass at 1200x680 takes 19 us, 6 of them
+// the launch and the solve, where a pass and its solve took 18 + 19 us on
+// average over the levels (the whole call 730 to 296 us).  The partial rows of
+// consecutive passes and the poses alternate between two places, so no workgroup
+// overwrites what another still reads.
+template <bool TAB>
+__global__ __launch_bounds__(kIcpThreads) void k_icp_pass(IcpLevel L, IcpPrev prev, const double* __restrict__ Tm,
+                                                          double dist, double sin_a, int strips,
+                                                          double* __restrict__ T_out, double* __restrict__ partials) {
+    __shared__ double red[kIcpThreads / 64][32];
+    __shared__ double sT[12];
+    extern __shared__ double ray_tab[];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if constexpr (TAB)
+        for (int i = threadIdx.x; i < L.W + L.H; i += kIcpThreads)
+            ray_tab[i] = i < L.W ? ray_x(L, i) : ray_y(L, i - L.W);
+    const IcpRays<TAB> rays{ray_tab};
+    icp_next_pose(prev, blockIdx.x == 0, red, sT);   // (ends with a barrier)
+    double T[12], M[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        T[k] = uniform64(sT[k]);
+        M[k] = Tm[k];
+    }
+    if (blockIdx.x == 0 && threadIdx.x < 12) T_out[threadIdx.x] = sT[threadIdx.x];
+    double t[32];
+#pragma unroll
+    for (int k = 0; k < 32; ++k) t[k] = 0.0;
+    // (the last row and column have no forward difference)
+    const int h = L.H - 1;
+    const uint64_t units = (uint64_t)strips * (uint32_t)h, nw = (uint64_t)gridDim.x * (kIcpThreads / 64);
+    const uint64_t wid = (uint64_t)blockIdx.x * (kIcpThreads / 64) + (uint32_t)readfirstlane(wv);
+    const int u0 = (int)(wid * units / nw), u1 = (int)((wid + 1) * units / nw);
+    // pixel of a unit in this lane: its depths are read in advance
+    struct Row {
+        float D, Dr, Dd;
+        int x, y;
+    };
+    auto load_row = [&](int u) {
+        Row r;
+        const int strip = u / h, x = strip * 64 + lane;
+        r.y = u - strip * h;
+        r.x = x;
+        const float* p = L.D + (int64_t)r.y * L.W + (x < L.W - 1 ? x : 0);
+        r.D = x < L.W - 1 ? p[0] : 0.f;
+        r.Dr = p[1];
+        r.Dd = p[L.W];
+        return r;
+    };
+    auto candidate = [&](const Row& rw) {
+        IcpCand c;
+        c.ok = rw.D > 0.f && rw.Dr > 0.f && rw.Dd > 0.f;
+        const double D = rw.D, Dr = rw.Dr, Dd = rw.Dd;
+        const int x = c.ok ? rw.x : 0;
+        const double rx = rays.x(L, x), rxr = rays.x(L, x + 1), ry = rays.y(L, rw.y), ryd = rays.y(L, rw.y + 1);
+        const double V[3] = {D * rx, D * ry, D};
+        const double a[3] = {Dr * rxr - V[0], Dr * ry - V[1], Dr - V[2]};
+        const double b[3] = {Dd * rx - V[0], Dd * ryd - V[1], Dd - V[2]};
+        double dm[3], pm[3];
+        cross3(a, b, c.Nn);
+        mat_vec(T, V, c.P);
+        for (int i = 0; i < 3; ++i) c.P[i] = c.P[i] + T[9 + i];
+        for (int i = 0; i < 3; ++i) dm[i] = c.P[i] - M[9 + i];
+        for (int i = 0; i < 3; ++i) pm[i] = (M[i] * dm[0] + M[3 + i] * dm[1]) + M[6 + i] * dm[2];
+        const double u = floor(L.fx * pm[0] / pm[2] + L.cx);
+        const double v = floor(L.fy * pm[1] / pm[2] + L.cy);
+        c.ok = c.ok && pm[2] > 0.0 && u >= 0.0 && u < (double)L.W && v >= 0.0 && v < (double)L.H;
+        c.ui = c.ok ? (int)u : 0;
+        c.vi = c.ok ? (int)v : 0;
+        const int64_t q = (int64_t)c.vi * L.W + c.ui;
+        c.Dm = L.Dm[q];
+        c.n0 = L.Nm[3 * q];
+        c.n1 = L.Nm[3 * q + 1];
+        c.n2 = L.Nm[3 * q + 2];
+        return c;
+    };
+    auto add_pair = [&](const IcpCand& c) {
+        const double Dmq = c.Dm, nm[3] = {c.n0, c.n1, c.n2};
+        if (!(c.ok && Dmq > 0.0 && dot3(nm, nm) > 0.0)) return;
+        const double Vm[3] = {Dmq * rays.x(L, c.ui), Dmq * rays.y(L, c.vi), Dmq};
+        double Q[3], n[3], m[3], dd[3], cr[3];
+        mat_vec(M, Vm, Q);
+        for (int i = 0; i < 3; ++i) Q[i] = Q[i] + M[9 + i];
+        mat_vec(M, nm, n);
+        mat_vec(T, c.Nn, m);
+        for (int i = 0; i < 3; ++i) dd[i] = c.P[i] - Q[i];
+        cross3(m, n, cr);
+        if (!(dot3(dd, dd) <= dist * dist && dot3(cr, cr) <= (sin_a * sin_a) * (dot3(m, m) * dot3(n, n)))) return;
+        const double r = dot3(dd, n);
+        double J[6];
+        cross3(c.P, n, J);
+        J[3] = n[0];
+        J[4] = n[1];
+        J[5] = n[2];
+        int k = 0;
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+#pragma unroll
+            for (int j = i; j < 6; ++j, ++k) t[k] = __builtin_fma(J[i], J[j], t[k]);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) t[21 + i] = __builtin_fma(J[i], r, t[21 + i]);
+        t[27] = __builtin_fma(r, r, t[27]);
+        t[28] += 1.0;
+    };
+    if (u0 < u1) {
+        Row rw = load_row(u0);
+        IcpCand c = candidate(rw);
+        rw = load_row(min(u0 + 1, u1 - 1));
+        for (int u = u0; u < u1; ++u) {
+            IcpCand nx = candidate(rw);   // pixel u + 1 (past the end: dropped)
+            rw = load_row(min(u + 2, u1 - 1));
+            add_pair(c);
+            c = nx;
         }
-    for (int i = 0; i < 6; ++i) bb[i] = tot[21 + i];
-    if (trace) {
-        for (int i = 0; i < 12; ++i) trace[i] = T[i];
-        trace[12] = tot[27];
-        trace[13] = tot[28];
-        for (int i = 0; i < 27; ++i) trace[14 + i] = tot[i];
-        for (int i = 41; i < kIcpTerms + 19; ++i) trace[i] = 0.0;
     }
-    // Cholesky A = L L^T
-    double Lc[36];
-    bool good = tot[28] >= 6.0;
-    for (int i = 0; i < 6 && good; ++i)
-        for (int j = 0; j <= i; ++j) {
-            double acc = A[6 * i + j];
-            for (int m = 0; m < j; ++m) acc -= Lc[6 * i + m] * Lc[6 * j + m];
-            if (i == j) {
-                if (!(acc > 0.0)) {
-                    good = false;
-                    break;
-                }
-                Lc[6 * i + i] = sqrt(acc);
-            } else {
-                Lc[6 * i + j] = acc / Lc[6 * j + j];
-            }
-        }
-    if (!good) return;
-    double yv[6], xi[6];
-    for (int i = 0; i < 6; ++i) {
-        double acc = bb[i];
-        for (int m = 0; m < i; ++m) acc -= Lc[6 * i + m] * yv[m];
-        yv[i] = acc / Lc[6 * i + i];
+    // fixed-order reduction: the wave's reduce-scatter, then the waves in order
+    const double s = reduce_scatter32(t, lane);
+    if ((lane & 1) == 0) red[wv][icp_slot(lane)] = s;
+    __syncthreads();
+    if (threadIdx.x < kIcpTerms) {
+        double o = 0.0;
+#pragma unroll
+        for (int w = 0; w < kIcpThreads / 64; ++w) o += red[w][threadIdx.x];
+        partials[(int64_t)blockIdx.x * kIcpTerms + threadIdx.x] = o;
     }
-    for (int i = 5; i >= 0; --i) {
-        double acc = yv[i];
-        for (int m = i + 1; m < 6; ++m) acc -= Lc[6 * m + i] * xi[m];
-        xi[i] = acc / Lc[6 * i + i];
-    }
-    for (int i = 0; i < 6; ++i) xi[i] = -xi[i];
-    double dR[9], dt[3];
-    se3_exp(xi, dR, dt);
-    double Rn[9], tn[3];
-    for (int i = 0; i < 3; ++i) {
-        for (int j = 0; j < 3; ++j) Rn[3 * i + j] = (dR[3 * i] * T[j] + dR[3 * i + 1] * T[3 + j]) + dR[3 * i + 2] * T[6 + j];
-        tn[i] = ((dR[3 * i] * T[9] + dR[3 * i + 1] * T[10]) + dR[3 * i + 2] * T[11]) + dt[i];
-    }
-    for (int i = 0; i < 9; ++i) T[i] = Rn[i];
-    for (int i = 0; i < 3; ++i) T[9 + i] = tn[i];
+}
+
+// The pose after the last pass (one workgroup).
+__global__ __launch_bounds__(kIcpThreads) void k_icp_finish(IcpPrev prev, double* __restrict__ T_out) {
+    __shared__ double red[kIcpThreads / 64][32];
+    __shared__ double sT[12];
+    icp_next_pose(prev, true, red, sT);
+    if (threadIdx.x < 12) T_out[threadIdx.x] = sT[threadIdx.x];
 }
 
 }  // namespace rtg

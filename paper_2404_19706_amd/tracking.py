@@ -42,7 +42,8 @@ def icp(cam, depth_in, depth_model, normal_model, pose_model, pose_init, prm=Non
     ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
     pose = torch.empty(12, dtype=torch.float64, device="cuda")
     n_it = sum(int(prm.iters[k]) for k in range(prm.levels))
-    tr = torch.zeros((max(n_it, 1), 48), dtype=torch.float64, device="cuda") if trace else None
+    # (the call writes every entry of a row per iteration)
+    tr = (torch.empty if n_it else torch.zeros)((max(n_it, 1), 48), dtype=torch.float64, device="cuda") if trace else None
     check(lib().rtg_icp(ctypes.byref(intr), ctypes.byref(prm), _p(depth_in), _p(depth_model), _p(normal_model),
                         _p(pose_model), _p(pose_init), _p(pose), _p(tr), _p(ws), nb,
                         ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)), "rtg_icp")

@@ -119,3 +119,39 @@ def test_tracking_on_rendered_depth_and_normals():
     err = np.abs(pose.cpu().numpy() - pose_true).max()
     print("tracking error %.2e (start %.2e)" % (err, err0))
     assert err < 0.1 * err0
+
+
+@pytest.mark.parametrize("w,h,levels", [(2, 2, 1), (16, 16, 1), (65, 7, 1), (45, 23, 2), (64, 40, 3), (131, 97, 3),
+                                        (130, 66, 2), (517, 389, 3)])
+def test_icp_pass_edges(w, h, levels):
+    """Strips, rows and partial-row places at their edges: a single
+    workgroup (images of a few hundred pixels), widths one off a strip of 64
+    columns, odd sizes in the pyramid, and too few pairs for an update; every
+    iteration's sums from the pose it used, as above."""
+    from paper_2404_19706_amd import tracking
+    cam = small_cam(w, h, 0.9 * w)
+    pose_m = np.concatenate([np.eye(3).ravel(), [0.1, 0.2, 0.0]])
+    Dm, Nm = corner_maps(cam, pose_m)
+    Din, _ = corner_maps(cam, _motion(pose_m, [0.004, -0.003, 0.002, 0.006, -0.005, 0.004]))
+    iters = (3, 2, 2)
+    start = _t(pose_m)
+    pose, trace = tracking.icp(cam, _t(Din), _t(Dm), _t(Nm), _t(pose_m), start, tracking.icp_params(levels, iters),
+                               trace=True)
+    torch.cuda.synchronize()
+    trace = trace.cpu().numpy()
+    assert np.array_equal(start.cpu().numpy(), pose_m)
+    lv = oicp.levels_of(cam, Din, Dm, Nm, levels)
+    row = 0
+    for l in range(levels - 1, -1, -1):
+        lin, lmo, K = lv[l]
+        for _ in range(iters[l]):
+            T = trace[row, :12]
+            ok, p, q, n = oicp.associate(lin, lmo, K, T, pose_m, 0.1, 0.3420201433256687)
+            A, b, err, cnt = oicp.normal_equations(ok, p, q, n)
+            assert int(trace[row, 13]) == cnt, (row, trace[row, 13], cnt)
+            iu = np.triu_indices(6)
+            np.testing.assert_allclose(trace[row, 14:35], A[iu], rtol=1e-10, atol=1e-9 * np.abs(A).max())
+            np.testing.assert_allclose(trace[row, 35:41], b, rtol=1e-9, atol=1e-9 * np.abs(b).max() + 1e-12)
+            assert not trace[row, 41:].any()
+            row += 1
+    assert row == len(trace) and np.isfinite(pose.cpu().numpy()).all()
