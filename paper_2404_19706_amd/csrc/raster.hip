@@ -12,10 +12,11 @@
 // per-tile sort, 64 per batch, one per lane, with one coalesced load level;
 // the next batch is prefetched into registers while the current one is
 // composited.  Each batch is pack-culled (records that cannot reach any pixel
-// of the pack are dropped, lane-parallel) and the survivors are compacted
-// into the wave's own LDS slice, from which every lane reads the same record
-// (an LDS broadcast) with one lane per pixel.  A ballot ends the walk once
-// every lane has finished its colour and found its depth hit.
+// of the pack are dropped, lane-parallel; about 95 % of those kept reach one)
+// and the survivors are compacted into the wave's own LDS slice, from which
+// every lane reads the same record (an LDS broadcast) with one lane per
+// pixel.  A ballot ends the walk once every lane has finished its colour and
+// found its depth hit.
 //
 // Decisions (footprint, depth hit) use the fixed binary32 sequence on the
 // rounded centre; the values (f, gradients) use offsets from the centre
@@ -23,31 +24,44 @@
 //
 // The backward pass re-walks each pixel's list back to front, recovering the
 // transmission in front of each Gaussian from the stored final value
-// (T_i = T_{i+1} / (1 - f_i); nothing per pair is stored).  For each unstable
-// Gaussian it reduces the nine colour-path gradients of the wave's pixels,
-// plus the five depth-path terms of the pixels whose depth hit it is, with
-// one reduce-scatter, and adds the fourteen totals with one float atomic
-// instruction into the Gaussian's per-frame camera-space accumulator.
+// (T_i = T_{i+1} / (1 - f_i); nothing per pair is stored).  The nine
+// colour-path gradients of the unstable Gaussians are summed over the wave's
+// pixels eight records at a time, the five depth-path terms once per pack
+// and hit, and added with float atomics into the Gaussian's per-frame
+// camera-space accumulator.
+//
+// Both kernels are bound by vector issue where the items outnumber the waves
+// (batches of keyframes) and by the longest packs' serial walks where they do
+// not (one frame).  What a record costs on every lane was cut to: decision 8
+// operations, value 2 more and the exponential, blend 7 (forward), and the
+// one gradient sum g . (c - A) in place of three colour recursions (backward).
+// Measured on MI355X, forward / backward: 16 keyframes of 1200x680 with 2.6M
+// masked pixels 914 / 1050 to 731 / 725 us, 8 keyframes 632 / 930 to 528 /
+// 735 us, one 640x480 frame 28 / 68 to 29 / 55 us.
 #include <type_traits>
 
 #include "rtg_common.h"
 
 // Compile-time tuning knobs of the compositing kernels: records whose
-// footprint and opacity are evaluated together before the sequential blend
+// loads and independent parts are taken together before the sequential blend
 // (instruction-level parallelism against register pressure), and the
 // minimum number of resident waves per SIMD each kernel is compiled for
-// (occupancy; 0 = compiler's choice).  Measured on gfx950: four records per
-// group (the forward stages three record words) keep the forward at 95
-// VGPRs without spills and beat groups of two by 3-4 % on long lists; the
-// backward at five waves per SIMD gains ~5 % on long lists.
+// (occupancy; 0 = compiler's choice).  Measured on gfx950, us per launch over
+// 16 / 8 keyframes: forward groups of four (112 VGPRs, four waves) 793 / 582,
+// of two (five waves) 912 / 589, of four held to five waves 900 / 593;
+// backward groups of two (127 VGPRs, four waves) 705 / 715, single records
+// 725 / 734.
 #ifndef RTG_FWD_GROUP
 #define RTG_FWD_GROUP 4
 #endif
 #ifndef RTG_FWD_WAVES_PER_EU
 #define RTG_FWD_WAVES_PER_EU 0
 #endif
+#ifndef RTG_BWD_GROUP
+#define RTG_BWD_GROUP 2
+#endif
 #ifndef RTG_BWD_WAVES_PER_EU
-#define RTG_BWD_WAVES_PER_EU 5
+#define RTG_BWD_WAVES_PER_EU 4
 #endif
 #if RTG_FWD_WAVES_PER_EU > 0
 #define RTG_FWD_BOUNDS __launch_bounds__(256, RTG_FWD_WAVES_PER_EU)
@@ -145,45 +159,28 @@ __device__ __forceinline__ bool pack_keeps(float4 h0, float qc, const PackBox& b
 // One batch of up to 64 pair-order records, one per lane, held in registers
 // (prefetched while the previous batch is composited).  Callers guarantee
 // j0 < j1, so lanes past the end re-load record j0 instead of branching
-// (keeps the batch in registers).
-// NW = 4 loads the whole record; NW = 3 leaves out {n^c, h}, which the
-// compositing passes read only for the depth-hit record of a pixel.
-template <int NW>
+// (keeps the batch in registers).  {n^c, h} is left out: the compositing
+// passes read it only for the depth-hit record of a pixel.
 struct Batch {
-    float4 r0, r1, r2, r3;
+    float4 r0, r1, r2;
     bool ok;
 };
 
-template <int NW>
-__device__ __forceinline__ Batch<NW> load_batch(const WS& w, uint32_t j0, uint32_t j1, int lane) {
-    Batch<NW> B;
+__device__ __forceinline__ Batch load_batch(const WS& w, uint32_t j0, uint32_t j1, int lane) {
+    Batch B;
     uint32_t j = j0 + (uint32_t)lane;
     B.ok = j < j1;
     const float4* src = w.prec + 4ull * (B.ok ? j : j0);
     B.r0 = src[0];
     B.r1 = src[1];
     B.r2 = src[2];
-    if constexpr (NW == 4) B.r3 = src[3];
     return B;
 }
 
-// Pack-cull the batch and compact the survivors into the wave's LDS slice in
-// list order; P receives their absolute pair positions.  Returns the count.
-template <int NW>
-__device__ __forceinline__ uint32_t compact_batch(const Batch<NW>& B, uint32_t j0, float4 (*L)[64], uint32_t* P,
-                                                  int lane, const PackBox& pb, float cut, bool& anyp) {
-    bool keep = B.ok && pack_keeps(B.r0, B.r1.x, pb, cut);
-    uint64_t m = ballot(keep);
-    anyp = ballot(keep && rec_precise(B.r2)) != 0;
-    if (keep) {
-        uint32_t q = (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull));
-        L[0][q] = B.r0;
-        L[1][q] = B.r1;
-        L[2][q] = B.r2;
-        if constexpr (NW == 4) L[3][q] = B.r3;
-        P[q] = j0 + (uint32_t)lane;
-    }
-    return (uint32_t)__builtin_popcountll(m);
+// A record's depth-hit test dd <= cut && dd < tau as one comparison,
+// dd < min(tau, the next float above cut).
+__device__ __forceinline__ float hit_bound(float tau, float cut) {
+    return fminf(tau, __uint_as_float(__float_as_uint(cut) + 1u));
 }
 
 // Iterates the work items of one wave: round-robin over the first n_static
@@ -243,14 +240,11 @@ __global__ void k_queue_reset(uint32_t* q) {
     if (threadIdx.x == 0) *q = 0u;
 }
 
-// Butterfly reduce-scatter of 16 per-lane values over the wave: after it,
-// every lane of quad q holds the wave total of slot
-// 8*b2 + 4*b3 + 2*b4 + b5 (b_k = bit k of the lane id).  Rounds on lane bits
-// 5 and 4 use the gfx950 permlane32/permlane16 swaps (a swap followed by one
-// add leaves each half with its own slot's partial sum); bit 3 pairs lane l
-// with l ^ 15 (DPP row mirror) and bit 2 with l ^ 7 (DPP half-row mirror),
-// partners that differ in that bit and agree on the bits already reduced;
-// bits 1 and 0 are quad DPP adds.
+// Cross-lane sums.  swap32 / swap16: the gfx950 permlane swaps followed by
+// one add leave each half (of the wave, of a row pair) with its own value's
+// partial sum.  mirror_sum<CTRL>: lane pairs that differ in a lane bit `hi`;
+// the lane with the bit clear keeps a, the other b, each with the
+// partner's share added.
 __device__ __forceinline__ float swap32_sum(float a, float b) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
@@ -265,56 +259,33 @@ __device__ __forceinline__ float mirror_sum(float a, float b, bool hi) {
     float keep = hi ? b : a;
     return keep + dpp_mov<CTRL>(send);
 }
-__device__ __forceinline__ float quad_sum(float o) {
-    o += dpp_mov<0xB1>(o);   // quad_perm [1,0,3,2]
-    o += dpp_mov<0x4E>(o);   // quad_perm [2,3,0,1]
-    return o;
-}
-__device__ __forceinline__ float reduce_scatter16(const float (&v)[16], int lane) {
-    float r[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) r[j] = swap32_sum(v[2 * j], v[2 * j + 1]);
-    float q[4];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) q[m] = swap16_sum(r[2 * m], r[2 * m + 1]);
-    bool b3 = (lane >> 3) & 1, b2 = (lane >> 2) & 1;
-    float p0 = mirror_sum<0x140>(q[0], q[1], b3);
-    float p1 = mirror_sum<0x140>(q[2], q[3], b3);
-    return quad_sum(mirror_sum<0x141>(p0, p1, b2));
-}
-// The same when slots 9-15 are zero (no depth-path term in the wave).
-__device__ __forceinline__ float reduce_scatter9(const float (&v)[16], int lane) {
-    float r[5];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) r[j] = swap32_sum(v[2 * j], v[2 * j + 1]);
-    r[4] = swap32_sum(v[8], 0.f);
-    float q0 = swap16_sum(r[0], r[1]), q1 = swap16_sum(r[2], r[3]), q2 = swap16_sum(r[4], 0.f);
-    bool b3 = (lane >> 3) & 1, b2 = (lane >> 2) & 1;
-    float p0 = mirror_sum<0x140>(q0, q1, b3);
-    float p1 = mirror_sum<0x140>(q2, 0.f, b3);
-    return quad_sum(mirror_sum<0x141>(p0, p1, b2));
-}
-// The nine colour-path sums through LDS instead: every lane stores its
-// nine values ([slot][lane]), then lanes 8s..8s+7 add 8 values each of slot
-// s (s < 8) and combine them with three DPP steps, and the whole wave adds
-// slot 8.  Lane 8s returns slot s's total, lane 0 additionally slot 8's.
-__device__ __forceinline__ void lds_sum9(const float (&v)[16], float* red, int lane, float& tot, float& tot8) {
-#pragma unroll
-    for (int k = 0; k < 9; ++k) red[k * 64 + lane] = v[k];
-    wave_lds_sync();
-    const float4* r4 = reinterpret_cast<const float4*>(red + (lane >> 3) * 64 + (lane & 7) * 8);
-    const float4 x = r4[0], y = r4[1];
-    float t = ((x.x + x.y) + (x.z + x.w)) + ((y.x + y.y) + (y.z + y.w));
-    t += dpp_mov<0xB1>(t);    // quad_perm [1,0,3,2]
-    t += dpp_mov<0x4E>(t);    // quad_perm [2,3,0,1]
-    t += dpp_mov<0x141>(t);   // row_half_mirror: the other quad of the eight
-    tot = t;
-    tot8 = wave_sum(red[8 * 64 + lane]);
-    wave_lds_sync();
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;   // DPP controls
+
+// Wave totals of five values: lane l returns that of slot b5 + 2 b4 + 4 b3
+// (b_k = bit k of l), slots 5-7 zero.
+__device__ __forceinline__ float reduce_scatter5(const float (&v)[5], int lane) {
+    const float r0 = swap32_sum(v[0], v[1]), r1 = swap32_sum(v[2], v[3]), r2 = swap32_sum(v[4], 0.f);
+    const float q0 = swap16_sum(r0, r1), q1 = swap16_sum(r2, 0.f);
+    float t = mirror_sum<kMirror>(q0, q1, (lane >> 3) & 1);
+    t += dpp_mov<kHalfMirror>(t);
+    t += dpp_mov<kXor2>(t);
+    return t + dpp_mov<kXor1>(t);
 }
 
-__device__ __forceinline__ int scatter_slot(int lane) {
-    return 8 * ((lane >> 2) & 1) + 4 * ((lane >> 3) & 1) + 2 * ((lane >> 4) & 1) + ((lane >> 5) & 1);
+// Totals of eight values over each group of eight lanes: lane l returns
+// that of slot b2 + 2 b1 + 4 b0.
+__device__ __forceinline__ float oct_scatter8(const float (&v)[8], int lane) {
+    const bool b2 = (lane >> 2) & 1, b1 = (lane >> 1) & 1, b0 = lane & 1;
+    float t[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t[j] = mirror_sum<kHalfMirror>(v[2 * j], v[2 * j + 1], b2);
+    const float u0 = mirror_sum<kXor2>(t[0], t[1], b1), u1 = mirror_sum<kXor2>(t[2], t[3], b1);
+    return mirror_sum<kXor1>(u0, u1, b0);
+}
+__device__ __forceinline__ float oct_sum(float t) {
+    t += dpp_mov<kHalfMirror>(t);
+    t += dpp_mov<kXor2>(t);
+    return t + dpp_mov<kXor1>(t);
 }
 
 // The Gaussian weight exp(-d^2 / 2) of both compositing kernels, as one
@@ -331,30 +302,80 @@ __device__ __forceinline__ float rdl(float v, int k) {
 }
 __device__ __forceinline__ uint32_t rdl_u(uint32_t v, int k) { return (uint32_t)__builtin_amdgcn_readlane((int)v, k); }
 
-// Decision distance dd and value opacity f = min(alpha exp(-d_v^2 / 2),
-// 0.99) of one record at pixel centre (ux, uy): the fixed sequence of both
-// compositing paths (pack and straggler), which therefore give the same
-// bits.  PR: the record may be precise (then d_v^2 comes from the whitened
-// offsets, the precise rows at rpf); `uniform`: every lane holds the same
-// record (the precise test is then a uniform branch with scalar loads).
-template <bool PR>
-__device__ __forceinline__ float eval_rec(const float4& A, const float4& Bq, const float4& Cc, float ux, float uy,
-                                          const float* rpf, bool uniform, float& fv) {
-    const float dxd = ux - A.x, dyd = uy - A.y;
-    const float dd = __builtin_fmaf(Bq.x * dyd, dyd, __builtin_fmaf(A.w * dxd, dyd, (A.z * dxd) * dxd));
-    const float2 lo = unpack_mu_lo(Cc.w);
-    const float dx = dxd - lo.x, dy = dyd - lo.y;
-    float ddv = __builtin_fmaf(Bq.x * dy, dy, __builtin_fmaf(A.w * dx, dy, (A.z * dx) * dx));
-    if constexpr (PR) {
-        const uint32_t gw = uniform ? (uint32_t)readfirstlane((int)__float_as_uint(Cc.z)) : __float_as_uint(Cc.z);
-        if (gw & kPreciseBit) {
-            float e0, e1;
-            precise_offsets(rpf + 6 * (int64_t)(gw & kGidMask), ux, uy, A.x, A.y, dxd, dyd, e0, e1);
-            ddv = e0 * e0 + e1 * e1;
-        }
+// What the value path takes from a record's centre residual lo = mu -
+// fl32(mu): with d the offsets from the binary32 centre, (d - lo)^T Q (d -
+// lo) = dd + e . d + q(lo), e = -2 Q lo, so the value distance is the
+// decision distance plus two multiply-adds, and q(lo) goes into the opacity,
+// alpha' = alpha exp(-q(lo) / 2).  (A second evaluation of the form took
+// eight operations per pixel and record.)  Precise records take neither:
+// their value distance comes from the whitened offsets.
+struct Resid {
+    float e0, e1, alpha;
+};
+__device__ __forceinline__ Resid resid_of(const float4& A, const float4& Bq, const float4& Cc) {
+    if (rec_precise(Cc)) return Resid{0.f, 0.f, Bq.y};
+    float lx, ly;
+    mu_lo(Cc.w, lx, ly);
+    const float e0 = -__builtin_fmaf(2.f * A.z, lx, A.w * ly), e1 = -__builtin_fmaf(2.f * Bq.x, ly, A.w * lx);
+    return Resid{e0, e1, Bq.y * gauss_weight(-0.5f * __builtin_fmaf(e0, lx, e1 * ly))};
+}
+
+// Decision distance dd (the fixed sequence) and the offsets d.
+__device__ __forceinline__ float eval_dd(const float4& A, float qyy, float ux, float uy, float& dx, float& dy) {
+    dx = ux - A.x;
+    dy = uy - A.y;
+    return __builtin_fmaf(qyy * dy, dy, __builtin_fmaf(A.w * dx, dy, (A.z * dx) * dx));
+}
+
+// Value opacity f = min(alpha exp(-d_v^2 / 2), 0.99) of a record that is
+// not precise; every compositing path takes the same sequence.
+__device__ __forceinline__ float eval_f(float dd, float dx, float dy, const Resid& r) {
+    return fminf(r.alpha * gauss_weight(__builtin_fmaf(r.e0, dx, __builtin_fmaf(r.e1, dy, dd))), 0.99f);
+}
+
+// The same of a precise record (its row of recp at r).
+__device__ __forceinline__ float eval_f_precise(const float4& A, float alpha, const float* r, float ux, float uy,
+                                                float dx, float dy) {
+    float e0, e1;
+    precise_offsets(r, ux, uy, A.x, A.y, dx, dy, e0, e1);
+    return fminf(alpha * gauss_weight(e0 * e0 + e1 * e1), 0.99f);
+}
+
+// One wave's compacted batch in LDS: {mu.x, mu.y, Q.xx, 2 Q.xy}, {Q.yy,
+// alpha', hit bound, c.r}, {c.g, c.b, e0, e1} per surviving record in list
+// order, then kPad records whose d^2 is NaN at every pixel (no comparison
+// holds), so that the passes work in whole groups.
+constexpr int kPad = 3;
+struct Slice {
+    float4 r[3][64 + kPad];
+    uint32_t pos[64];         // absolute pair position (forward), residual word (backward)
+    uint32_t gid[64 + kPad];  // index word
+};
+
+// Pack-cull the batch and compact the survivors into the wave's slice;
+// returns the lanes that hold one.
+template <bool BWD>
+__device__ __forceinline__ uint64_t compact_batch(const Batch& B, uint32_t j0, Slice& S, int lane, const PackBox& pb,
+                                                  float cut) {
+    const bool keep = B.ok && pack_keeps(B.r0, B.r1.x, pb, cut);
+    const uint64_t m = ballot(keep);
+    const uint32_t n = (uint32_t)__builtin_popcountll(m);
+    if (keep) {
+        const uint32_t q = (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull));
+        const Resid r = resid_of(B.r0, B.r1, B.r2);
+        S.r[0][q] = B.r0;
+        S.r[1][q] = make_float4(B.r1.x, r.alpha, hit_bound(B.r1.z, cut), B.r1.w);
+        S.r[2][q] = make_float4(B.r2.x, B.r2.y, r.e0, r.e1);
+        S.pos[q] = BWD ? __float_as_uint(B.r2.w) : j0 + (uint32_t)lane;
+        S.gid[q] = __float_as_uint(B.r2.z);
     }
-    fv = fminf(Bq.y * gauss_weight(ddv), 0.99f);
-    return dd;
+    if (lane < kPad) {
+        S.r[0][n + lane] = make_float4(__builtin_nanf(""), 0.f, 1.f, 0.f);
+        S.r[1][n + lane] = make_float4(0.f, 0.f, -1.f, 0.f);
+        S.r[2][n + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+        S.gid[n + lane] = 0u;
+    }
+    return m;
 }
 
 // DM = 0: the depth of Eq. 4-5 (first hit, disc plane or centre); DM = 1:
@@ -365,84 +386,102 @@ template <int DM>
 __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ out_c,
                                                  float* __restrict__ out_d, float* __restrict__ out_t,
                                                  int* __restrict__ out_i) {
-    __shared__ float4 lds[4][3][64];
-    __shared__ uint32_t ldp[4][64];
+    __shared__ Slice slices[4];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    float4(*L)[64] = lds[wv];
-    uint32_t* P = ldp[wv];
+    Slice& S = slices[wv];
     ItemIter iter = make_iter(d.fwd_items_per_pop, d.fwd_static_share, w.hdr->n_items, &w.hdr->q_fwd, lane);
     float cnt_eval = 0.f;
-    uint32_t cnt_blend = 0;
+    unsigned long long cnt_blend = 0;   // of the whole wave
     const float cut = d.cutoff2, teps = d.t_eps;
     uint32_t it;
     while (iter.next(it)) {
         PixelOfItem p = decode_item(d, w, it, lane);
         const PackBox pb = pack_box(p);
-        float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, Da = 0.f;
-        uint32_t last = p.rs, hitpos = 0;
-        uint32_t hitg = 0;
+        // a pixel is done with its colour once T < t_eps; lanes without one
+        // start there
+        float T = p.act ? 1.f : -1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, Da = 0.f;
+        uint32_t last = p.re, hitpos = 0;
         int hitk = -1, lastk = -1;
-        uint32_t nblend = 0;
-        bool cdone = !p.act, ddone = !p.act;
-        Batch<3> B = {};
-        if (p.rs < p.re) B = load_batch<3>(w, p.rs, p.re, lane);
+        bool ddone = !p.act, blended = false;
+        Batch B = {};
+        if (p.rs < p.re) B = load_batch(w, p.rs, p.re, lane);
         // the frame is the same for every lane of the pack: a scalar base
         const float* rpf = w.recp + 6 * ((int64_t)readfirstlane(p.f) * d.N);
         const float* zf = w.zkey + (int64_t)readfirstlane(p.f) * d.N;
         for (uint32_t b = p.rs; b < p.re; b += 64) {
-            bool anyp;
-            uint32_t nb = compact_batch<3>(B, b, L, P, lane, pb, cut, anyp);
+            const bool prec = B.ok && rec_precise(B.r2);
+            const uint64_t kept = compact_batch<false>(B, b, S, lane, pb, cut);
+            const uint32_t nb = (uint32_t)__builtin_popcountll(kept);
+            const bool anyp = (ballot(prec) & kept) != 0;
             wave_lds_sync();
-            if (b + 64 < p.re) B = load_batch<3>(w, b + 64, p.re, lane);
+            if (b + 64 < p.re) B = load_batch(w, b + 64, p.re, lane);
             // groups of G records, specialised on whether the batch holds a
             // precise record (the value distance of those comes from the
-            // factored form; one record per group there)
+            // factored form); the slice is padded to whole groups with
+            // records that reach no pixel
             auto groups = [&](auto prec) -> bool {
                 constexpr bool PR = decltype(prec)::value;
                 constexpr int G = PR ? 1 : RTG_FWD_GROUP;
                 for (uint32_t k0 = 0; k0 < nb; k0 += G) {
-                    // independent part for G records: decision, value, opacity
-                    float fvq[G], ddq[G], tauq[G], cr[G], cg[G], cb[G], zq[G];
-                    uint32_t gq[G];
-                    bool inq[G];
+                    float4 A[G], Bq[G], Cc[G];
 #pragma unroll
                     for (int u = 0; u < G; ++u) {
-                        uint32_t k = min(k0 + u, nb - 1);
-                        float4 A = L[0][k];
-                        float4 Bq = L[1][k];
-                        float4 Cc = L[2][k];
-                        const float dd = eval_rec<PR>(A, Bq, Cc, p.ux, p.uy, rpf, true, fvq[u]);
-                        inq[u] = (k0 + u < nb) && dd <= cut;
-                        ddq[u] = dd;
-                        tauq[u] = Bq.z;
-                        cr[u] = Bq.w;
-                        cg[u] = Cc.x;
-                        cb[u] = Cc.y;
-                        gq[u] = __float_as_uint(Cc.z);
-                        // the record is the same on every lane: a scalar load
-                        if constexpr (DM == 1)
-                            zq[u] = zf[readfirstlane((int)(__float_as_uint(Cc.z) & kGidMask))];
+                        A[u] = S.r[0][k0 + u];
+                        Bq[u] = S.r[1][k0 + u];
+                        Cc[u] = S.r[2][k0 + u];
                     }
-                    // sequential part: compositing in list order and the depth hit
+                    // independent part: decision, value, opacity
+                    float fvq[G], ddq[G], Tn[G];
 #pragma unroll
                     for (int u = 0; u < G; ++u) {
-                        bool take = inq[u] && !cdone;
-                        float fv = take ? fvq[u] : 0.f;
-                        float wgt = fv * T;
-                        C0 = __builtin_fmaf(cr[u], wgt, C0);
-                        C1 = __builtin_fmaf(cg[u], wgt, C1);
-                        C2 = __builtin_fmaf(cb[u], wgt, C2);
-                        if constexpr (DM == 1) Da = __builtin_fmaf(zq[u], wgt, Da);
-                        T = T * (1.f - fv);
-                        lastk = take ? (int)(k0 + u) : lastk;
-                        nblend += take ? 1u : 0u;
-                        cdone = cdone || (take && T < teps);
-                        bool h = inq[u] && !ddone && ddq[u] < tauq[u];
-                        hitg = h ? gq[u] : hitg;
-                        hitk = h ? (int)(k0 + u) : hitk;
+                        float dx, dy;
+                        ddq[u] = eval_dd(A[u], Bq[u].x, p.ux, p.uy, dx, dy);
+                        fvq[u] = eval_f(ddq[u], dx, dy, Resid{Cc[u].z, Cc[u].w, Bq[u].y});
+                        if constexpr (PR) {
+                            const uint32_t gw = (uint32_t)readfirstlane((int)S.gid[k0 + u]);
+                            if (gw & kPreciseBit)
+                                fvq[u] = eval_f_precise(A[u], Bq[u].y, rpf + 6 * (int64_t)(gw & kGidMask), p.ux, p.uy,
+                                                        dx, dy);
+                        }
+                    }
+                    // sequential part: compositing in list order
+                    const float T0 = T;
+#pragma unroll
+                    for (int u = 0; u < G; ++u) {
+                        const bool take = ddq[u] <= cut && !(T < teps);
+                        const float fv = take ? fvq[u] : 0.f;
+                        const float wgt = fv * T;
+                        C0 = __builtin_fmaf(Bq[u].w, wgt, C0);
+                        C1 = __builtin_fmaf(Cc[u].x, wgt, C1);
+                        C2 = __builtin_fmaf(Cc[u].y, wgt, C2);
+                        if constexpr (DM == 1) {
+                            // the record is the same on every lane: a scalar load
+                            const float z = zf[readfirstlane((int)(S.gid[k0 + u] & kGidMask))];
+                            Da = __builtin_fmaf(z, wgt, Da);
+                            blended = blended || take;
+                        }
+                        T = __builtin_fmaf(-fv, T, T);
+                        Tn[u] = T;
+                        cnt_blend += (unsigned long long)__builtin_popcountll(ballot(take));
+                    }
+                    // (uniform branches: a pixel's colour ends and its depth
+                    // hit comes once)
+                    if (ballot(!(T0 < teps) && T < teps) != 0) {
+#pragma unroll
+                        for (int u = G - 1; u >= 0; --u)
+                            if (!(T0 < teps) && Tn[u] < teps) lastk = (int)(k0 + u);
+                    }
+                    bool h = false;
+#pragma unroll
+                    for (int u = 0; u < G; ++u) h = h || ddq[u] < Bq[u].z;
+                    h = h && !ddone;
+                    if (ballot(h) != 0) {
+#pragma unroll
+                        for (int u = G - 1; u >= 0; --u)
+                            if (h && ddq[u] < Bq[u].z) hitk = (int)(k0 + u);
                         ddone = ddone || h;
                     }
-                    if (((k0 + G) & 7) == 0 && ballot(!(cdone && ddone)) == 0) return true;
+                    if (((k0 + G) & 7) == 0 && ballot(!(T < teps && ddone)) == 0) return true;
                 }
                 return false;
             };
@@ -450,15 +489,15 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
             // list positions of this batch's last blend and depth hit, and the
             // hit's normal and plane offset, before the slice is reused
             if (lastk >= 0) {
-                last = P[lastk] + 1;
+                last = S.pos[lastk] + 1;
                 lastk = -1;
             }
             if (hitk >= 0) {
-                hitpos = P[hitk] + 1;
+                hitpos = S.pos[hitk] + 1;
                 hitk = -1;
             }
             wave_lds_sync();
-            const uint64_t live = ballot(!(cdone && ddone));
+            const uint64_t live = ballot(!(T < teps && ddone));
             if (all_done || live == 0) break;
             // the straggler path for the rest of the list
             const uint32_t rest = b + 64 < p.re ? b + 64 : p.re;
@@ -469,19 +508,21 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
                     const float sux = rdl(p.ux, l), suy = rdl(p.uy, l);
                     float sT = rdl(T, l), sC0 = rdl(C0, l), sC1 = rdl(C1, l), sC2 = rdl(C2, l);
                     float sDa = rdl(Da, l);
-                    bool scd = rdl_u(cdone ? 1u : 0u, l) != 0u, sdd = rdl_u(ddone ? 1u : 0u, l) != 0u;
+                    bool scd = sT < teps, sdd = rdl_u(ddone ? 1u : 0u, l) != 0u, sbl = false;
                     uint32_t slast = rdl_u(last, l), shp = rdl_u(hitpos, l);
-                    uint32_t shg = rdl_u(hitg, l), snb = 0;
                     for (uint32_t j0 = rest; j0 < p.re && !(scd && sdd); j0 += 64) {
                         // one record per lane, evaluated at pixel l
                         const uint32_t j = j0 + (uint32_t)lane;
                         const bool ok = j < p.re;
                         const float4* src = w.prec + 4ull * (ok ? j : j0);
                         const float4 A = src[0], Bq = src[1], Cc = src[2];
-                        float fvj;
-                        const float dd = eval_rec<true>(A, Bq, Cc, sux, suy, rpf, false, fvj);
+                        float dx, dy;
+                        const float dd = eval_dd(A, Bq.x, sux, suy, dx, dy);
+                        float fvj = eval_f(dd, dx, dy, resid_of(A, Bq, Cc));
+                        if (rec_precise(Cc))
+                            fvj = eval_f_precise(A, Bq.y, rpf + 6 * (int64_t)rec_gid(Cc), sux, suy, dx, dy);
                         const bool in = ok && dd <= cut;
-                        const bool hj = in && dd < Bq.z;
+                        const bool hj = ok && dd < hit_bound(Bq.z, cut);
                         float zj = 0.f;
                         if constexpr (DM == 1) zj = in ? zf[__float_as_uint(Cc.z) & kGidMask] : 0.f;
                         // the records that reach it, in list order
@@ -495,13 +536,13 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
                                 sC1 = __builtin_fmaf(rdl(Cc.x, k), wgt, sC1);
                                 sC2 = __builtin_fmaf(rdl(Cc.y, k), wgt, sC2);
                                 if constexpr (DM == 1) sDa = __builtin_fmaf(rdl(zj, k), wgt, sDa);
-                                sT = sT * (1.f - fv);
-                                slast = j0 + (uint32_t)k + 1u;
-                                snb += 1u;
+                                sT = __builtin_fmaf(-fv, sT, sT);
+                                cnt_blend += 1;
+                                sbl = true;
                                 scd = sT < teps;
+                                if (scd) slast = j0 + (uint32_t)k + 1u;
                             }
                             if (!sdd && ((hm >> k) & 1ull) != 0) {
-                                shg = rdl_u(__float_as_uint(Cc.z), k);
                                 shp = j0 + (uint32_t)k + 1u;
                                 sdd = true;
                             }
@@ -514,32 +555,29 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
                         C1 = sC1;
                         C2 = sC2;
                         Da = sDa;
-                        cdone = scd;
                         ddone = sdd;
+                        blended = blended || sbl;
                         last = slast;
                         hitpos = shp;
-                        hitg = shg;
-                        nblend += snb;
                     }
                 }
                 break;
             }
         }
-        uint32_t cterm = (T < teps) ? last : p.re;
-        cnt_eval += p.act ? (float)(max(cterm, hitpos ? hitpos : p.re) - p.rs) : 0.f;
-        cnt_blend += nblend;
+        cnt_eval += p.act ? (float)(max(last, hitpos ? hitpos : p.re) - p.rs) : 0.f;
         if (p.act) {
             size_t pix = ((size_t)p.f * d.H + p.py) * d.W + p.px;
             out_c[3 * pix + 0] = C0;
             out_c[3 * pix + 1] = C1;
             out_c[3 * pix + 2] = C2;
             out_t[pix] = T;
-            const int hit = hitpos ? (int)(hitg & kGidMask) : -1;
+            const float4* hr = w.prec + 4ull * (hitpos ? hitpos - 1u : 0u);
+            const int hit = hitpos ? rec_gid(hr[2]) : -1;
             float D = -1.f;
             if constexpr (DM == 1) {
-                D = nblend ? Da : -1.f;
+                D = blended ? Da : -1.f;
             } else if (hit >= 0) {
-                const float4 hn = w.prec[4ull * (hitpos - 1u) + 3];
+                const float4 hn = hr[3];
                 if (plane_branch(d, hn.x, hn.y, hn.z, p.ux, p.uy)) {
                     double d0 = ((double)p.ux - d.cx) / d.fx, d1 = ((double)p.uy - d.cy) / d.fy;
                     double dn = ((double)hn.x * d0 + (double)hn.y * d1) + (double)hn.z;
@@ -555,11 +593,11 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
     }
     // per-wave counters: no shared-address atomics
     {
-        float se = wave_sum(cnt_eval), sb = wave_sum((float)cnt_blend);
+        float se = wave_sum(cnt_eval);
         uint32_t gw = blockIdx.x * 4u + (uint32_t)wv;
         if (lane == 0 && gw < (uint32_t)kMaxWaves) {
             w.wcount[gw] = (unsigned long long)se;
-            w.wcount[kMaxWaves + gw] = (unsigned long long)sb;
+            w.wcount[kMaxWaves + gw] = cnt_blend;
         }
         if (lane == 0 && gw == 0) w.hdr->fwd_waves = gridDim.x * 4u;
     }
@@ -584,28 +622,147 @@ struct L1Up {
     int l1;
 };
 
+// Gradients of the unstable records, kQ at a time.  Walking a pixel's list
+// is serial, so there the wave has one pixel per lane and only leaves two
+// numbers per record and pixel in LDS: e = dL/df g and w = f T (zero where the
+// pixel takes no part).  Once kQ records are held, the wave turns round: eight
+// lanes per record, each adding up eight pixels' moments of e about the
+// record's centre and their colour sums in registers, then one
+// reduce-scatter over the eight lanes and one float atomic per value.  That
+// takes about 23 vector operations per record, where reducing nine values
+// across the wave for every record took about 60.
+constexpr int kQ = 8, kQLanes = 64 / kQ;
+struct GradQueue {
+    float2 ew[kQ][64 + 8];      // e, w per pixel (rows staggered over the banks)
+    float4 px[64];              // ux, uy, g0, g1 per pixel
+    float2 px2[64];             // g2, gD
+    float4 ra[kQ], rb[kQ];      // {mu, Q.xx, 2 Q.xy}, {Q.yy, alpha', residual word, index word}
+};
+
+// Parameters of the records held since the last call (their places in the
+// slice one byte each in qk), before the slice is reused or they are summed.
+__device__ __forceinline__ void queue_records(GradQueue& G, const Slice& S, int lane, int n0, int n, uint64_t qk) {
+    if (lane >= n0 && lane < n) {
+        const int k = (int)((qk >> (8 * lane)) & 63u);
+        G.ra[lane] = S.r[0][k];
+        const float4 b = S.r[1][k];
+        G.rb[lane] = make_float4(b.x, b.y, __uint_as_float(S.pos[k]), __uint_as_float(S.gid[k]));
+    }
+}
+
+// The held records' sums into their gradient rows (slots 0-8, and 13 with
+// the alpha-blended depth); grad is the frame's first row, rpf its recp.
+template <int DM>
+__device__ __forceinline__ void queue_sums(const GradQueue& G, int lane, int n, bool anyp, const float* rpf,
+                                           float* grad) {
+    const int r = lane / kQLanes, s = lane % kQLanes;
+    const int rr = r < n ? r : 0;
+    const float4 a = G.ra[rr], b = G.rb[rr];
+    const uint32_t gw = __float_as_uint(b.w);
+    const bool prec = (gw & kPreciseBit) != 0u;
+    float lx, ly;
+    mu_lo(b.z, lx, ly);
+    float s0 = 0.f, sx = 0.f, sy = 0.f, sxx = 0.f, sxy = 0.f, syy = 0.f, w0 = 0.f, w1 = 0.f, w2 = 0.f, wd = 0.f;
+#pragma unroll 1
+    for (int i = 0; i < 64 / kQLanes; ++i) {
+        const int k = s + kQLanes * i;
+        const float2 ew = G.ew[rr][k];
+        const float4 p = G.px[k];
+        const float2 p2 = G.px2[k];
+        const float dxd = p.x - a.x, dyd = p.y - a.y;
+        float dx = dxd - lx, dy = dyd - ly;
+        // precise records: the whitened offsets e = U (u - mu), Q = U^T U;
+        // their slots hold sum g e and sum g e e^T, which the projection
+        // backward maps back through U
+        if (anyp && prec) precise_offsets(rpf + 6 * (int64_t)(gw & kGidMask), p.x, p.y, a.x, a.y, dxd, dyd, dx, dy);
+        const float ex = ew.x * dx, ey = ew.x * dy;
+        s0 += ew.x;
+        sx = __builtin_fmaf(ew.x, dx, sx);
+        sy = __builtin_fmaf(ew.x, dy, sy);
+        sxx = __builtin_fmaf(ex, dx, sxx);
+        sxy = __builtin_fmaf(ex, dy, sxy);
+        syy = __builtin_fmaf(ey, dy, syy);
+        w0 = __builtin_fmaf(p.z, ew.y, w0);
+        w1 = __builtin_fmaf(p.w, ew.y, w1);
+        w2 = __builtin_fmaf(p2.x, ew.y, w2);
+        if constexpr (DM == 1) wd = __builtin_fmaf(p2.y, ew.y, wd);   // dL/dz of the blended depth
+    }
+    // d^2 enters f as exp(-d^2 / 2): h = -alpha' / 2; alpha' = alpha q0
+    const float h = -0.5f * b.y, h2 = -2.f * h;
+    const float qxx = a.z, qxy = 0.5f * a.w, qyy = b.x;
+    const float q0 = prec ? 1.f : gauss_weight(__builtin_fmaf(__builtin_fmaf(qxx, lx, a.w * ly), lx, (qyy * ly) * ly));
+    float v[8];
+    v[0] = prec ? h * sx : h2 * __builtin_fmaf(qxx, sx, qxy * sy);
+    v[1] = prec ? h * sy : h2 * __builtin_fmaf(qyy, sy, qxy * sx);
+    v[2] = h * sxx;
+    v[3] = -h2 * sxy;
+    v[4] = h * syy;
+    v[5] = q0 * s0;
+    v[6] = w0;
+    v[7] = w1;
+    const float t = oct_scatter8(v, lane), t8 = oct_sum(w2);
+    float t13 = 0.f;
+    if constexpr (DM == 1) t13 = oct_sum(wd);
+    if (r >= n) return;
+    float* row = grad + 16 * (int64_t)(gw & kGidMask);
+    atomic_add_f32(row + (((s >> 2) & 1) + 2 * ((s >> 1) & 1) + 4 * (s & 1)), t);
+    if (s == 0) atomic_add_f32(row + 8, t8);
+    if constexpr (DM == 1)
+        if (s == 1) atomic_add_f32(row + 13, t13);
+}
+
+// Depth-path terms (Eq. 4-5) of the pixels whose depth hit is an unstable
+// Gaussian, slots 9-13 of its row: the pixels that share a hit are summed
+// over the wave, one round per distinct hit.
+__device__ __forceinline__ void depth_hits(const Dims& d, const WS& w, const PixelOfItem& p, int lane, uint32_t hitpos,
+                                           float gd, float D, float* grad) {
+    uint32_t gw = 0u;
+    float v[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+    if (hitpos) {
+        const float4* hr = w.prec + 4ull * (hitpos - 1u);
+        gw = __float_as_uint(hr[2].z);
+        if (gw & kUnstableBit) {
+            const float4 nh = hr[3];
+            if (plane_branch(d, nh.x, nh.y, nh.z, p.ux, p.uy)) {
+                const float rx = (float)(((double)p.ux - d.cx) / d.fx);
+                const float ry = (float)(((double)p.uy - d.cy) / d.fy);
+                const float dn = (nh.x * rx + nh.y * ry) + nh.z;
+                v[0] = gd / dn;
+                const float aD = v[0] * D;
+                v[1] = aD * rx;
+                v[2] = aD * ry;
+                v[3] = aD;
+            } else {
+                v[4] = gd;
+            }
+        }
+    }
+    for (uint64_t m = ballot((gw & kUnstableBit) != 0u); m != 0;) {
+        const uint32_t hw = rdl_u(gw, __builtin_ctzll(m));
+        const bool mine = gw == hw;
+        m &= ~ballot(mine);
+        float u[5];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) u[k] = mine ? v[k] : 0.f;
+        const float t = reduce_scatter5(u, lane);
+        const int slot = ((lane >> 5) & 1) + 2 * ((lane >> 4) & 1) + 4 * ((lane >> 3) & 1);
+        if ((lane & 7) == 0 && slot < 5) atomic_add_f32(grad + 16 * (int64_t)(hw & kGidMask) + 9 + slot, t);
+    }
+}
+
 template <int DM>
 __global__ RTG_BWD_BOUNDS void k_raster_bwd(Dims d, WS w, const float* __restrict__ out_d,
                                                  const float* __restrict__ out_t,
                                                  const int* __restrict__ out_i,
                                                  const float* __restrict__ gC,
                                                  const float* __restrict__ gD, L1Up up) {
-    __shared__ float4 lds[4][3][64];
-    __shared__ uint32_t ldp[4][64];
-    __shared__ __attribute__((aligned(16))) float lred[4][9 * 64];
+    __shared__ Slice slices[4];
+    __shared__ GradQueue queues[4];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    float4(*L)[64] = lds[wv];
-    uint32_t* P = ldp[wv];
-    float* red = lred[wv];
+    Slice& S = slices[wv];
+    GradQueue& GQ = queues[wv];
     ItemIter iter = make_iter(d.items_per_pop, d.static_share, w.hdr->n_items, &w.hdr->q_bwd, lane);
-    // this lane's L1 sums, kept in LDS (its own slots) rather than in
-    // registers that would live across the whole item loop
-    __shared__ float l1acc[3][4][64];
-    l1acc[0][wv][lane] = 0.f;
-    l1acc[1][wv][lane] = 0.f;
-    l1acc[2][wv][lane] = 0.f;
-    const int myslot = scatter_slot(lane);
-    const bool writer = (lane & 3) == 0 && myslot < 14;
+    float l1 = 0.f;   // the wave's L1 sums: colour in lane 0, depth in lane 1, depth count in lane 2
     const float cut = d.cutoff2;
     float cnt_walk = 0.f;
     unsigned long long cnt_part = 0;
@@ -615,6 +772,7 @@ __global__ RTG_BWD_BOUNDS void k_raster_bwd(Dims d, WS w, const float* __restric
         PixelOfItem p = decode_item(d, w, it, lane);
         size_t pix = ((size_t)p.f * d.H + p.py) * d.W + p.px;
         float Tc = 1.f, g0 = 0.f, g1 = 0.f, g2 = 0.f, gd = 0.f, D = -1.f;
+        float ec = 0.f, ed = 0.f, nd = 0.f;
         uint32_t last = p.rs, hitpos = 0;
         if (p.act) {
             Tc = out_t[pix];
@@ -629,11 +787,9 @@ __global__ RTG_BWD_BOUNDS void k_raster_bwd(Dims d, WS w, const float* __restric
                 const float dt = up.tgt_d[pix];
                 const bool vd = D != -1.f && dt > 0.f;
                 gd = vd ? sgn(D - dt) : 0.f;
-                l1acc[0][wv][lane] += fabsf(e0) + fabsf(e1) + fabsf(e2);
-                if (vd) {
-                    l1acc[1][wv][lane] += fabsf(D - dt);
-                    l1acc[2][wv][lane] += 1.f;
-                }
+                ec = fabsf(e0) + fabsf(e1) + fabsf(e2);
+                ed = vd ? fabsf(D - dt) : 0.f;
+                nd = vd ? 1.f : 0.f;
             } else {
                 g0 = gC[3 * pix];
                 g1 = gC[3 * pix + 1];
@@ -642,140 +798,117 @@ __global__ RTG_BWD_BOUNDS void k_raster_bwd(Dims d, WS w, const float* __restric
             }
             uint2 aux = reinterpret_cast<const uint2*>(w.px_aux)[(size_t)p.ft * d.tarea + p.r];
             last = aux.x;
-            // alpha-blended depth: the depth path follows the colour's
-            hitpos = (DM == 0 && gd != 0.f) ? aux.y : 0u;
+            hitpos = gd != 0.f ? aux.y : 0u;
+        }
+        if (up.l1) {
+            const float tc = wave_sum(ec), td = wave_sum(ed), tn = wave_sum(nd);
+            l1 += lane == 0 ? tc : lane == 1 ? td : lane == 2 ? tn : 0.f;
         }
         const PackBox pb = pack_box(p);
-        // the frame is the same for every lane of the pack: a scalar base
-        const float* rpf = w.recp + 6 * ((int64_t)readfirstlane(p.f) * d.N);
-        const float* zf = w.zkey + (int64_t)readfirstlane(p.f) * d.N;
-        uint32_t jend = wave_max_u32(max(last, hitpos));
-        float A0 = 0.f, A1 = 0.f, A2 = 0.f, Az = 0.f;
-        Batch<3> B = {};
-        if (jend > p.rs) B = load_batch<3>(w, jend - p.rs > 64u ? jend - 64u : p.rs, jend, lane);
+        // the frame is the same for every lane of the pack: scalar bases
+        const int64_t f0 = (int64_t)readfirstlane(p.f) * d.N;
+        const float* rpf = w.recp + 6 * f0;
+        const float* zf = w.zkey + f0;
+        float* grad = w.grad + 16 * f0;
+        const uint32_t jend = wave_max_u32(last);
+        Batch B = {};
+        if (jend > p.rs) B = load_batch(w, jend - p.rs > 64u ? jend - 64u : p.rs, jend, lane);
+        GQ.px[lane] = make_float4(p.ux, p.uy, g0, g1);
+        GQ.px2[lane] = make_float2(g2, gd);
+        // alpha-blended depth: the depth path follows the colour's
+        if constexpr (DM == 0) depth_hits(d, w, p, lane, hitpos, gd, D, grad);
+        // the upstream-weighted colour (and blended depth) behind: only g . A
+        // enters the gradients, so one sum replaces one per channel
+        float Ag = 0.f;
+        int nq = 0, nq0 = 0;   // records held, and those whose parameters are
+        uint64_t qk = 0;
+        bool qprec = false;
         for (uint32_t top = jend; top > p.rs;) {
             uint32_t b0 = top - p.rs > 64u ? top - 64u : p.rs;
-            bool anyp;
-            uint32_t nk = compact_batch<3>(B, b0, L, P, lane, pb, cut, anyp);
+            const uint64_t kept = compact_batch<true>(B, b0, S, lane, pb, cut);
+            const int nk = __builtin_popcountll(kept);
+            // this lane's records: the first kl of the slice lie before `last`
+            const uint32_t lim = last > b0 ? last - b0 : 0u;
+            const int kl = __builtin_popcountll(lim >= 64u ? kept : kept & ((1ull << lim) - 1ull));
             wave_lds_sync();
-            if (b0 > p.rs) B = load_batch<3>(w, b0 - p.rs > 64u ? b0 - 64u : p.rs, b0, lane);
-            // the record loop; when the batch holds a precise record (a
-            // uniform test), the value distance of those comes from the
-            // whitened offsets e = U (u - mu) (Q = U^T U), and the conic
-            // slots take m = g e and M = g e e^T instead of the derivatives
-            // by mu and Q, which the projection backward maps back through U
-            {
-                for (int k = (int)nk - 1; k >= 0; --k) {
-                    uint32_t j = P[k];
-                    float4 A = L[0][k];
-                    float4 Bq = L[1][k];
-                    float4 Cc = L[2][k];
-                    float dxd = p.ux - A.x, dyd = p.uy - A.y;
-                    float dd = __builtin_fmaf(Bq.x * dyd, dyd, __builtin_fmaf(A.w * dxd, dyd, (A.z * dxd) * dxd));
-                    bool part = (j < last) && (dd <= cut);
-                    bool ish = (j + 1 == hitpos);
-                    const uint64_t bp = ballot(part), bh = ballot(ish);
-                    if ((bp | bh) == 0) continue;   // no pixel of the wave takes part
-                    float2 lo = unpack_mu_lo(Cc.w);
-                    float dx = dxd - lo.x, dy = dyd - lo.y;
-                    float ddv = __builtin_fmaf(Bq.x * dy, dy, __builtin_fmaf(A.w * dx, dy, (A.z * dx) * dx));
-                    if (anyp) {
-                        // (dx, dy) become the whitened offsets; every lane
-                        // holds the same record: a uniform branch and scalar
-                        // loads
-                        const uint32_t gwu = (uint32_t)readfirstlane((int)__float_as_uint(Cc.z));
-                        if (gwu & kPreciseBit) {
-                            const int gu = (int)(gwu & kGidMask);
-                            precise_offsets(rpf + 6 * (int64_t)gu, p.ux, p.uy, A.x, A.y, dxd, dyd, dx, dy);
-                            ddv = dx * dx + dy * dy;
-                            // conic entries for the slots below: with
-                            // Q.xx = Q.yy = -1/2 and Q.xy = 0 they take
-                            // m = g e and M = g e e^T
-                            A.z = -0.5f;
-                            A.w = 0.f;
-                            Bq.x = -0.5f;
+            const uint32_t gwl = lane < nk ? S.gid[lane] : 0u;
+            const uint64_t um = ballot((gwl & kUnstableBit) != 0u), pm = ballot((gwl & kPreciseBit) != 0u);
+            qprec = qprec || pm != 0;
+            if (b0 > p.rs) B = load_batch(w, b0 - p.rs > 64u ? b0 - 64u : p.rs, b0, lane);
+            constexpr int G = RTG_BWD_GROUP;
+            for (int k0 = (nk - 1) / G * G; k0 >= 0; k0 -= G) {
+                float4 A[G], Bq[G], Cc[G];
+#pragma unroll
+                for (int u = 0; u < G; ++u) {
+                    A[u] = S.r[0][k0 + u];
+                    Bq[u] = S.r[1][k0 + u];
+                    Cc[u] = S.r[2][k0 + u];
+                }
+                // independent part: decision, weight, 1 / (1 - f), upstream . colour
+                float gw[G], fv[G], ro[G], gc[G];
+                bool part[G], free[G];
+#pragma unroll
+                for (int u = 0; u < G; ++u) {
+                    const int k = k0 + u;
+                    float dx, dy;
+                    const float dd = eval_dd(A[u], Bq[u].x, p.ux, p.uy, dx, dy);
+                    part[u] = dd <= cut && k < kl;
+                    float ddv = __builtin_fmaf(Cc[u].z, dx, __builtin_fmaf(Cc[u].w, dy, dd));
+                    if ((pm >> k) & 1ull) {
+                        float e0, e1;
+                        precise_offsets(rpf + 6 * (int64_t)(readfirstlane((int)S.gid[k]) & (int)kGidMask), p.ux, p.uy,
+                                        A[u].x, A[u].y, dx, dy, e0, e1);
+                        ddv = e0 * e0 + e1 * e1;
+                    }
+                    gw[u] = gauss_weight(ddv);
+                    const float fa = Bq[u].y * gw[u];
+                    free[u] = !(fa > 0.99f);   // not clamped
+                    fv[u] = fminf(fa, 0.99f);
+                    // 1 / (1 - f) to binary32: one step on the hardware
+                    // reciprocal, with the residual from f itself (the
+                    // transmission recovered over a long list is a product of
+                    // these: without the step d_pos was 5 % further from 64
+                    // bits than with per-record sums, with it 2 % nearer)
+                    const float r0 = __builtin_amdgcn_rcpf(1.f - fv[u]);
+                    ro[u] = __builtin_fmaf(__builtin_fmaf(fv[u], r0, 1.f - r0), r0, r0);
+                    gc[u] = __builtin_fmaf(g2, Cc[u].y, __builtin_fmaf(g1, Cc[u].x, g0 * Bq[u].w));
+                    if constexpr (DM == 1)
+                        gc[u] = __builtin_fmaf(gd, zf[readfirstlane((int)(S.gid[k] & kGidMask))], gc[u]);
+                }
+                // sequential part, back to front
+#pragma unroll
+                for (int u = G - 1; u >= 0; --u) {
+                    const float Tb = Tc * ro[u];
+                    const float gsum = gc[u] - Ag;
+                    const float fp = part[u] ? fv[u] : 0.f;
+                    if ((um >> (k0 + u)) & 1ull) {
+                        // a stable one only moves T and the colour behind
+                        const float e = part[u] && free[u] ? (gsum * Tb) * gw[u] : 0.f;
+                        GQ.ew[nq][lane] = make_float2(e, fp * Tb);
+                        qk |= (uint64_t)(uint32_t)(k0 + u) << (8 * nq);
+                        if (++nq == kQ) {
+                            queue_records(GQ, S, lane, nq0, nq, qk);
+                            wave_lds_sync();
+                            queue_sums<DM>(GQ, lane, nq, qprec, rpf, grad);
+                            wave_lds_sync();
+                            nq = nq0 = 0;
+                            qk = 0;
+                            qprec = pm != 0;
                         }
                     }
-                    float g = gauss_weight(ddv);
-                    float fa = Bq.y * g;
-                    bool clamped = fa > 0.99f;
-                    float fv = clamped ? 0.99f : fa;
-                    float om = 1.f - fv;
-                    float Tb = Tc * __builtin_amdgcn_rcpf(om);
-                    float zr = 0.f;
-                    if constexpr (DM == 1) zr = zf[readfirstlane((int)rec_gid(Cc))];
-                    // gradient terms and their reduction only for an unstable
-                    // Gaussian (the record is the same on every lane: a
-                    // uniform branch); a stable one only moves T and the
-                    // colour behind
-                    if ((readfirstlane((int)__float_as_uint(Cc.z)) & (int)kUnstableBit) != 0) {
-                        float wgt = fv * Tb;
-                        float gsum = (g0 * (Bq.w - A0) + g1 * (Cc.x - A1)) + g2 * (Cc.y - A2);
-                        if constexpr (DM == 1) gsum = __builtin_fmaf(gd, zr - Az, gsum);
-                        float gf = gsum * Tb;
-                        float gdd = (part && !clamped) ? -0.5f * fv * gf : 0.f;
-                        float v[16];
-                        float qb = 0.5f * A.w;
-                        v[0] = gdd * -2.f * (A.z * dx + qb * dy);
-                        v[1] = gdd * -2.f * (qb * dx + Bq.x * dy);
-                        v[2] = gdd * dx * dx;
-                        v[3] = gdd * 2.f * dx * dy;
-                        v[4] = gdd * dy * dy;
-                        v[5] = (part && !clamped) ? gf * g : 0.f;
-                        float wp = part ? wgt : 0.f;
-                        v[6] = g0 * wp;
-                        v[7] = g1 * wp;
-                        v[8] = g2 * wp;
-                        // depth path (Eq. 4-5) of the pixels whose depth hit this is
-                        float da = 0.f, db0 = 0.f, db1 = 0.f, db2 = 0.f, de = 0.f;
-                        if (bh != 0 && ish) {
-                            const float4 nh = w.prec[4ull * j + 3];
-                            if (plane_branch(d, nh.x, nh.y, nh.z, p.ux, p.uy)) {
-                                float rx = (float)(((double)p.ux - d.cx) / d.fx);
-                                float ry = (float)(((double)p.uy - d.cy) / d.fy);
-                                float dn = (nh.x * rx + nh.y * ry) + nh.z;
-                                da = gd / dn;
-                                float aD = da * D;
-                                db0 = aD * rx;
-                                db1 = aD * ry;
-                                db2 = aD;
-                            } else {
-                                de = gd;
-                            }
-                        }
-                        if constexpr (DM == 1) de = gd * wp;   // dL/dz of the blended depth
-                        v[9] = da;
-                        v[10] = db0;
-                        v[11] = db1;
-                        v[12] = db2;
-                        v[13] = de;
-                        v[14] = 0.f;
-                        v[15] = 0.f;
-                        float* gr = w.grad + 16 * ((int64_t)p.f * d.N + rec_gid(Cc)) + myslot;
-                        if (DM == 0 && bh == 0) {
-                            float tot, tot8;
-                            lds_sum9(v, red, lane, tot, tot8);
-                            float* g0p = w.grad + 16 * ((int64_t)p.f * d.N + rec_gid(Cc));
-                            if ((lane & 7) == 0) atomic_add_f32(g0p + (lane >> 3), tot);
-                            if (lane == 1) atomic_add_f32(g0p + 8, tot8);
-                        } else {
-                            float tot = reduce_scatter16(v, lane);
-                            if (writer) atomic_add_f32(gr, tot);
-                        }
-                    }
-                    // (a pixel that does not take part adds 0 and keeps its
-                    // colour behind: fma(0, c, 1 * A) = A exactly)
-                    const float fp = part ? fv : 0.f, op = 1.f - fp;
-                    A0 = __builtin_fmaf(fp, Bq.w, op * A0);
-                    A1 = __builtin_fmaf(fp, Cc.x, op * A1);
-                    A2 = __builtin_fmaf(fp, Cc.y, op * A2);
-                    if constexpr (DM == 1) Az = __builtin_fmaf(fp, zr, op * Az);
-                    Tc = part ? Tb : Tc;
-                    cnt_part += (unsigned long long)__builtin_popcountll(bp);
+                    Ag = __builtin_fmaf(fp, gsum, Ag);
+                    Tc = part[u] ? Tb : Tc;
+                    cnt_part += (unsigned long long)__builtin_popcountll(ballot(part[u]));
                 }
             }
+            if (nq > nq0) queue_records(GQ, S, lane, nq0, nq, qk);
+            nq0 = nq;
             wave_lds_sync();
             top = b0;
+        }
+        if (nq) {
+            queue_sums<DM>(GQ, lane, nq, qprec, rpf, grad);
+            wave_lds_sync();
         }
         cnt_walk += (float)(last - p.rs);
     }
@@ -789,18 +922,11 @@ __global__ RTG_BWD_BOUNDS void k_raster_bwd(Dims d, WS w, const float* __restric
         if (up.l1) {
             // one triple per workgroup (every wave reaches this point)
             __shared__ float l1red[3][4];
-            const float sc = wave_sum(l1acc[0][wv][lane]), sd = wave_sum(l1acc[1][wv][lane]);
-            const float sn = wave_sum(l1acc[2][wv][lane]);
-            if (lane == 0) {
-                l1red[0][wv] = sc;
-                l1red[1][wv] = sd;
-                l1red[2][wv] = sn;
-            }
+            if (lane < 3) l1red[lane][wv] = l1;
             __syncthreads();
-            if (threadIdx.x == 0 && blockIdx.x < (uint32_t)kMaxWaves) {
-                w.lwave[blockIdx.x] = (l1red[0][0] + l1red[0][1]) + (l1red[0][2] + l1red[0][3]);
-                w.lwave[kMaxWaves + blockIdx.x] = (l1red[1][0] + l1red[1][1]) + (l1red[1][2] + l1red[1][3]);
-                w.lwave[2 * kMaxWaves + blockIdx.x] = (l1red[2][0] + l1red[2][1]) + (l1red[2][2] + l1red[2][3]);
+            if (threadIdx.x < 3 && blockIdx.x < (uint32_t)kMaxWaves) {
+                const float* t = l1red[threadIdx.x];
+                w.lwave[threadIdx.x * kMaxWaves + blockIdx.x] = (t[0] + t[1]) + (t[2] + t[3]);
             }
         }
         if (lane == 0 && gw == 0) w.hdr->bwd_waves = gridDim.x * 4u;

@@ -181,20 +181,12 @@ __device__ __forceinline__ float pack_mu_lo(float lx, float ly) {
     half2_t v = {(_Float16)(lx * kLoScale), (_Float16)(ly * kLoScale)};
     return __builtin_bit_cast(float, v);
 }
-__device__ __forceinline__ float2 unpack_mu_lo(float w) {
-    half2_t v = __builtin_bit_cast(half2_t, w);
-    return make_float2((float)v.x * (1.0f / kLoScale), (float)v.y * (1.0f / kLoScale));
-}
 
-// Value-path squared distance: offsets from the centre including its
-// residual, same quadratic form as the decision.
-__device__ __forceinline__ float dd_value(float4 h0, float qc, float2 lo, float ux, float uy, float& dx,
-                                          float& dy) {
-    dx = (ux - h0.x) - lo.x;
-    dy = (uy - h0.y) - lo.y;
-    float t0 = (h0.z * dx) * dx;
-    float t1 = __builtin_fmaf(h0.w * dx, dy, t0);
-    return __builtin_fmaf(qc * dy, dy, t1);
+// The two halves of the residual word, in pixels.
+__device__ __forceinline__ void mu_lo(float w, float& lx, float& ly) {
+    const half2_t v = __builtin_bit_cast(half2_t, w);
+    lx = (float)v.x * (1.0f / kLoScale);
+    ly = (float)v.y * (1.0f / kLoScale);
 }
 
 constexpr int kMaxWaves = 32768;  // per-wave counter slots of the persistent kernels
