@@ -266,8 +266,6 @@ rtg_status rtg_plan_create(const rtg_config* cfg, const rtg_intrinsics* intr, in
     d.items_per_pop = cfg->items_per_pop;
     d.sh_deg = cfg->sh_degree;
     d.depth_mode = cfg->depth_mode;
-    d.strag_lanes = cfg->straggler_lanes;
-    d.strag_rest = cfg->straggler_rest;
     d.static_share = cfg->static_share;
     d.fwd_items_per_pop = cfg->fwd_items_per_pop >= 0 ? cfg->fwd_items_per_pop : cfg->items_per_pop;
     d.fwd_static_share = cfg->fwd_static_share >= 0 ? cfg->fwd_static_share : cfg->static_share;

@@ -15,8 +15,14 @@
 // of the pack are dropped, lane-parallel; about 95 % of those kept reach one)
 // and the survivors are compacted into the wave's own LDS slice, from which
 // every lane reads the same record (an LDS broadcast) with one lane per
-// pixel.  A ballot ends the walk once every lane has finished its colour and
-// found its depth hit.
+// pixel.  Culling follows the pixels that are still open (forward: colour or
+// hit outstanding; backward: entries left below their last): where a few
+// pixels of a pack keep compositing through a long list, its later batches
+// shrink to what reaches those.  (A path of its own for them, one entry per
+// lane and pixel after pixel, took 106 of the 120 thousand cycles of a frame's
+// longest pack; without it the forward of one masked 1200x680 frame went from
+// 61 to 45 us, of 16 keyframes from 679 to 632 us.)  A ballot ends the walk once
+// every lane has finished its colour and found its depth hit.
 //
 // Decisions (footprint, depth hit) use the fixed binary32 sequence on the
 // rounded centre; the values (f, gradients) use offsets from the centre
@@ -36,8 +42,9 @@
 // operations, value 2 more and the exponential, blend 7 (forward), and the
 // one gradient sum g . (c - A) in place of three colour recursions (backward).
 // Measured on MI355X, forward / backward: 16 keyframes of 1200x680 with 2.6M
-// masked pixels 914 / 1050 to 731 / 725 us, 8 keyframes 632 / 930 to 528 /
-// 735 us, one 640x480 frame 28 / 68 to 29 / 55 us.
+// masked pixels 914 / 1050 to 632 / 661 us, 8 keyframes 632 / 930 to 510 /
+// 675 us, one masked 1200x680 frame 63 / 103 to 45 / 61 us, one full 640x480
+// frame 28 / 68 to 28 / 51 us.
 #include <type_traits>
 
 #include "rtg_common.h"
@@ -92,7 +99,9 @@ __device__ __forceinline__ PixelOfItem decode_item(const Dims& d, const WS& w, u
     uint32_t npx = w.tile_npx[p.ft];
     p.r = pack * 64u + (uint32_t)lane;
     p.act = p.r < npx;
-    int l = p.act ? (int)w.pix[(size_t)p.ft * d.tarea + p.r] : 0;
+    // (loaded beside the count: the list has room for every rank of a pack)
+    const int lp = (int)w.pix[(size_t)p.ft * d.tarea + p.r];
+    const int l = p.act ? lp : 0;
     p.f = (int)(p.ft / (uint32_t)d.ntiles);
     int t = (int)(p.ft - (uint32_t)p.f * (uint32_t)d.ntiles);
     p.px = (t % d.tx) * d.tw + (l & (d.tw - 1));
@@ -104,26 +113,35 @@ __device__ __forceinline__ PixelOfItem decode_item(const Dims& d, const WS& w, u
     return p;
 }
 
-// Bounding box of the pixels of one pack (inclusive pixel indices).
+// Bounding box of pixels of one pack (inclusive pixel indices).
 struct PackBox {
     int x0, x1, y0, y1;
 };
 
+// Wave minimum: DPP within the rows, then the permlane swaps across them.
+template <int CTRL>
+__device__ __forceinline__ int dpp_mov_i(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
+}
 __device__ __forceinline__ int wave_min_i(int v) {
-    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
-    return v;
+    v = min(v, dpp_mov_i<0xB1>(v));
+    v = min(v, dpp_mov_i<0x4E>(v));
+    v = min(v, dpp_mov_i<0x141>(v));
+    v = min(v, dpp_mov_i<0x140>(v));
+    auto a = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    v = min((int)a[0], (int)a[1]);
+    auto b = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    return min((int)b[0], (int)b[1]);
 }
-__device__ __forceinline__ int wave_max_i(int v) {
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
-    return v;
-}
+__device__ __forceinline__ int wave_max_i(int v) { return ~wave_min_i(~v); }
 
-__device__ __forceinline__ PackBox pack_box(const PixelOfItem& p) {
+// (`on`: the lanes whose pixels count)
+__device__ __forceinline__ PackBox pack_box(const PixelOfItem& p, bool on) {
     PackBox b;
-    b.x0 = wave_min_i(p.act ? p.px : 0x7fffffff);
-    b.x1 = wave_max_i(p.act ? p.px : -1);
-    b.y0 = wave_min_i(p.act ? p.py : 0x7fffffff);
-    b.y1 = wave_max_i(p.act ? p.py : -1);
+    b.x0 = readfirstlane(wave_min_i(on ? p.px : 0x7fffffff));
+    b.x1 = readfirstlane(wave_max_i(on ? p.px : -1));
+    b.y0 = readfirstlane(wave_min_i(on ? p.py : 0x7fffffff));
+    b.y1 = readfirstlane(wave_max_i(on ? p.py : -1));
     return b;
 }
 
@@ -297,9 +315,6 @@ __device__ __forceinline__ float gauss_weight(float dd) {
 }
 
 // Lane k's value (k the same on every lane).
-__device__ __forceinline__ float rdl(float v, int k) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
-}
 __device__ __forceinline__ uint32_t rdl_u(uint32_t v, int k) { return (uint32_t)__builtin_amdgcn_readlane((int)v, k); }
 
 // What the value path takes from a record's centre residual lo = mu -
@@ -396,7 +411,8 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
     uint32_t it;
     while (iter.next(it)) {
         PixelOfItem p = decode_item(d, w, it, lane);
-        const PackBox pb = pack_box(p);
+        PackBox pb = pack_box(p, p.act);
+        uint64_t boxed = ballot(p.act);   // the pixels pb holds
         // a pixel is done with its colour once T < t_eps; lanes without one
         // start there
         float T = p.act ? 1.f : -1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, Da = 0.f;
@@ -499,69 +515,10 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
             wave_lds_sync();
             const uint64_t live = ballot(!(T < teps && ddone));
             if (all_done || live == 0) break;
-            // the straggler path for the rest of the list
-            const uint32_t rest = b + 64 < p.re ? b + 64 : p.re;
-            if (__builtin_popcountll(live) <= d.strag_lanes && p.re - rest >= (uint32_t)d.strag_rest) {
-                for (uint64_t lm = live; lm != 0; lm &= lm - 1) {
-                    const int l = __builtin_ctzll(lm);
-                    // pixel l's state, the same on every lane
-                    const float sux = rdl(p.ux, l), suy = rdl(p.uy, l);
-                    float sT = rdl(T, l), sC0 = rdl(C0, l), sC1 = rdl(C1, l), sC2 = rdl(C2, l);
-                    float sDa = rdl(Da, l);
-                    bool scd = sT < teps, sdd = rdl_u(ddone ? 1u : 0u, l) != 0u, sbl = false;
-                    uint32_t slast = rdl_u(last, l), shp = rdl_u(hitpos, l);
-                    for (uint32_t j0 = rest; j0 < p.re && !(scd && sdd); j0 += 64) {
-                        // one record per lane, evaluated at pixel l
-                        const uint32_t j = j0 + (uint32_t)lane;
-                        const bool ok = j < p.re;
-                        const float4* src = w.prec + 4ull * (ok ? j : j0);
-                        const float4 A = src[0], Bq = src[1], Cc = src[2];
-                        float dx, dy;
-                        const float dd = eval_dd(A, Bq.x, sux, suy, dx, dy);
-                        float fvj = eval_f(dd, dx, dy, resid_of(A, Bq, Cc));
-                        if (rec_precise(Cc))
-                            fvj = eval_f_precise(A, Bq.y, rpf + 6 * (int64_t)rec_gid(Cc), sux, suy, dx, dy);
-                        const bool in = ok && dd <= cut;
-                        const bool hj = ok && dd < hit_bound(Bq.z, cut);
-                        float zj = 0.f;
-                        if constexpr (DM == 1) zj = in ? zf[__float_as_uint(Cc.z) & kGidMask] : 0.f;
-                        // the records that reach it, in list order
-                        const uint64_t hm = ballot(hj);
-                        for (uint64_t mi = ballot(in); mi != 0; mi &= mi - 1) {
-                            const int k = __builtin_ctzll(mi);
-                            if (!scd) {
-                                const float fv = rdl(fvj, k);
-                                const float wgt = fv * sT;
-                                sC0 = __builtin_fmaf(rdl(Bq.w, k), wgt, sC0);
-                                sC1 = __builtin_fmaf(rdl(Cc.x, k), wgt, sC1);
-                                sC2 = __builtin_fmaf(rdl(Cc.y, k), wgt, sC2);
-                                if constexpr (DM == 1) sDa = __builtin_fmaf(rdl(zj, k), wgt, sDa);
-                                sT = __builtin_fmaf(-fv, sT, sT);
-                                cnt_blend += 1;
-                                sbl = true;
-                                scd = sT < teps;
-                                if (scd) slast = j0 + (uint32_t)k + 1u;
-                            }
-                            if (!sdd && ((hm >> k) & 1ull) != 0) {
-                                shp = j0 + (uint32_t)k + 1u;
-                                sdd = true;
-                            }
-                            if (scd && sdd) break;
-                        }
-                    }
-                    if (lane == l) {
-                        T = sT;
-                        C0 = sC0;
-                        C1 = sC1;
-                        C2 = sC2;
-                        Da = sDa;
-                        ddone = sdd;
-                        blended = blended || sbl;
-                        last = slast;
-                        hitpos = shp;
-                    }
-                }
-                break;
+            // culling the rest of the list for the pixels still open only
+            if (live != boxed) {
+                pb = pack_box(p, !(T < teps && ddone));
+                boxed = live;
             }
         }
         cnt_eval += p.act ? (float)(max(last, hitpos ? hitpos : p.re) - p.rs) : 0.f;
@@ -601,11 +558,6 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
         }
         if (lane == 0 && gw == 0) w.hdr->fwd_waves = gridDim.x * 4u;
     }
-}
-
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-    for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o));
-    return v;
 }
 
 // The upstream gradients come from gC / gD, or, with `l1` set, are the L1
@@ -663,29 +615,49 @@ __device__ __forceinline__ void queue_sums(const GradQueue& G, int lane, int n, 
     float lx, ly;
     mu_lo(b.z, lx, ly);
     float s0 = 0.f, sx = 0.f, sy = 0.f, sxx = 0.f, sxy = 0.f, syy = 0.f, w0 = 0.f, w1 = 0.f, w2 = 0.f, wd = 0.f;
-#pragma unroll 1
-    for (int i = 0; i < 64 / kQLanes; ++i) {
+    struct Px {
+        float2 ew, p2;
+        float4 p;
+    };
+    auto load = [&](int i) {
         const int k = s + kQLanes * i;
-        const float2 ew = G.ew[rr][k];
-        const float4 p = G.px[k];
-        const float2 p2 = G.px2[k];
-        const float dxd = p.x - a.x, dyd = p.y - a.y;
-        float dx = dxd - lx, dy = dyd - ly;
-        // precise records: the whitened offsets e = U (u - mu), Q = U^T U;
-        // their slots hold sum g e and sum g e e^T, which the projection
-        // backward maps back through U
-        if (anyp && prec) precise_offsets(rpf + 6 * (int64_t)(gw & kGidMask), p.x, p.y, a.x, a.y, dxd, dyd, dx, dy);
-        const float ex = ew.x * dx, ey = ew.x * dy;
-        s0 += ew.x;
-        sx = __builtin_fmaf(ew.x, dx, sx);
-        sy = __builtin_fmaf(ew.x, dy, sy);
+        return Px{G.ew[rr][k], G.px2[k], G.px[k]};
+    };
+    auto add = [&](const Px& q, float dx, float dy) {
+        const float ex = q.ew.x * dx, ey = q.ew.x * dy;
+        s0 += q.ew.x;
+        sx = __builtin_fmaf(q.ew.x, dx, sx);
+        sy = __builtin_fmaf(q.ew.x, dy, sy);
         sxx = __builtin_fmaf(ex, dx, sxx);
         sxy = __builtin_fmaf(ex, dy, sxy);
         syy = __builtin_fmaf(ey, dy, syy);
-        w0 = __builtin_fmaf(p.z, ew.y, w0);
-        w1 = __builtin_fmaf(p.w, ew.y, w1);
-        w2 = __builtin_fmaf(p2.x, ew.y, w2);
-        if constexpr (DM == 1) wd = __builtin_fmaf(p2.y, ew.y, wd);   // dL/dz of the blended depth
+        w0 = __builtin_fmaf(q.p.z, q.ew.y, w0);
+        w1 = __builtin_fmaf(q.p.w, q.ew.y, w1);
+        w2 = __builtin_fmaf(q.p2.x, q.ew.y, w2);
+        if constexpr (DM == 1) wd = __builtin_fmaf(q.p2.y, q.ew.y, wd);   // dL/dz of the blended depth
+    };
+    if (!anyp) {
+        Px q = load(0);
+#pragma unroll
+        for (int i = 0; i < 64 / kQLanes; ++i) {
+            // (one pixel ahead, no more: registers)
+            const Px nx = load(i + 1 < 64 / kQLanes ? i + 1 : i);
+            __builtin_amdgcn_sched_barrier(0);
+            add(q, (q.p.x - a.x) - lx, (q.p.y - a.y) - ly);
+            q = nx;
+        }
+    } else {
+        // precise records: the whitened offsets e = U (u - mu), Q = U^T U;
+        // their slots hold sum g e and sum g e e^T, which the projection
+        // backward maps back through U
+#pragma unroll 1
+        for (int i = 0; i < 64 / kQLanes; ++i) {
+            const Px q = load(i);
+            const float dxd = q.p.x - a.x, dyd = q.p.y - a.y;
+            float dx = dxd - lx, dy = dyd - ly;
+            if (prec) precise_offsets(rpf + 6 * (int64_t)(gw & kGidMask), q.p.x, q.p.y, a.x, a.y, dxd, dyd, dx, dy);
+            add(q, dx, dy);
+        }
     }
     // d^2 enters f as exp(-d^2 / 2): h = -alpha' / 2; alpha' = alpha q0
     const float h = -0.5f * b.y, h2 = -2.f * h;
@@ -765,7 +737,6 @@ __global__ RTG_BWD_BOUNDS void k_raster_bwd(Dims d, WS w, const float* __restric
     float l1 = 0.f;   // the wave's L1 sums: colour in lane 0, depth in lane 1, depth count in lane 2
     const float cut = d.cutoff2;
     float cnt_walk = 0.f;
-    unsigned long long cnt_part = 0;
     (void)out_i;   // the depth hit is identified by its list position
     uint32_t it;
     while (iter.next(it)) {
@@ -804,13 +775,12 @@ __global__ RTG_BWD_BOUNDS void k_raster_bwd(Dims d, WS w, const float* __restric
             const float tc = wave_sum(ec), td = wave_sum(ed), tn = wave_sum(nd);
             l1 += lane == 0 ? tc : lane == 1 ? td : lane == 2 ? tn : 0.f;
         }
-        const PackBox pb = pack_box(p);
         // the frame is the same for every lane of the pack: scalar bases
         const int64_t f0 = (int64_t)readfirstlane(p.f) * d.N;
         const float* rpf = w.recp + 6 * f0;
         const float* zf = w.zkey + f0;
         float* grad = w.grad + 16 * f0;
-        const uint32_t jend = wave_max_u32(last);
+        const uint32_t jend = (uint32_t)wave_max_i((int)last);   // (pair positions are below 2^31)
         Batch B = {};
         if (jend > p.rs) B = load_batch(w, jend - p.rs > 64u ? jend - 64u : p.rs, jend, lane);
         GQ.px[lane] = make_float4(p.ux, p.uy, g0, g1);
@@ -823,84 +793,113 @@ __global__ RTG_BWD_BOUNDS void k_raster_bwd(Dims d, WS w, const float* __restric
         int nq = 0, nq0 = 0;   // records held, and those whose parameters are
         uint64_t qk = 0;
         bool qprec = false;
+        PackBox pb = {};
+        uint64_t boxed = 0;   // the pixels pb holds
         for (uint32_t top = jend; top > p.rs;) {
             uint32_t b0 = top - p.rs > 64u ? top - 64u : p.rs;
+            // this lane's records: the first kl of the slice lie before `last`;
+            // the batch is culled for the pixels that have any
+            const uint32_t lim = last > b0 ? last - b0 : 0u;
+            const uint64_t open = ballot(lim != 0u);
+            if (open != boxed) {
+                pb = pack_box(p, lim != 0u);
+                boxed = open;
+            }
             const uint64_t kept = compact_batch<true>(B, b0, S, lane, pb, cut);
             const int nk = __builtin_popcountll(kept);
-            // this lane's records: the first kl of the slice lie before `last`
-            const uint32_t lim = last > b0 ? last - b0 : 0u;
             const int kl = __builtin_popcountll(lim >= 64u ? kept : kept & ((1ull << lim) - 1ull));
             wave_lds_sync();
             const uint32_t gwl = lane < nk ? S.gid[lane] : 0u;
             const uint64_t um = ballot((gwl & kUnstableBit) != 0u), pm = ballot((gwl & kPreciseBit) != 0u);
             qprec = qprec || pm != 0;
             if (b0 > p.rs) B = load_batch(w, b0 - p.rs > 64u ? b0 - 64u : p.rs, b0, lane);
-            constexpr int G = RTG_BWD_GROUP;
-            for (int k0 = (nk - 1) / G * G; k0 >= 0; k0 -= G) {
+            // groups of G records, specialised on whether the batch holds a
+            // precise record; the next group is read from LDS while the
+            // sequential part of this one runs
+            auto groups = [&](auto prec) {
+                constexpr bool PR = decltype(prec)::value;
+                constexpr int G = RTG_BWD_GROUP;
+                int k0 = nk > 0 ? (nk - 1) / G * G : -1;
                 float4 A[G], Bq[G], Cc[G];
+                auto load = [&](int kb) {
 #pragma unroll
-                for (int u = 0; u < G; ++u) {
-                    A[u] = S.r[0][k0 + u];
-                    Bq[u] = S.r[1][k0 + u];
-                    Cc[u] = S.r[2][k0 + u];
-                }
-                // independent part: decision, weight, 1 / (1 - f), upstream . colour
-                float gw[G], fv[G], ro[G], gc[G];
-                bool part[G], free[G];
-#pragma unroll
-                for (int u = 0; u < G; ++u) {
-                    const int k = k0 + u;
-                    float dx, dy;
-                    const float dd = eval_dd(A[u], Bq[u].x, p.ux, p.uy, dx, dy);
-                    part[u] = dd <= cut && k < kl;
-                    float ddv = __builtin_fmaf(Cc[u].z, dx, __builtin_fmaf(Cc[u].w, dy, dd));
-                    if ((pm >> k) & 1ull) {
-                        float e0, e1;
-                        precise_offsets(rpf + 6 * (int64_t)(readfirstlane((int)S.gid[k]) & (int)kGidMask), p.ux, p.uy,
-                                        A[u].x, A[u].y, dx, dy, e0, e1);
-                        ddv = e0 * e0 + e1 * e1;
+                    for (int u = 0; u < G; ++u) {
+                        A[u] = S.r[0][kb + u];
+                        Bq[u] = S.r[1][kb + u];
+                        Cc[u] = S.r[2][kb + u];
                     }
-                    gw[u] = gauss_weight(ddv);
-                    const float fa = Bq[u].y * gw[u];
-                    free[u] = !(fa > 0.99f);   // not clamped
-                    fv[u] = fminf(fa, 0.99f);
-                    // 1 / (1 - f) to binary32: one step on the hardware
-                    // reciprocal, with the residual from f itself (the
-                    // transmission recovered over a long list is a product of
-                    // these: without the step d_pos was 5 % further from 64
-                    // bits than with per-record sums, with it 2 % nearer)
-                    const float r0 = __builtin_amdgcn_rcpf(1.f - fv[u]);
-                    ro[u] = __builtin_fmaf(__builtin_fmaf(fv[u], r0, 1.f - r0), r0, r0);
-                    gc[u] = __builtin_fmaf(g2, Cc[u].y, __builtin_fmaf(g1, Cc[u].x, g0 * Bq[u].w));
-                    if constexpr (DM == 1)
-                        gc[u] = __builtin_fmaf(gd, zf[readfirstlane((int)(S.gid[k] & kGidMask))], gc[u]);
-                }
-                // sequential part, back to front
+                };
+                if (nk > 0) load(k0);
+                for (; k0 >= 0; k0 -= G) {
+                    // independent part: decision, weight, 1 / (1 - f), upstream . colour
+                    float gw[G], fv[G], ro[G], gc[G];
+                    bool part[G], free[G];
 #pragma unroll
-                for (int u = G - 1; u >= 0; --u) {
-                    const float Tb = Tc * ro[u];
-                    const float gsum = gc[u] - Ag;
-                    const float fp = part[u] ? fv[u] : 0.f;
-                    if ((um >> (k0 + u)) & 1ull) {
-                        // a stable one only moves T and the colour behind
-                        const float e = part[u] && free[u] ? (gsum * Tb) * gw[u] : 0.f;
-                        GQ.ew[nq][lane] = make_float2(e, fp * Tb);
-                        qk |= (uint64_t)(uint32_t)(k0 + u) << (8 * nq);
-                        if (++nq == kQ) {
-                            queue_records(GQ, S, lane, nq0, nq, qk);
-                            wave_lds_sync();
-                            queue_sums<DM>(GQ, lane, nq, qprec, rpf, grad);
-                            wave_lds_sync();
-                            nq = nq0 = 0;
-                            qk = 0;
-                            qprec = pm != 0;
+                    for (int u = 0; u < G; ++u) {
+                        const int k = k0 + u;
+                        float dx, dy;
+                        const float dd = eval_dd(A[u], Bq[u].x, p.ux, p.uy, dx, dy);
+                        part[u] = dd <= cut && k < kl;
+                        float ddv = __builtin_fmaf(Cc[u].z, dx, __builtin_fmaf(Cc[u].w, dy, dd));
+                        if constexpr (PR) {
+                            const uint32_t gi = (uint32_t)readfirstlane((int)S.gid[k]);
+                            if (gi & kPreciseBit) {
+                                float e0, e1;
+                                precise_offsets(rpf + 6 * (int64_t)(gi & kGidMask), p.ux, p.uy, A[u].x, A[u].y, dx, dy,
+                                                e0, e1);
+                                ddv = e0 * e0 + e1 * e1;
+                            }
                         }
+                        gw[u] = gauss_weight(ddv);
+                        const float fa = Bq[u].y * gw[u];
+                        free[u] = !(fa > 0.99f);   // not clamped
+                        fv[u] = fminf(fa, 0.99f);
+                        // 1 / (1 - f) to binary32: one step on the hardware
+                        // reciprocal, with the residual from f itself (the
+                        // transmission recovered over a long list is a product
+                        // of these: without the step d_pos was 5 % further from
+                        // 64 bits than with per-record sums, with it 2 % nearer)
+                        const float r0 = __builtin_amdgcn_rcpf(1.f - fv[u]);
+                        ro[u] = __builtin_fmaf(__builtin_fmaf(fv[u], r0, 1.f - r0), r0, r0);
+                        gc[u] = __builtin_fmaf(g2, Cc[u].y, __builtin_fmaf(g1, Cc[u].x, g0 * Bq[u].w));
+                        if constexpr (DM == 1)
+                            gc[u] = __builtin_fmaf(gd, zf[readfirstlane((int)(S.gid[k] & kGidMask))], gc[u]);
                     }
-                    Ag = __builtin_fmaf(fp, gsum, Ag);
-                    Tc = part[u] ? Tb : Tc;
-                    cnt_part += (unsigned long long)__builtin_popcountll(ballot(part[u]));
+                    load(max(k0 - G, 0));
+                    // (without this the compiler moves each record's
+                    // evaluation behind the branch of the one before, and the
+                    // chains no longer overlap)
+#pragma unroll
+                    for (int u = 0; u < G; ++u) asm volatile("" : "+v"(ro[u]), "+v"(gc[u]));
+                    // sequential part, back to front
+#pragma unroll
+                    for (int u = G - 1; u >= 0; --u) {
+                        const float Tb = Tc * ro[u];
+                        const float gsum = gc[u] - Ag;
+                        const float fp = part[u] ? fv[u] : 0.f;
+                        if ((um >> (k0 + u)) & 1ull) {
+                            // a stable one only moves T and the colour behind
+                            const float e = part[u] && free[u] ? (gsum * Tb) * gw[u] : 0.f;
+                            GQ.ew[nq][lane] = make_float2(e, fp * Tb);
+                            qk |= (uint64_t)(uint32_t)(k0 + u) << (8 * nq);
+                            ++nq;
+                        }
+                        Ag = __builtin_fmaf(fp, gsum, Ag);
+                        Tc = part[u] ? Tb : Tc;
+                    }
+                    if (nq > kQ - G) {   // no room for another group
+                        queue_records(GQ, S, lane, nq0, nq, qk);
+                        wave_lds_sync();
+                        queue_sums<DM>(GQ, lane, nq, qprec, rpf, grad);
+                        wave_lds_sync();
+                        nq = nq0 = 0;
+                        qk = 0;
+                        qprec = pm != 0;
+                    }
                 }
-            }
+            };
+            if (pm != 0) groups(std::true_type{});
+            else groups(std::false_type{});
             if (nq > nq0) queue_records(GQ, S, lane, nq0, nq, qk);
             nq0 = nq;
             wave_lds_sync();
@@ -917,7 +916,6 @@ __global__ RTG_BWD_BOUNDS void k_raster_bwd(Dims d, WS w, const float* __restric
         uint32_t gw = blockIdx.x * 4u + (uint32_t)wv;
         if (lane == 0 && gw < (uint32_t)kMaxWaves) {
             w.wcount[2 * kMaxWaves + gw] = (unsigned long long)sw;
-            w.wcount[3 * kMaxWaves + gw] = cnt_part;
         }
         if (up.l1) {
             // one triple per workgroup (every wave reaches this point)
