@@ -913,17 +913,27 @@ rtg_status rtg_select_top_error(int32_t frames, int32_t height, int32_t width, d
     uint32_t* hist = reinterpret_cast<uint32_t*>(b + align256(4 * (size_t)npx));
     SelState* st = reinterpret_cast<SelState*>(b + align256(4 * (size_t)npx) + align256(4 * 256 * (size_t)frames));
     const uint32_t k = (uint32_t)std::floor(frac * (double)hw);
-    hipLaunchKernelGGL(k_sel_keys, dim3(grid_for(npx, 256)), dim3(256), 0, S(stream), npx, color_r, color_in, keys);
-    hipLaunchKernelGGL(k_sel_init, dim3(frames), dim3(256), 0, S(stream), frames, k, hist, st);
-    // about 64 pixels per thread per pass, at most 1024 workgroups per frame
-    const unsigned bx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(1024, (hw + 16383) / 16384));
+    // four pixels per access where every frame starts 16-byte aligned (the
+    // mask: 4-byte); about 32 pixels per thread, at most 1024 workgroups
+    // per frame
+    const bool v4 = hw % 4 == 0 && ((reinterpret_cast<uintptr_t>(color_r) | reinterpret_cast<uintptr_t>(color_in)) & 15) == 0 &&
+                    (reinterpret_cast<uintptr_t>(mask_out) & 3) == 0;
+    const unsigned bx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(1024, (hw + 8191) / 8192));
+    const dim3 g(bx, frames), b256(256);
+    const uint32_t* ck = keys;
+    const SelState* cst = st;
+    hipLaunchKernelGGL(k_sel_init, dim3(frames), b256, 0, S(stream), frames, k, hist, st);
+    if (v4) hipLaunchKernelGGL(k_sel_keys<true>, g, b256, 0, S(stream), hw, color_r, color_in, keys, hist);
+    else hipLaunchKernelGGL(k_sel_keys<false>, g, b256, 0, S(stream), hw, color_r, color_in, keys, hist);
     for (int shift = 24; shift >= 0; shift -= 8) {
-        hipLaunchKernelGGL(k_sel_hist, dim3(bx, frames), dim3(256), 0, S(stream), hw, shift, (const uint32_t*)keys,
-                           hist, (const SelState*)st);
-        hipLaunchKernelGGL(k_sel_pick, dim3(frames), dim3(256), 0, S(stream), shift, hist, st);
+        if (shift < 24) {
+            if (v4) hipLaunchKernelGGL(k_sel_hist<true>, g, b256, 0, S(stream), hw, shift, ck, hist, cst);
+            else hipLaunchKernelGGL(k_sel_hist<false>, g, b256, 0, S(stream), hw, shift, ck, hist, cst);
+        }
+        hipLaunchKernelGGL(k_sel_pick, dim3(frames), b256, 0, S(stream), shift, hist, st);
     }
-    hipLaunchKernelGGL(k_sel_mask, dim3(grid_for(npx, 256)), dim3(256), 0, S(stream), hw, frames,
-                       (const uint32_t*)keys, (const SelState*)st, mask_out);
+    if (v4) hipLaunchKernelGGL(k_sel_mask<true>, g, b256, 0, S(stream), hw, ck, cst, mask_out);
+    else hipLaunchKernelGGL(k_sel_mask<false>, g, b256, 0, S(stream), hw, ck, cst, mask_out);
     return launched();
 }
 

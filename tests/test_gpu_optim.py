@@ -90,3 +90,25 @@ def test_top_error_selection_is_bit_exact(frac):
     k = int(np.floor(frac * H * W))
     for f in range(F):
         assert ref[f].sum() >= k
+
+
+@pytest.mark.parametrize("frames,h,w,offset", [(1, 1, 1, 0), (2, 1, 3, 0), (3, 2, 2, 0), (2, 37, 53, 0), (2, 64, 60, 0),
+                                               (2, 64, 60, 1), (5, 130, 126, 0), (1, 300, 301, 0)])
+def test_top_error_selection_at_the_edges(frames, h, w, offset):
+    """Frames of a few pixels, frame sizes that are and are not multiples of
+    four, images that start off 16-byte alignment (one float in), errors that
+    share their leading digits or are all alike: the oracle's masks."""
+    from paper_2404_19706_amd import mapping
+    rng = np.random.default_rng(7)
+    for spread in (0.0, 1e-6, 1.0):
+        Cin = rng.random((frames, h, w, 3)).astype(np.float32)
+        Cr = (Cin + spread * rng.standard_normal(Cin.shape)).astype(np.float32)
+
+        def t(a):
+            buf = torch.zeros(a.size + offset, device="cuda")
+            buf[offset:] = torch.as_tensor(a.ravel())
+            return buf[offset:].view(a.shape)
+        for frac in (0.0, 0.4, 1.0):
+            m = mapping.select_top_error(t(Cr), t(Cin), frac)
+            torch.cuda.synchronize()
+            assert np.array_equal(m.cpu().numpy(), optim.select_top_error(Cr, Cin, frac)), (spread, frac)
