@@ -888,8 +888,13 @@ rtg_status rtg_fuse(int64_t n, int32_t color_width, const int32_t* eta_prev, con
     if (!eta_prev || !eta_cur || !pos_prev || !scale_prev || !rot_prev || !color_prev || !pos || !scale || !rot ||
         !color)
         return RTG_E_INVALID;
-    hipLaunchKernelGGL(k_fuse, dim3(grid_for(n, 256)), dim3(256), 0, S(stream), n, color_width, eta_prev, eta_cur,
-                       pos_prev, scale_prev, rot_prev, color_prev, pos, scale, rot, color);
+    const FuseArrays A{{pos_prev, scale_prev, rot_prev, color_prev}, {pos, scale, rot, color}, {3, 3, 4, color_width}};
+    uintptr_t al = 0;
+    for (int k = 0; k < 4; ++k) al |= reinterpret_cast<uintptr_t>(A.prev[k]) | reinterpret_cast<uintptr_t>(A.cur[k]);
+    if ((al & 15) == 0)
+        hipLaunchKernelGGL(k_fuse<true>, dim3(grid_for(n, 256)), dim3(256), 0, S(stream), n, eta_prev, eta_cur, A);
+    else
+        hipLaunchKernelGGL(k_fuse<false>, dim3(grid_for(n, 256)), dim3(256), 0, S(stream), n, eta_prev, eta_cur, A);
     return launched();
 }
 

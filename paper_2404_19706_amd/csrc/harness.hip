@@ -164,6 +164,11 @@ struct AdamArgs {
     int32_t K;   // colour parameters per channel: 1 (RGB) or (D+1)^2 (SH)
 };
 
+// A workgroup lists the unstable ones of its 256 rows and walks their values
+// by elements, neighbouring lanes neighbouring values of a row, so that the
+// moments and wide SH rows are read contiguously (a thread per row read them
+// at a stride of 52 to 232 bytes).  Bound by memory: seven accesses per value,
+// whole lines where the unstable rows are scattered.
 __global__ __launch_bounds__(256) void k_adam(int64_t N, float* __restrict__ pos, float* __restrict__ scale,
                                               float* __restrict__ rot, float* __restrict__ col,
                                               const uint8_t* __restrict__ unstable,
@@ -171,28 +176,58 @@ __global__ __launch_bounds__(256) void k_adam(int64_t N, float* __restrict__ pos
                                               const float* __restrict__ grot, const float* __restrict__ gcol,
                                               float* __restrict__ m, float* __restrict__ v,
                                               const int32_t* __restrict__ step, AdamArgs a) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N || !unstable[i]) return;
-    float t = (float)step[0];
-    float bc1 = 1.f - powf(a.b1, t), bc2 = 1.f - powf(a.b2, t);
-    const int64_t stride = 10 + 3 * (int64_t)a.K;
-    float* mi = m + stride * i;
-    float* vi = v + stride * i;
-    auto upd = [&](int k, float g) {
-        float mk = a.b1 * mi[k] + (1.f - a.b1) * g;
-        float vk = a.b2 * vi[k] + (1.f - a.b2) * g * g;
-        mi[k] = mk;
-        vi[k] = vk;
-        return (mk / bc1) / (sqrtf(vk / bc2) + a.eps);
-    };
-    for (int c = 0; c < 3; ++c) pos[3 * i + c] -= a.lr_pos * upd(c, gpos[3 * i + c]);
-    for (int c = 0; c < 3; ++c) {
-        float s = scale[3 * i + c];
-        scale[3 * i + c] = s * __expf(-a.lr_scale * upd(3 + c, s * gscale[3 * i + c]));
+    __shared__ uint16_t list[256];
+    __shared__ uint32_t wc[4];
+    const int64_t i0 = (int64_t)blockIdx.x * 256;
+    const bool un = i0 + threadIdx.x < N && unstable[i0 + threadIdx.x] != 0;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const uint64_t bits = ballot(un);
+    if (lane == 0) wc[wv] = (uint32_t)__builtin_popcountll(bits);
+    __syncthreads();
+    uint32_t at = 0;
+    for (int k = 0; k < wv; ++k) at += wc[k];
+    if (un) list[at + (uint32_t)__builtin_popcountll(bits & ((1ull << lane) - 1ull))] = (uint16_t)threadIdx.x;
+    const uint32_t rows = (wc[0] + wc[1]) + (wc[2] + wc[3]);
+    __syncthreads();
+    if (rows == 0) return;
+    const float t = (float)step[0];
+    const float bc1 = 1.f - powf(a.b1, t), bc2 = 1.f - powf(a.b2, t);
+    const uint32_t K3 = 3u * (uint32_t)a.K, W = 10u + K3, tot = rows * W;
+    // e / W for e < 256 W, W <= 58: as for a 2^-20 reciprocal above 1 / W
+    const uint32_t inv = (1u << 20) / W + 1u;
+    for (uint32_t e = threadIdx.x; e < tot; e += 256u) {
+        const uint32_t r = (e * inv) >> 20, k = e - r * W;
+        const int64_t i = i0 + list[r];
+        float* __restrict__ p;
+        const float* __restrict__ g;
+        float lr;
+        if (k < 3u) {
+            p = pos + 3 * i + k;
+            g = gpos + 3 * i + k;
+            lr = a.lr_pos;
+        } else if (k < 6u) {
+            p = scale + 3 * i + (k - 3u);
+            g = gscale + 3 * i + (k - 3u);
+            lr = a.lr_scale;
+        } else if (k < 10u) {
+            p = rot + 4 * i + (k - 6u);
+            g = grot + 4 * i + (k - 6u);
+            lr = a.lr_rot;
+        } else {
+            p = col + (int64_t)K3 * i + (k - 10u);
+            g = gcol + (int64_t)K3 * i + (k - 10u);
+            lr = k < 13u ? a.lr_col : a.lr_rest;
+        }
+        const int64_t q = (int64_t)W * i + k;
+        const bool log_scale = k >= 3u && k < 6u;   // scales move in their logarithm
+        const float x = *p, gx = log_scale ? x * *g : *g;
+        const float mk = a.b1 * m[q] + (1.f - a.b1) * gx;
+        const float vk = a.b2 * v[q] + (1.f - a.b2) * gx * gx;
+        m[q] = mk;
+        v[q] = vk;
+        const float u = (mk / bc1) / (sqrtf(vk / bc2) + a.eps);
+        *p = log_scale ? x * __expf(-lr * u) : x - lr * u;
     }
-    for (int c = 0; c < 4; ++c) rot[4 * i + c] -= a.lr_rot * upd(6 + c, grot[4 * i + c]);
-    const int64_t cb = 3 * (int64_t)a.K * i;
-    for (int c = 0; c < 3 * a.K; ++c) col[cb + c] -= (c < 3 ? a.lr_col : a.lr_rest) * upd(10 + c, gcol[cb + c]);
 }
 
 }  // namespace rtg

@@ -47,31 +47,57 @@ __global__ __launch_bounds__(256) void k_reg_l2(int64_t n, double w_reg, const u
 
 // Eq. 9 per Gaussian: w = (eta' - eta_prev) / eta' (a binary32 division of
 // the two counts; 1 when eta' = 0), G = fl32(fl32((1 - w) G_prev) +
-// fl32(w G')) for every optimised value, written over G'.
-__global__ __launch_bounds__(256) void k_fuse(int64_t n, int32_t ncol, const int32_t* __restrict__ eta_prev,
-                                              const int32_t* __restrict__ eta_cur,
-                                              const float* __restrict__ pos_prev,
-                                              const float* __restrict__ scale_prev,
-                                              const float* __restrict__ rot_prev,
-                                              const float* __restrict__ col_prev, float* __restrict__ pos,
-                                              float* __restrict__ scale, float* __restrict__ rot,
-                                              float* __restrict__ col) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const int32_t ec = eta_cur[i];
-    const float w = ec != 0 ? (float)(ec - eta_prev[i]) / (float)ec : 1.f;
-    const float v = 1.f - w;
-    auto mix = [&](const float* g0, float* g1, int64_t base, int cnt) {
-        for (int c = 0; c < cnt; ++c) {
-            const float a = v * g0[base + c];
-            const float b = w * g1[base + c];
-            g1[base + c] = a + b;
+// fl32(w G')) for every optimised value, written over G'.  A workgroup forms
+// the weights of 256 rows once and then walks each array's part of them by
+// elements (V4: 16-byte aligned arrays, four per access), so that wide SH
+// rows are read contiguously; a thread per row read 48 floats at a stride
+// of 192 bytes.  Bound by memory: 12 bytes per value.
+struct FuseArrays {
+    const float* prev[4];
+    float* cur[4];
+    int32_t width[4];
+};
+
+template <bool V4>
+__global__ __launch_bounds__(256) void k_fuse(int64_t n, const int32_t* __restrict__ eta_prev,
+                                              const int32_t* __restrict__ eta_cur, FuseArrays A) {
+    __shared__ float wt[256];
+    const int64_t i0 = (int64_t)blockIdx.x * 256;
+    const uint32_t rows = (uint32_t)(n - i0 < 256 ? n - i0 : 256);
+    if (threadIdx.x < rows) {
+        const int32_t ec = eta_cur[i0 + threadIdx.x];
+        wt[threadIdx.x] = ec != 0 ? (float)(ec - eta_prev[i0 + threadIdx.x]) / (float)ec : 1.f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t W = (uint32_t)A.width[k], tot = rows * W;
+        // e / W for e < 256 W, W <= 48: the reciprocal is above 1 / W by less
+        // than 2^-20, e times that by less than 1 / W
+        const uint32_t inv = (1u << 20) / W + 1u;
+        const float* __restrict__ g0 = A.prev[k] + i0 * W;
+        float* __restrict__ g1 = A.cur[k] + i0 * W;
+        auto mix = [&](uint32_t e, float a, float b) {
+            const float w = wt[(e * inv) >> 20];
+            const float x = (1.f - w) * a, y = w * b;
+            return x + y;
+        };
+        if constexpr (V4) {
+            for (uint32_t e = 4u * threadIdx.x; e + 4u <= tot; e += 1024u) {
+                const float4 a = *reinterpret_cast<const float4*>(g0 + e);
+                float4 b = *reinterpret_cast<const float4*>(g1 + e);
+                b.x = mix(e, a.x, b.x);
+                b.y = mix(e + 1u, a.y, b.y);
+                b.z = mix(e + 2u, a.z, b.z);
+                b.w = mix(e + 3u, a.w, b.w);
+                *reinterpret_cast<float4*>(g1 + e) = b;
+            }
+            const uint32_t e = (tot & ~3u) + threadIdx.x;
+            if (e < tot) g1[e] = mix(e, g0[e], g1[e]);
+        } else {
+            for (uint32_t e = threadIdx.x; e < tot; e += 256u) g1[e] = mix(e, g0[e], g1[e]);
         }
-    };
-    mix(pos_prev, pos, 3 * i, 3);
-    mix(scale_prev, scale, 3 * i, 3);
-    mix(rot_prev, rot, 4 * i, 4);
-    mix(col_prev, col, (int64_t)ncol * i, ncol);
+    }
 }
 
 // ---- top colour-error selection ---------------------------------------------
