@@ -84,6 +84,9 @@ hipStream_t S(void* s) { return static_cast<hipStream_t>(s); }
 
 rtg_status launched() { return hipGetLastError() == hipSuccess ? RTG_OK : RTG_E_HIP; }
 
+// Workgroups of k_fill_u8: 16 bytes per thread and step.
+unsigned fill_grid(size_t n) { return (unsigned)std::max<size_t>(1, std::min<size_t>((n + 4095) / 4096, 4096)); }
+
 unsigned grid_for(int64_t n, int per_block) { return (unsigned)((n + per_block - 1) / per_block); }
 
 // Persistent-grid size per device (CU count x resident blocks per CU).
@@ -387,11 +390,10 @@ rtg_status rtg_unstable_mask(const rtg_plan* p, void* ws, uint8_t* mask_out, voi
     if (!ws_ok(p, ws) || !mask_out) return RTG_E_INVALID;
     WS w = make_ws(p, ws);
     size_t n = (size_t)p->d.F * p->d.W * p->d.H;
-    hipLaunchKernelGGL(k_fill_u8, dim3((unsigned)std::min<size_t>((n + 255) / 256, 65535)), dim3(256), 0, S(stream),
-                       mask_out, n, (uint8_t)0);
+    hipLaunchKernelGGL(k_fill_u8, dim3(fill_grid(n)), dim3(256), 0, S(stream), mask_out, n, (uint8_t)0);
     if (launched() != RTG_OK) return RTG_E_HIP;
     if (p->d.N > 0)
-        hipLaunchKernelGGL(k_unstable_mask, dim3(grid_for(p->d.N, 4)), dim3(256), 0, S(stream), p->d, w, mask_out);
+        hipLaunchKernelGGL(k_unstable_mask, dim3(grid_for(p->d.N, 4 * kMaskGroup)), dim3(256), 0, S(stream), p->d, w, mask_out);
     return launched();
 }
 
@@ -802,8 +804,7 @@ rtg_status rtg_state_update(const rtg_intrinsics* intr, const rtg_adding_params*
     const AddParams a = add_params(prm);
     const Intr c = to_intr(intr);
     const int64_t np = (int64_t)intr->width * intr->height;
-    hipLaunchKernelGGL(k_fill_u8, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 65535)), dim3(256), 0,
-                       S(stream), flag_ws, (size_t)n, (uint8_t)0);
+    hipLaunchKernelGGL(k_fill_u8, dim3(fill_grid((size_t)n)), dim3(256), 0, S(stream), flag_ws, (size_t)n, (uint8_t)0);
     hipLaunchKernelGGL(k_state_flag, dim3(grid_for(np, 256)), dim3(256), 0, S(stream), a, c, color_in, depth_in,
                        color_r, depth_r, index_r, n, (const uint8_t*)unstable, flag_ws);
     hipLaunchKernelGGL(k_state_apply, dim3(grid_for(n, 256)), dim3(256), 0, S(stream), a, n, frame_k,

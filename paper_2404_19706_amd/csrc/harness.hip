@@ -6,10 +6,15 @@
 
 namespace rtg {
 
-__global__ void k_fill_u8(uint8_t* p, size_t n, uint8_t v) {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) p[i] = v;
+// Bytes to v: 16 per store between the first and last aligned address.
+__global__ __launch_bounds__(256) void k_fill_u8(uint8_t* p, size_t n, uint8_t v) {
+    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x, stride = (size_t)gridDim.x * 256;
+    const size_t head = min((size_t)(-(intptr_t)p & 15), n), body = (n - head) / 16, tail = head + 16 * body;
+    const uint32_t q = 0x01010101u * v;
+    uint4* p4 = reinterpret_cast<uint4*>(p + head);
+    for (size_t i = t; i < body; i += stride) p4[i] = make_uint4(q, q, q, q);
+    if (t < head) p[t] = v;
+    if (t < n - tail) p[tail + t] = v;
 }
 
 // Status of the calls on a workspace as an rtg_status value, written on the

@@ -331,30 +331,37 @@ __global__ __launch_bounds__(256) void k_project(Dims d, WS w, const float* __re
     }
 }
 
-// M_unstable (supp. B): one wave per Gaussian; lanes stride over the pixel
-// rectangle of each frame in which the unstable Gaussian is visible and set
-// the mask where the decision d^2 is within the cut-off.
+// M_unstable (supp. B).  A wave takes kMaskGroup Gaussians: its first lanes
+// look up which of them are visible and unstable (usually few), then the
+// whole wave covers the pixel rectangle of each in 8x8 blocks and sets the
+// mask where the decision d^2 is within the cut-off.  With one wave per
+// Gaussian the launch of 125,000 workgroups for 500,000 Gaussians of which
+// 14,000 count took 45 us, and every pixel two integer divisions.
+constexpr int kMaskGroup = 16;
+
 __global__ __launch_bounds__(256) void k_unstable_mask(Dims d, WS w, uint8_t* __restrict__ mask) {
-    int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    int lane = threadIdx.x & 63;
-    if (i >= d.N) return;
-    uint32_t vis = w.vis[i];
-    while (vis) {
-        int f = __builtin_ctz(vis);
-        vis &= vis - 1;
-        int64_t slot = (int64_t)f * d.N + i;
-        float4 h2 = w.rec[4 * slot + 2];
-        if (!rec_unstable(h2)) return;
-        float4 h0 = w.rec[4 * slot + 0];
-        float4 h1 = w.rec[4 * slot + 1];
-        short4 r = w.rect[slot];
-        int rw = r.y - r.x + 1;
-        int n = rw * (r.w - r.z + 1);
-        uint8_t* m = mask + (size_t)f * d.W * d.H;
-        for (int p = lane; p < n; p += 64) {
-            int px = r.x + p % rw, py = r.z + p / rw;
-            float dd = dd_decision(h0.x, h0.y, h0.z, h0.w, h1.x, (float)px + 0.5f, (float)py + 0.5f);
-            if (dd <= d.cutoff2) m[(size_t)py * d.W + px] = 1;
+    const int64_t i0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kMaskGroup;
+    const int lane = threadIdx.x & 63;
+    uint32_t vis = 0;
+    if (lane < kMaskGroup && i0 + lane < d.N) vis = w.vis[i0 + lane];
+    bool un = false;
+    if (vis) un = rec_unstable(w.rec[4 * ((int64_t)__builtin_ctz(vis) * d.N + i0 + lane) + 2]);
+    for (uint64_t m = ballot(un); m != 0; m &= m - 1) {
+        const int l = __builtin_ctzll(m);
+        for (uint32_t fs = (uint32_t)__builtin_amdgcn_readlane((int)vis, l); fs != 0; fs &= fs - 1u) {
+            const int f = __builtin_ctz(fs);
+            const int64_t slot = (int64_t)f * d.N + i0 + l;
+            const float4 h0 = w.rec[4 * slot];
+            const float qc = w.rec[4 * slot + 1].x;
+            const short4 r = w.rect[slot];
+            uint8_t* mf = mask + (size_t)f * d.W * d.H;
+            for (int y0 = r.z; y0 <= r.w; y0 += 8)
+                for (int x0 = r.x; x0 <= r.y; x0 += 8) {
+                    const int px = x0 + (lane & 7), py = y0 + (lane >> 3);
+                    if (px > r.y || py > r.w) continue;
+                    const float dd = dd_decision(h0.x, h0.y, h0.z, h0.w, qc, (float)px + 0.5f, (float)py + 0.5f);
+                    if (dd <= d.cutoff2) mf[(size_t)py * d.W + px] = 1;
+                }
         }
     }
 }

@@ -796,3 +796,21 @@ def test_gpu_gradients_against_finite_differences_of_the_gpu_forward():
     print("GPU FD sanity: %d entries, worst |fd - grad| / group scale %.2e" % (checked, worst), flush=True)
     assert checked >= 40
     assert worst < 2e-2
+
+
+# --------------------------------------- Gaussian groups and ranges at their edges
+
+@pytest.mark.parametrize("n,frames", [(1, 1), (15, 2), (17, 1), (64, 3), (129, 2)])
+def test_unstable_mask_groups_at_the_edges(n, frames):
+    """Groups of Gaussians with a remainder, footprints larger than a block
+    of pixels and cut by the image: bit-exact against the oracle."""
+    cam = small_cam(61, 43, 60.0)
+    rng = np.random.default_rng(n)
+    sc = random_scene(rng, n, spread=1.2, smin=0.02, smax=0.3, unstable_frac=0.5)
+    sc["unstable"][0] = 1
+    poses = np.repeat(identity_pose(), frames, 0)
+    poses[:, 9] += 0.1 * np.arange(frames)
+    rast = _rast(cam, n, frames)
+    m = rast.unstable_mask(dev_params(sc), dev_poses(poses)).cpu().numpy()
+    recs = orc.project(orc.make_params(cam), sc, poses)
+    assert np.array_equal(m, orc.unstable_mask_image(orc.make_params(cam), recs, sc["unstable"]))
