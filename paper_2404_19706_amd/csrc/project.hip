@@ -371,14 +371,13 @@ __global__ __launch_bounds__(256) void k_unstable_mask(Dims d, WS w, uint8_t* __
 // (binary64).  Rows of stable Gaussians are left untouched; unstable rows
 // are always written (zero when no frame sees the Gaussian).  The slot
 // accumulators are cleared as they are consumed.
-__device__ void project_bwd_one(const Dims& d, const WS& w, int64_t i, const float* __restrict__ pos,
+__device__ void project_bwd_one(const Dims& d, const WS& w, int64_t i, uint32_t vis, const float* __restrict__ pos,
                                 const float* __restrict__ scale, const float* __restrict__ rot,
                                 const double* __restrict__ poses, float* __restrict__ d_pos,
                                 float* __restrict__ d_scale, float* __restrict__ d_rot, float* __restrict__ d_opac,
                                 float* __restrict__ d_col, float kc, float kd) {
     double gp[3] = {0, 0, 0}, gs[3] = {0, 0, 0}, gq[4] = {0, 0, 0, 0}, ga = 0, gc[3] = {0, 0, 0};
-    uint32_t vis = w.vis[i];
-    if (vis) {
+    {
         double s[3] = {scale[3 * i], scale[3 * i + 1], scale[3 * i + 2]};
         float qf[4] = {rot[4 * i], rot[4 * i + 1], rot[4 * i + 2], rot[4 * i + 3]};
         double R[9];
@@ -421,7 +420,8 @@ __device__ void project_bwd_one(const Dims& d, const WS& w, int64_t i, const flo
             double y = Rg[1] * v[0] + Rg[4] * v[1] + Rg[7] * v[2];
             double z = Rg[2] * v[0] + Rg[5] * v[1] + Rg[8] * v[2];
             double fx = d.fx, fy = d.fy;
-            double J00 = fx / z, J02 = -fx * x / (z * z), J11 = fy / z, J12 = -fy * y / (z * z);
+            const double iz = 1.0 / z, iz2 = iz * iz, iz3 = iz2 * iz;
+            double J00 = fx * iz, J02 = -fx * x * iz2, J11 = fy * iz, J12 = -fy * y * iz2;
             double M[6];
             for (int kk = 0; kk < 3; ++kk) {
                 M[kk] = J00 * Rg[kk * 3 + 0] + J02 * Rg[kk * 3 + 2];
@@ -436,7 +436,8 @@ __device__ void project_bwd_one(const Dims& d, const WS& w, int64_t i, const flo
             double sxy = T[0] * M[3] + T[1] * M[4] + T[2] * M[5];
             double syy = T[3] * M[3] + T[4] * M[4] + T[5] * M[5] + d.dilation;
             double det = sxx * syy - sxy * sxy;
-            double Qa = syy / det, Qb = -sxy / det, Qc = sxx / det;
+            const double idet = 1.0 / det;
+            double Qa = syy * idet, Qb = -sxy * idet, Qc = sxx * idet;
             double GS00, GS01, GS11, dmx, dmy;
             if (rec_precise(w.rec[4 * slot + 2])) {
                 // precise slot: slots 0-4 hold m = sum g e and M = sum g e e^T
@@ -481,17 +482,16 @@ __device__ void project_bwd_one(const Dims& d, const WS& w, int64_t i, const flo
             double dJ02 = dM[0] * Rg[2] + dM[1] * Rg[5] + dM[2] * Rg[8];
             double dJ11 = dM[3] * Rg[1] + dM[4] * Rg[4] + dM[5] * Rg[7];
             double dJ12 = dM[3] * Rg[2] + dM[4] * Rg[5] + dM[5] * Rg[8];
-            double z2 = z * z, z3 = z2 * z;
             // depth path: plane branch dD/dpc = a n, dD/dnc = a pc - b; centre branch e on pc.z
             double n0 = R[0 * 3 + k], n1 = R[1 * 3 + k], n2 = R[2 * 3 + k];
             double nc0 = Rg[0] * n0 + Rg[3] * n1 + Rg[6] * n2;
             double nc1 = Rg[1] * n0 + Rg[4] * n1 + Rg[7] * n2;
             double nc2 = Rg[2] * n0 + Rg[5] * n1 + Rg[8] * n2;
             double pa = ga2.y, pb0 = ga2.z, pb1 = ga2.w, pb2 = ga3.x, pe = ga3.y;
-            double dpc0 = pa * nc0 + dJ02 * (-fx / z2) + dmx * fx / z;
-            double dpc1 = pa * nc1 + dJ12 * (-fy / z2) + dmy * fy / z;
-            double dpc2 = pa * nc2 + pe + dJ00 * (-fx / z2) + dJ02 * (2.0 * fx * x / z3) + dJ11 * (-fy / z2) +
-                          dJ12 * (2.0 * fy * y / z3) - dmx * fx * x / z2 - dmy * fy * y / z2;
+            double dpc0 = pa * nc0 + dJ02 * (-fx * iz2) + dmx * fx * iz;
+            double dpc1 = pa * nc1 + dJ12 * (-fy * iz2) + dmy * fy * iz;
+            double dpc2 = pa * nc2 + pe + dJ00 * (-fx * iz2) + dJ02 * (2.0 * fx * x * iz3) + dJ11 * (-fy * iz2) +
+                          dJ12 * (2.0 * fy * y * iz3) - dmx * fx * x * iz2 - dmy * fy * y * iz2;
             double dnc0 = pa * x - pb0, dnc1 = pa * y - pb1, dnc2 = pa * z - pb2;
             for (int a = 0; a < 3; ++a) {
                 gp[a] += Rg[a * 3] * dpc0 + Rg[a * 3 + 1] * dpc1 + Rg[a * 3 + 2] * dpc2;
@@ -551,11 +551,12 @@ __device__ void project_bwd_one(const Dims& d, const WS& w, int64_t i, const flo
     d_opac[i] = (float)ga;
 }
 
-// Unstable Gaussians can be a few percent of the set, so a thread per
-// Gaussian would run the double-precision chain in nearly every wave with one
+// Unstable Gaussians that a frame sees can be a few percent of the set, so a
+// thread per Gaussian would run the double-precision chain in nearly every wave with one
 // or two lanes active.  Each workgroup walks its range of Gaussians 256 at a
-// time, queues the unstable ones in LDS, and runs the chain on the queue
-// whenever it holds a full workgroup's worth (and at the end of the range).
+// time, writes the zero rows of the unstable ones that no frame sees, queues
+// the others in LDS, and runs the chain on the queue whenever it holds a full
+// workgroup's worth (and at the end of the range).
 // With `on` set the camera-space gradients hold the L1 loss at unit
 // upstream (the backward compositing's L1 form): every workgroup adds up the
 // per-workgroup counts of M_D pixels (integers, so all agree) to form the
@@ -718,7 +719,7 @@ __global__ __launch_bounds__(256) void k_project_bwd(Dims d, WS w, const float* 
                                                      float* __restrict__ d_pos, float* __restrict__ d_scale,
                                                      float* __restrict__ d_rot, float* __restrict__ d_opac,
                                                      float* __restrict__ d_col, L1Scale ls) {
-    __shared__ uint32_t q[512];
+    __shared__ uint32_t q[512], qv[512];   // place in the range, frames
     __shared__ uint32_t qn;
     float kc, kd;
     l1_scales(w, ls, blockIdx.x == 0, kc, kd);
@@ -728,15 +729,33 @@ __global__ __launch_bounds__(256) void k_project_bwd(Dims d, WS w, const float* 
     __syncthreads();
     for (int64_t base = r0; base < r1; base += 256) {
         const int64_t i = base + threadIdx.x;
-        if (i < r1 && unstable[i]) q[atomicAdd(&qn, 1u)] = (uint32_t)(i - r0);
+        if (i < r1 && unstable[i]) {
+            const uint32_t vis = w.vis[i];
+            if (vis) {
+                const uint32_t at = atomicAdd(&qn, 1u);
+                q[at] = (uint32_t)(i - r0);
+                qv[at] = vis;
+            } else {
+                // (with SH colour k_sh_bwd has written the other two)
+                for (int a = 0; a < 3; ++a) {
+                    if (d.sh_deg == 0) {
+                        d_pos[3 * i + a] = 0.f;
+                        d_col[3 * i + a] = 0.f;
+                    }
+                    d_scale[3 * i + a] = 0.f;
+                }
+                for (int a = 0; a < 4; ++a) d_rot[4 * i + a] = 0.f;
+                d_opac[i] = 0.f;
+            }
+        }
         __syncthreads();
         const uint32_t n = qn;
         if (n >= 256 || base + 256 >= r1) {
             if (threadIdx.x < n)
-                project_bwd_one(d, w, r0 + q[threadIdx.x], pos, scale, rot, poses, d_pos, d_scale, d_rot, d_opac,
+                project_bwd_one(d, w, r0 + q[threadIdx.x], qv[threadIdx.x], pos, scale, rot, poses, d_pos, d_scale, d_rot, d_opac,
                                 d_col, kc, kd);
             if (n > 256 && threadIdx.x + 256 < n)
-                project_bwd_one(d, w, r0 + q[threadIdx.x + 256], pos, scale, rot, poses, d_pos, d_scale, d_rot,
+                project_bwd_one(d, w, r0 + q[threadIdx.x + 256], qv[threadIdx.x + 256], pos, scale, rot, poses, d_pos, d_scale, d_rot,
                                 d_opac, d_col, kc, kd);
             __syncthreads();
             if (threadIdx.x == 0) qn = 0u;

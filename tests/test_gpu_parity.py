@@ -814,3 +814,38 @@ def test_unstable_mask_groups_at_the_edges(n, frames):
     m = rast.unstable_mask(dev_params(sc), dev_poses(poses)).cpu().numpy()
     recs = orc.project(orc.make_params(cam), sc, poses)
     assert np.array_equal(m, orc.unstable_mask_image(orc.make_params(cam), recs, sc["unstable"]))
+
+
+@pytest.mark.parametrize("n", [1, 255, 257, 140_000])
+def test_projection_backward_ranges(n):
+    """Workgroup ranges of 256 and more Gaussians with few and many of them
+    in view: unstable rows in view equal the oracle's chain, unstable rows
+    out of view are zero, stable rows are not touched."""
+    cam = small_cam(61, 43, 60.0)
+    rng = np.random.default_rng(n)
+    k = min(n, 300)
+    sc = random_scene(rng, n, spread=0.8, unstable_frac=0.5)
+    hidden = np.ones(n, bool)
+    hidden[rng.permutation(n)[:k]] = False
+    sc["pos"][hidden, 2] = -3.0                    # behind the camera
+    poses = identity_pose()
+    mask = np.ones((1, 43, 61), np.uint8)
+    rast = _rast(cam, n, 1)
+    params, dp = dev_params(sc), dev_poses(poses)
+    C, D, T, I, ws = rast.forward(params, dp, dev_mask(mask))
+    gC, gD = random_upstream(mask, seed=3)
+    grads = {key: torch.full_like(v, 7.0) for key, v in rast.alloc_grads().items()}
+    rast.backward_into(ws, params, dp, D, T, I, torch.as_tensor(gC).cuda(), torch.as_tensor(gD).cuda(), grads)
+    torch.cuda.synchronize()
+    sub = {key: v[~hidden] for key, v in sc.items()}
+    P = orc.make_params(cam)
+    recs = orc.project(P, sub, poses)
+    pix = orc.masked_pixels(mask)
+    f, x, y = pix[:, 0], pix[:, 1], pix[:, 2]
+    ref = orc.backward(P, recs, sub, poses, pix, gC[f, y, x], gD[f, y, x])
+    un = sc["unstable"] != 0
+    for key in ("pos", "scale", "rot", "opacity", "color"):
+        g = grads[key].cpu().numpy().reshape(n, -1)
+        assert (g[~un] == 7.0).all() and (g[un & hidden] == 0.0).all(), key
+        r = np.asarray(ref[key]).reshape(k, -1)[un[~hidden]]
+        assert np.linalg.norm(g[un & ~hidden] - r) <= 1e-4 * max(np.linalg.norm(r), 1e-30), key
