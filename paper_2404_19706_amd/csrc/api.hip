@@ -441,6 +441,19 @@ SideStream* side_stream(hipStream_t caller) {
 
 rtg_status bin_impl(const rtg_plan* p, void* ws, const uint8_t* mask, void* stream, bool allow_side);
 
+// Binning by one workgroup per tile (k_tile_gather).  Measured against the
+// general path, us per step of one frame unless said (Gaussians, tiles):
+// 2,000, 48: 52 / 68; 10,000, 117: 55 / 68; 2,000, 1,000: 69 / 76; 20,000,
+// 300: 66 / 72; 3 frames of 10,000, 741: 73 / 78; 16,000, 640: 70 / 74;
+// 30,000, 300: 73 / 74; 10,000, 1,000: 78 / 77; 40,000, 300: 80 / 77; 30,000,
+// 1,000: 100 / 82.  (The configurations of the sort and of the staging mean
+// the general path.)
+bool bin_gathers(const rtg_plan* p) {
+    const int64_t nft = (int64_t)p->d.F * p->d.ntiles;
+    return p->cfg.sort_cap == 0 && p->cfg.stage_cap == 0 && p->d.N > 0 && p->d.N <= 24576 && nft <= 1000 &&
+           p->d.N * nft <= (int64_t(1) << 23);
+}
+
 }  // namespace
 
 rtg_status rtg_bin(const rtg_plan* p, void* ws, const uint8_t* mask, void* stream) {
@@ -462,6 +475,12 @@ rtg_status bin_impl(const rtg_plan* p, void* ws, const uint8_t* mask, void* stre
         m = eff;
     }
     int64_t nft = (int64_t)d.F * d.ntiles;
+    if (bin_gathers(p)) {
+        hipLaunchKernelGGL(k_tile_gather, dim3((unsigned)nft), dim3(256), 0, S(stream), d, w, m);
+        hipLaunchKernelGGL(k_tile_items, dim3(1), dim3(1024), 0, S(stream), d, w);
+        hipLaunchKernelGGL(k_tile_put, dim3((unsigned)nft), dim3(256), 0, S(stream), d, w);
+        return launched();
+    }
     hipLaunchKernelGGL(k_tile_pixels, dim3(grid_for(nft, 4)), dim3(256), 0, S(stream), d, w, m);
     const unsigned nbb = (unsigned)((int64_t)d.F * d.nbpf * d.nchunks);
     const size_t lds = 4 * ((size_t)d.chunk + (d.chunk + 31) / 32);
@@ -708,7 +727,7 @@ rtg_status rtg_read_status(const rtg_plan* p, void* ws, int64_t* counts, void* s
     // the work counters are summed on the device; one 128-byte header copy
     // then carries everything (no host-side buffers)
     WS w = make_ws(p, ws);
-    const uint32_t nbb = (uint32_t)((int64_t)p->d.F * p->d.nbpf * p->d.nchunks);
+    const uint32_t nbb = bin_gathers(p) ? 0u : (uint32_t)((int64_t)p->d.F * p->d.nbpf * p->d.nchunks);
     hipLaunchKernelGGL(k_sum_counters, dim3(1), dim3(1024), 0, S(stream), w, nbb);
     if (launched() != RTG_OK) return RTG_E_HIP;
     Hdr h;

@@ -20,7 +20,8 @@
 //      rounds above), with the sorted slot ids and the pair-order record
 //      copy for the compositing kernels.
 // Keys are unique inside a tile, so the order equals the full (frame, tile,
-// depth, index) sort and is deterministic.
+// depth, index) sort and is deterministic.  Plans of few Gaussians and tiles
+// take three launches of one workgroup per tile instead (end of the file).
 #include "rtg_common.h"
 
 namespace rtg {
@@ -58,32 +59,37 @@ __global__ __launch_bounds__(256) void k_filter50(Dims d, const uint8_t* __restr
     }
 }
 
-// Masked pixels of each (frame, tile), compacted in 8x8-block order (blocks
+// Masked pixels of one (frame, tile), compacted in 8x8-block order (blocks
 // in raster order, raster order inside a block), so a full tile's packs of
-// 64 pixels are 8x8 squares; one wave per tile.
-// The first workgroup also clears the staging region counters of step 2.
-__global__ __launch_bounds__(256) void k_tile_pixels(Dims d, WS w, const uint8_t* __restrict__ mask) {
-    if (blockIdx.x == 0) w.stagec[threadIdx.x] = 0u;
-    int64_t ft = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    int lane = threadIdx.x & 63;
-    if (ft >= (int64_t)d.F * d.ntiles) return;
-    int f = (int)(ft / d.ntiles), t = (int)(ft % d.ntiles);
-    int ox = (t % d.tx) * d.tw, oy = (t / d.tx) * d.th;
+// 64 pixels are 8x8 squares; one wave.
+__device__ __forceinline__ uint32_t tile_pixel_list(const Dims& d, const WS& w, const uint8_t* mask, int f, int t,
+                                                    int64_t ft, int lane) {
+    const int ox = (t % d.tx) * d.tw, oy = (t / d.tx) * d.th;
     const uint8_t* m = mask + (size_t)f * d.W * d.H;
     uint8_t* pl = w.pix + ft * d.tarea;
     const int bxn = d.tw >> 3;
     uint32_t cnt = 0;
-    uint64_t lt = (1ull << lane) - 1ull;
+    const uint64_t lt = (1ull << lane) - 1ull;
     for (int blk = 0; blk < d.tarea >> 6; ++blk) {
-        int lx = (blk % bxn) * 8 + (lane & 7), ly = (blk / bxn) * 8 + (lane >> 3);
-        int l = ly * d.tw + lx;
-        int px = ox + lx, py = oy + ly;
-        bool on = px < d.W && py < d.H && m[(size_t)py * d.W + px] != 0;
-        uint64_t b = ballot(on);
-        if (on) pl[cnt + __builtin_popcountll(b & lt)] = (uint8_t)l;
+        const int lx = (blk % bxn) * 8 + (lane & 7), ly = (blk / bxn) * 8 + (lane >> 3);
+        const int px = ox + lx, py = oy + ly;
+        const bool on = px < d.W && py < d.H && m[(size_t)py * d.W + px] != 0;
+        const uint64_t b = ballot(on);
+        if (on) pl[cnt + __builtin_popcountll(b & lt)] = (uint8_t)(ly * d.tw + lx);
         cnt += (uint32_t)__builtin_popcountll(b);
     }
     if (lane == 0) w.tile_npx[ft] = cnt;
+    return cnt;
+}
+
+// One wave per tile; the first workgroup also clears the staging region
+// counters of step 2.
+__global__ __launch_bounds__(256) void k_tile_pixels(Dims d, WS w, const uint8_t* __restrict__ mask) {
+    if (blockIdx.x == 0) w.stagec[threadIdx.x] = 0u;
+    const int64_t ft = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (ft >= (int64_t)d.F * d.ntiles) return;
+    const int f = (int)(ft / d.ntiles);
+    (void)tile_pixel_list(d, w, mask, f, (int)(ft - (int64_t)f * d.ntiles), ft, threadIdx.x & 63);
 }
 
 __device__ __forceinline__ void tile_range(const Dims& d, short4 r, int& a0, int& a1, int& b0, int& b1) {
@@ -566,6 +572,19 @@ __device__ __forceinline__ uint32_t class_field(unsigned long long lo, unsigned 
     return (uint32_t)(((c < 4 ? lo : hi) >> (16 * (c & 3))) & 0xffffu);
 }
 
+// The work items of tile e, the k-th of this thread's quad, given the
+// per-class item bases.
+__device__ __forceinline__ void emit_items(const Dims& d, const WS& w, int64_t e, int k, const TileQuad& t,
+                                           const QuadScan& s, const uint32_t* cbase) {
+    const uint32_t packs = (t.q[k] + 63) >> 6;
+    const int c = t.cls[k];
+    uint32_t oi = cbase[c] + class_field(s.oc0, s.oc1, c);
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+        if (j < k && t.cls[j] == c) oi += (t.q[j] + 63) >> 6;
+    for (uint32_t pk = 0; pk < packs; ++pk) w.items[oi + pk] = (uint32_t)e * (uint32_t)d.ppt + pk;
+}
+
 // Pair ranges, long lists and work items of this thread's four tiles, given
 // the chunk's pair base co, long-list base cb and per-class item bases.
 __device__ __forceinline__ void emit_quad(const Dims& d, const WS& w, int64_t e0, int64_t total, const TileQuad& t,
@@ -582,13 +601,7 @@ __device__ __forceinline__ void emit_quad(const Dims& d, const WS& w, int64_t e0
             w.tile_start[e] = st;
             w.tile_end[e] = overflow ? 0u : st + t.v[k];
             if (!overflow && t.v[k] > cap) w.bigl[ob++] = (uint32_t)e;
-            const uint32_t packs = (t.q[k] + 63) >> 6;
-            const int c = t.cls[k];
-            uint32_t oi = cbase[c] + class_field(s.oc0, s.oc1, c);
-#pragma unroll
-            for (int j = 0; j < k; ++j)
-                if (t.cls[j] == c) oi += (t.q[j] + 63) >> 6;
-            for (uint32_t pk = 0; pk < packs; ++pk) w.items[oi + pk] = (uint32_t)e * (uint32_t)d.ppt + pk;
+            emit_items(d, w, e, k, t, s, cbase);
         }
         o += t.v[k];
     }
@@ -908,8 +921,8 @@ __device__ __forceinline__ void rs_step(unsigned long long (&a)[1 << EB], uint32
     }
 }
 
-// The n <= P keys at kin (global), padded with the largest key, sorted into
-// K[0..P) in plain order (ends with a workgroup barrier).
+// The n <= P keys at kin (global, or K itself), padded with the largest key,
+// sorted into K[0..P) in plain order (ends with a workgroup barrier).
 template <int EB>
 __device__ void bitonic_regs(unsigned long long* K, const unsigned long long* kin, uint32_t n) {
     static_assert(EB >= 1 && EB <= 4, "2 to 16 keys per thread");
@@ -922,6 +935,7 @@ __device__ void bitonic_regs(unsigned long long* K, const unsigned long long* ki
         const uint32_t g = t + 256u * (uint32_t)m;
         a[m] = g < n ? kin[g] : ~0ull;
     }
+    if (kin == K) __syncthreads();
     for (int q = 1; q <= pb; ++q) {
         const uint32_t k = 1u << q;
         for (int b = q - 1; b >= 0;) {
@@ -950,9 +964,9 @@ __device__ void bitonic_regs(unsigned long long* K, const unsigned long long* ki
     __syncthreads();
 }
 
-// The n keys at kin sorted into K[0..P) (P the power of two >= n, at most
-// kSortLds) by a 256-thread workgroup: registers from 1024 keys on, LDS
-// steps below.
+// The n keys at kin (global, or K itself) sorted into K[0..P) (P the power of
+// two >= n, at most kSortLds) by a 256-thread workgroup: registers from 1024
+// keys on, LDS steps below.
 __device__ __forceinline__ void sort_keys(unsigned long long* K, const unsigned long long* kin, uint32_t n) {
     static_assert(kSortLds == (256 << 4), "the register sort covers kSortLds keys");
     uint32_t P = 1;
@@ -1187,11 +1201,77 @@ __device__ __forceinline__ uint32_t co_rank(uint32_t k, KA A, uint32_t la, KB B,
     return lo;
 }
 
-// Tiles are taken from a queue (longest lists first).  Merge rounds work in
-// output windows of up to kBigLds keys, which never straddle two runs being
-// merged: the co-ranks of all window starts of a round are searched in
-// parallel (one thread each), then each window's inputs are staged in LDS
-// and merged by the whole workgroup.
+// Merge rounds of one list whose runs of big_chunk keys are sorted, by the
+// whole workgroup: output windows of up to LDSK keys, which never straddle
+// two runs being merged; the co-ranks of all window starts of a round are
+// searched in parallel (one thread each, NCR - 1 windows at a time), then each
+// window's inputs are staged in L and merged.  The keys are at `at` of w.keys
+// (and of the merge buffer); the last round writes the records from list
+// position `start` on.
+template <int LDSK, int NCR>
+__device__ void merge_runs(const WS& w, unsigned long long* L, uint32_t* cr, uint32_t C, uint32_t at, uint32_t start,
+                           uint32_t n, uint32_t fbase) {
+    unsigned long long* S0 = w.keys + at;
+    unsigned long long* S1 = w.scratch + at;
+    // pairwise merges: runs of width -> 2 width (a list of one run
+    // was finished by its run sort)
+    unsigned long long *src = S0, *dst = S1;
+    for (uint32_t width = C; width < n; width <<= 1) {
+        const bool last = 2 * width >= n;
+        const uint32_t win = min((uint32_t)LDSK, 2 * width);
+        const uint32_t nwin = (n + win - 1) / win;
+        for (uint32_t mb = 0; mb < nwin; mb += NCR - 1) {
+            const uint32_t me = min(mb + (uint32_t)(NCR - 1), nwin);
+            for (uint32_t m = mb + threadIdx.x; m < me; m += blockDim.x) {
+                const uint32_t r0 = (m * win) / (2 * width) * (2 * width);
+                const uint32_t la = min(width, n - r0), lb = min(width, n - r0 - la);
+                cr[m - mb] = co_rank(m * win - r0, src + r0, la, src + r0 + la, lb);
+            }
+            __syncthreads();
+            for (uint32_t m = mb; m < me; ++m) {
+                const uint32_t r0 = (m * win) / (2 * width) * (2 * width);
+                const uint32_t la = min(width, n - r0), lb = min(width, n - r0 - la);
+                const uint32_t k0 = m * win - r0, k1 = min(k0 + win, la + lb);
+                const uint32_t a0 = cr[m - mb];
+                const uint32_t a1 = (k1 == la + lb) ? la : (m + 1 < me ? cr[m + 1 - mb] : 0u);
+                // (a window that does not end its runs is never the last of a batch
+                // unless another batch follows; that case is handled below)
+                uint32_t a1f = a1;
+                if (k1 != la + lb && m + 1 == me)
+                    a1f = co_rank(k1, src + r0, la, src + r0 + la, lb);
+                const uint32_t b0 = k0 - a0, b1 = k1 - a1f;
+                const uint32_t na = a1f - a0, nb = b1 - b0;
+                const unsigned long long* A = src + r0;
+                const unsigned long long* B = src + r0 + la;
+                for (uint32_t j = threadIdx.x; j < na; j += blockDim.x) L[j] = A[a0 + j];
+                for (uint32_t j = threadIdx.x; j < nb; j += blockDim.x) L[na + j] = B[b0 + j];
+                __syncthreads();
+                const uint32_t mm = k1 - k0;
+                const uint32_t per = (mm + blockDim.x - 1) / blockDim.x;
+                const uint32_t q0 = min(threadIdx.x * per, mm), q1 = min(q0 + per, mm);
+                if (q0 < q1) {
+                    uint32_t ia = co_rank(q0, L, na, L + na, nb), ib = q0 - ia;
+                    for (uint32_t q = q0; q < q1; ++q) {
+                        const bool takeA = ib >= nb || (ia < na && L[ia] < L[na + ib]);
+                        const unsigned long long v = takeA ? L[ia] : L[na + ib];
+                        ia += takeA;
+                        ib += !takeA;
+                        dst[r0 + k0 + q] = v;
+                    }
+                }
+                __syncthreads();
+                // the final pass: the merged window's records, copied
+                // four threads per record
+                if (last) put_sorted_run(w, dst + r0 + k0, start + r0 + k0, mm, fbase, threadIdx.x, blockDim.x);
+            }
+        }
+        unsigned long long* t = src;
+        src = dst;
+        dst = t;
+    }
+}
+
+// Tiles are taken from a queue (longest lists first).
 __global__ __launch_bounds__(1024) void k_tile_sort_big(Dims d, WS w) {
     __shared__ unsigned long long L[kBigLds];
     __shared__ uint32_t cr[1024];
@@ -1206,69 +1286,194 @@ __global__ __launch_bounds__(1024) void k_tile_sort_big(Dims d, WS w) {
         const uint32_t start = w.tile_start[ft];
         const uint32_t n = w.tile_end[ft] - start;
         const uint32_t fbase = (ft / (uint32_t)d.ntiles) * (uint32_t)d.N;
-        unsigned long long* S0 = w.keys + start;
-        unsigned long long* S1 = w.scratch + start;
-        // pairwise merges: runs of width -> 2 width (a list of one run
-        // was finished by its run sort)
-        unsigned long long *src = S0, *dst = S1;
-        for (uint32_t width = C; width < n; width <<= 1) {
-            const bool last = 2 * width >= n;
-            const uint32_t win = min((uint32_t)kBigLds, 2 * width);
-            const uint32_t nwin = (n + win - 1) / win;
-            for (uint32_t mb = 0; mb < nwin; mb += 1023) {
-                const uint32_t me = min(mb + 1023u, nwin);
-                for (uint32_t m = mb + threadIdx.x; m < me; m += blockDim.x) {
-                    const uint32_t r0 = (m * win) / (2 * width) * (2 * width);
-                    const uint32_t la = min(width, n - r0), lb = min(width, n - r0 - la);
-                    cr[m - mb] = co_rank(m * win - r0, src + r0, la, src + r0 + la, lb);
-                }
-                __syncthreads();
-                for (uint32_t m = mb; m < me; ++m) {
-                    const uint32_t r0 = (m * win) / (2 * width) * (2 * width);
-                    const uint32_t la = min(width, n - r0), lb = min(width, n - r0 - la);
-                    const uint32_t k0 = m * win - r0, k1 = min(k0 + win, la + lb);
-                    const uint32_t a0 = cr[m - mb];
-                    const uint32_t a1 = (k1 == la + lb) ? la : (m + 1 < me ? cr[m + 1 - mb] : 0u);
-                    // (a window that does not end its runs is never the last of a batch
-                    // unless another batch follows; that case is handled below)
-                    uint32_t a1f = a1;
-                    if (k1 != la + lb && m + 1 == me)
-                        a1f = co_rank(k1, src + r0, la, src + r0 + la, lb);
-                    const uint32_t b0 = k0 - a0, b1 = k1 - a1f;
-                    const uint32_t na = a1f - a0, nb = b1 - b0;
-                    const unsigned long long* A = src + r0;
-                    const unsigned long long* B = src + r0 + la;
-                    for (uint32_t j = threadIdx.x; j < na; j += blockDim.x) L[j] = A[a0 + j];
-                    for (uint32_t j = threadIdx.x; j < nb; j += blockDim.x) L[na + j] = B[b0 + j];
-                    __syncthreads();
-                    const uint32_t mm = k1 - k0;
-                    const uint32_t per = (mm + blockDim.x - 1) / blockDim.x;
-                    const uint32_t q0 = min(threadIdx.x * per, mm), q1 = min(q0 + per, mm);
-                    if (q0 < q1) {
-                        uint32_t ia = co_rank(q0, L, na, L + na, nb), ib = q0 - ia;
-                        for (uint32_t q = q0; q < q1; ++q) {
-                            const bool takeA = ib >= nb || (ia < na && L[ia] < L[na + ib]);
-                            const unsigned long long v = takeA ? L[ia] : L[na + ib];
-                            ia += takeA;
-                            ib += !takeA;
-                            dst[r0 + k0 + q] = v;
-                        }
-                    }
-                    __syncthreads();
-                    // the final pass: the merged window's records, copied
-                    // four threads per record
-                    if (last) put_sorted_run(w, dst + r0 + k0, start + r0 + k0, mm, fbase, threadIdx.x, blockDim.x);
-                }
-            }
-            unsigned long long* t = src;
-            src = dst;
-            dst = t;
-        }
+        merge_runs<kBigLds, 1024>(w, L, cr, C, start, start, n, fbase);
         if (threadIdx.x == 0) s_it = gridDim.x + atomicAdd(&w.hdr->q_big, 1u);
         __syncthreads();
         it = s_it;
         __syncthreads();
     }
+}
+
+// ---- few tiles, few Gaussians: one workgroup per tile -----------------------
+//
+// Where a launch costs more than its work (about 3.5 us of host time and 5 us
+// in a chain of dependent ones), the eight launches above become three.  1:
+// every (frame, tile) lists its masked pixels and tests all of the frame's
+// Gaussians: their rectangle (12 bytes each, coalesced), then the thinning
+// rule for those it holds; it sorts its keys in LDS and leaves them at a place
+// claimed with one atomic.  2: one workgroup gives every list its range, in
+// tile order, and makes the work items and the header.  3: the records.  The
+// tests grow with Gaussians x tiles and the claims queue up on one counter;
+// bin_gathers says where that still pays.
+constexpr int kCand = 2048;   // candidates between two passes of the thinning rule
+
+// n <= 256 keys in K sorted in place by a workgroup of 256: a thread per
+// key, its rank the number of smaller keys (read as broadcasts).
+__device__ __forceinline__ void rank_sort_256(unsigned long long* K, uint32_t n) {
+    const uint32_t t = threadIdx.x;
+    const unsigned long long key = t < n ? K[t] : ~0ull;
+    const uint32_t n8 = (n + 7u) & ~7u;
+    if (t >= n && t < n8) K[t] = ~0ull;
+    __syncthreads();
+    uint32_t rk = 0;
+    rank_count<1>(K, n8, &key, &rk);
+    __syncthreads();
+    if (t < n) K[rk] = key;
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(256) void k_tile_gather(Dims d, WS w, const uint8_t* __restrict__ mask) {
+    __shared__ unsigned long long K[kSortLds];
+    __shared__ uint32_t cand[kCand];
+    __shared__ uint32_t nkey, s_start, s_npx;
+    const int64_t ft = blockIdx.x;
+    const int f = (int)(ft / d.ntiles), t = (int)(ft - (int64_t)f * d.ntiles);
+    const int ta = t % d.tx, tb = t / d.tx;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (wv == 0) {
+        const uint32_t npx = tile_pixel_list(d, w, mask, f, t, ft, lane);
+        if (lane == 0) {
+            s_npx = npx;
+            nkey = s_start = 0u;
+        }
+    }
+    __syncthreads();
+    if (s_npx == 0u) {
+        if (tid == 0) w.bigl[ft] = w.tile_end[ft] = 0u;
+        return;
+    }
+    const uint32_t fb = (uint32_t)((int64_t)f * d.N);
+    const uint64_t below = (1ull << lane) - 1ull;
+    const int tx0 = ta * d.tw, tx1 = tx0 + d.tw - 1, ty0 = tb * d.th, ty1 = ty0 + d.th - 1;
+    // every key of the tile into put(position, key).  Each wave takes 256
+    // Gaussians at a time, the next ones loaded while these are tested, and
+    // keeps its own candidates: no barrier until all are done
+    auto gather = [&](auto put) {
+        uint32_t* q = cand + wv * (kCand / 4);
+        uint32_t held = 0;   // wave-uniform
+        auto thin = [&]() {
+            wave_lds_sync();
+            for (uint32_t c = (uint32_t)lane; c < held; c += 64u) {
+                const uint32_t i = q[c], slot = fb + i;
+                int a0, a1, b0, b1, ka, kb;
+                tile_range(d, w.rect[slot], a0, a1, b0, b1);
+                const float4 r0 = w.rec[4ull * slot], r1 = w.rec[4ull * slot + 1];
+                const uint32_t zb = __float_as_uint(w.zkey[slot]);
+                row_span(d, Conic{r0.x, r0.y, r0.z, r0.w, r1.x}, a0, a1, tb, ka, kb);
+                if (ta >= ka && ta <= kb)
+                    put(atomicAdd(&nkey, 1u), ((unsigned long long)zb << 32) | (unsigned long long)i);
+            }
+            wave_lds_sync();
+            held = 0;
+        };
+        uint32_t v[4], vn[4];
+        short4 r[4], rn[4];
+        auto load = [&](int64_t base, uint32_t (&v)[4], short4 (&r)[4]) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t i = min(base + 64 * u + lane, d.N - 1);
+                v[u] = w.vis[i];
+                r[u] = w.rect[fb + i];   // (set only where visible)
+            }
+        };
+        load(256 * wv, v, r);
+        for (int64_t base = 256 * wv; base < d.N; base += 1024) {
+            load(base + 1024, vn, rn);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t i = base + 64 * u + lane;
+                const bool in = i < d.N && ((v[u] >> f) & 1u) && r[u].x <= tx1 && r[u].y >= tx0 && r[u].z <= ty1 &&
+                                r[u].w >= ty0;
+                const uint64_t m = ballot(in);
+                if (in) q[held + (uint32_t)__builtin_popcountll(m & below)] = (uint32_t)i;
+                held += (uint32_t)__builtin_popcountll(m);
+                v[u] = vn[u];
+                r[u] = rn[u];
+            }
+            if (held > (uint32_t)(kCand / 4 - 256)) thin();
+        }
+        thin();
+        __syncthreads();
+    };
+    gather([&](uint32_t at, unsigned long long key) {
+        if (at < (uint32_t)kSortLds) K[at] = key;
+    });
+    const uint32_t n = nkey;
+    if (tid == 0 && n) s_start = atomicAdd(&w.hdr->n_alloc, n);
+    __syncthreads();
+    const uint32_t at = s_start;
+    if (tid == 0) {
+        w.bigl[ft] = at;       // the place of the keys and their number, for
+        w.tile_end[ft] = n;    // the next launch
+    }
+    // (a list that does not fit is not written: the total then exceeds the
+    // capacity too, and the next launch clears every range)
+    if (n == 0u || (uint64_t)at + n > (uint64_t)d.max_pairs) return;
+    unsigned long long* keys = w.keys + at;
+    if (n <= (uint32_t)kSortLds) {
+        if (n <= 256u) rank_sort_256(K, n);
+        else sort_keys(K, K, n);
+        for (uint32_t i = tid; i < n; i += 256u) keys[i] = K[i];
+    } else {
+        // too long for LDS: found again into the global keys and sorted in
+        // runs, which the last launch merges
+        if (tid == 0) nkey = 0u;
+        __syncthreads();
+        gather([&](uint32_t k, unsigned long long key) { keys[k] = key; });
+        for (uint32_t r0 = 0; r0 < n; r0 += (uint32_t)kSortLds) {
+            const uint32_t len = min((uint32_t)kSortLds, n - r0);
+            sort_keys(K, keys + r0, len);
+            for (uint32_t i = tid; i < len; i += 256u) keys[r0 + i] = K[i];
+            __syncthreads();
+        }
+    }
+}
+
+// Ranges, work items and header of at most 4096 tiles whose counts are in
+// tile_end; the pair counter is cleared for the next binning of this
+// projection.
+__global__ __launch_bounds__(1024) void k_tile_items(Dims d, WS w) {
+    __shared__ unsigned long long s64[16];
+    const int tid = threadIdx.x;
+    const int64_t total = (int64_t)d.F * d.ntiles, e0 = 4 * tid;
+    TileQuad t;
+    load_quad(w, e0, total, t);
+    const QuadScan s = quad_scans(t, (uint32_t)d.sort_cap, s64);
+    const unsigned long long K = s.tp;
+    const bool overflow = K > (unsigned long long)d.max_pairs;
+    uint32_t cbase[kCls], acc = 0, o = (uint32_t)s.op;
+#pragma unroll
+    for (int c = 0; c < kCls; ++c) {
+        cbase[c] = acc;
+        acc += class_field(s.tc0, s.tc1, c);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int64_t e = e0 + k;
+        if (e < total) {
+            w.tile_start[e] = overflow ? 0u : o;
+            w.tile_end[e] = overflow ? 0u : o + t.v[k];
+            emit_items(d, w, e, k, t, s, cbase);
+        }
+        o += t.v[k];
+    }
+    if (tid == 0) {
+        write_header(w, K, overflow, (uint32_t)((s.tib >> kPkX) & kPkXMask), (uint32_t)(s.tib >> kPkI),
+                     overflow ? 0u : (uint32_t)(s.tib & kPkBMask));
+        w.hdr->n_alloc = 0u;
+    }
+}
+
+// The sorted lists' slot ids and records, one workgroup per tile.
+__global__ __launch_bounds__(256) void k_tile_put(Dims d, WS w) {
+    __shared__ unsigned long long L[kSortLds];
+    __shared__ uint32_t cr[kCand];
+    const uint32_t ft = blockIdx.x;
+    const uint32_t start = w.tile_start[ft], n = w.tile_end[ft] - start, at = w.bigl[ft];
+    if (n == 0u) return;
+    const uint32_t fb = (ft / (uint32_t)d.ntiles) * (uint32_t)d.N;
+    if (n <= (uint32_t)kSortLds) put_sorted_run(w, w.keys + at, start, n, fb, threadIdx.x, 256u);
+    else merge_runs<kSortLds, kCand>(w, L, cr, (uint32_t)kSortLds, at, start, n, fb);
 }
 
 }  // namespace rtg

@@ -58,7 +58,8 @@ struct Hdr {
     uint32_t pad;
     uint32_t fwd_waves, bwd_waves;   // waves of the last render / backward launch
     uint32_t n_restaged;             // binning blocks whose staging overflowed (rtg_read_status)
-    uint32_t pad2[5];
+    uint32_t n_alloc;                // pairs claimed by k_tile_gather (0 outside a binning)
+    uint32_t pad2[4];
     unsigned long long sums[4];      // per-wave work counters summed (rtg_read_status)
 };
 static_assert(sizeof(Hdr) == 128, "header layout");

@@ -849,3 +849,69 @@ def test_projection_backward_ranges(n):
         assert (g[~un] == 7.0).all() and (g[un & hidden] == 0.0).all(), key
         r = np.asarray(ref[key]).reshape(k, -1)[un[~hidden]]
         assert np.linalg.norm(g[un & ~hidden] - r) <= 1e-4 * max(np.linalg.norm(r), 1e-30), key
+
+
+def _tile_lists(rast, ws, F, nt):
+    tend = ws_view(rast, ws, "tile_end", torch.int32, F * nt).cpu().numpy()
+    start = ws_view(rast, ws, "tile_start", torch.int32, F * nt).cpu().numpy()
+    pairs = ws_view(rast, ws, "pairs", torch.int32, rast.max_pairs).cpu().numpy()
+    npx = ws_view(rast, ws, "tile_npx", torch.int32, F * nt).cpu().numpy()
+    return [pairs[a:b] for a, b in zip(start, tend)], npx
+
+
+@pytest.mark.parametrize("n,size,frames,tile,cover,big", [
+    (1, (61, 43), 1, (16, 16), 1.0, False), (255, (61, 43), 2, (8, 8), 0.5, False),
+    (1025, (130, 70), 1, (16, 16), 1.0, False), (2050, (97, 66), 3, (32, 8), 0.2, False),
+    (5000, (128, 96), 1, (16, 16), 0.02, False), (300, (64, 48), 1, (16, 16), 1.0, True),
+    (700, (64, 48), 1, (16, 16), 1.0, True), (4096, (33, 17), 1, (16, 16), 1.0, True),
+    (4097, (33, 17), 2, (16, 16), 1.0, True), (9000, (33, 17), 1, (16, 16), 1.0, True)])
+def test_binning_per_tile_equals_the_general_path(n, size, frames, tile, cover, big):
+    """The one-workgroup-per-tile binning of small plans against the general
+    path (a plan with sort_cap given): the same lists tile by tile, pixels,
+    totals and rendered bits; lists of 0 to 9,000 pairs (rank, LDS, register
+    and merge sorts), empty tiles, a second binning with another mask, and a
+    capacity that is one pair short."""
+    cam = small_cam(*size, 0.9 * size[0])
+    rng = np.random.default_rng(n)
+    sc = random_scene(rng, n, spread=0.1 if big else 0.9, smin=0.3 if big else 0.01, smax=0.6 if big else 0.08,
+                      opaque_frac=0.02 if big else 0.7)
+    sc["opacity"] = np.where(sc["opacity"] > 0.5, sc["opacity"], 0.002 if big else sc["opacity"]).astype(np.float32)
+    poses = np.repeat(identity_pose(), frames, 0)
+    poses[:, 9] += 0.05 * np.arange(frames)
+    masks = [(rng.random((frames, size[1], size[0])) < cover).astype(np.uint8) for _ in range(2)]
+    masks[0][:, : size[1] // 3] = 0
+    nt = -(-size[0] // tile[0]) * -(-size[1] // tile[1])
+    got = {}
+    for cap in (0, 4096):
+        rast = _rast(cam, n, frames, tile_w=tile[0], tile_h=tile[1], sort_cap=cap)
+        ws = rast.new_workspace()
+        rast.project(ws, *dev_params(sc), dev_poses(poses))
+        for k, m in enumerate(masks):
+            rast.bin(ws, dev_mask(m))
+            out = rast.alloc_outputs()
+            rast.render_into(ws, *out)
+            st = rast.read_status(ws)
+            lists, npx = _tile_lists(rast, ws, frames, nt)
+            got[cap, k] = (lists, npx, {key: st[key] for key in ("pairs", "pixels", "items", "overflow", "err", "big_tiles",
+                                                                 "restaged_blocks", "status")},
+                           [t.cpu().numpy() for t in out])
+    for k in range(2):
+        a, b = got[0, k], got[4096, k]
+        assert a[2] == b[2] and a[2]["status"] == 0
+        assert np.array_equal(a[1], b[1])
+        for x, y, p in zip(a[0], b[0], a[1]):
+            assert np.array_equal(x, y) if p else len(x) == 0
+        for x, y in zip(a[3], b[3]):
+            assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
+    K = got[0, 1][2]["pairs"]
+    if K > 1:
+        rast = _rast(cam, n, frames, tile_w=tile[0], tile_h=tile[1], max_pairs=K - 1)
+        ws = rast.new_workspace()
+        rast.project(ws, *dev_params(sc), dev_poses(poses))
+        for _ in range(2):
+            rast.bin(ws, dev_mask(masks[1]))
+            out = rast.alloc_outputs()
+            rast.render_into(ws, *out)
+            st = rast.read_status(ws)
+            assert st["overflow"] == 1 and st["pairs"] == K and st["items"] == 0 and st["status"] != 0
+            assert (out[3].cpu().numpy() == -1).all() and not out[0].any()
