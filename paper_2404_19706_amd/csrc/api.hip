@@ -660,9 +660,13 @@ rtg_status launch_project_bwd(const rtg_plan* p, void* ws, const float* pos, con
     // 2048 / 1024 / 512: 28 / 17 / 12 for 500,000 Gaussians of one frame, 94 /
     // 66 / 52 for 1M of 8 frames, 167 / 131 / 144 for 5M of 16)
     const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(grid_for(p->d.N, 256), 512));
-    if (p->d.sh_deg > 0)
-        hipLaunchKernelGGL(k_sh_bwd, dim3(grid_for(p->d.N, 256)), dim3(256), 0, S(stream), p->d, w, pos, color,
-                           unstable, poses, d_pos, d_color_param, ls);
+    if (p->d.sh_deg > 0) {
+        const auto k = p->d.sh_deg == 1 ? k_sh_bwd<1> : p->d.sh_deg == 2 ? k_sh_bwd<2> : k_sh_bwd<3>;
+        // one round of resident workgroups (registers: 4, 3 or 2 per CU)
+        const unsigned round = p->d.sh_deg == 1 ? 1024u : p->d.sh_deg == 2 ? 768u : 512u;
+        hipLaunchKernelGGL(k, dim3(std::min<unsigned>(grid_for(p->d.N, 256), round)), dim3(256), 0, S(stream), p->d, w, pos, color, unstable, poses, d_pos,
+                           d_color_param, ls);
+    }
     hipLaunchKernelGGL(k_project_bwd, dim3(blocks), dim3(256), 0, S(stream), p->d, w, pos, scale, rot, unstable,
                        poses, d_pos, d_scale, d_rot, d_opacity, d_color_param, ls);
     return launched();

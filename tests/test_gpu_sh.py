@@ -194,3 +194,46 @@ def test_sh_rows_of_added_gaussians():
     assert got.shape == (n_new, 9, 3)
     np.testing.assert_allclose(got, ref["rows"]["color"], rtol=1e-6, atol=1e-7)
     assert (got[:, 1:, :] == 0).all()
+
+
+@pytest.mark.parametrize("n,deg", [
+    (1, 1), (255, 3), (257, 2), (150_000, 3), (330_000, 1),
+    pytest.param(270_000, 1, marks=pytest.mark.xfail(strict=True, reason=(
+        "known defect of rtg_plan_create, older than this test: halving binning ranges of 1,280 Gaussians gives 160, "
+        "not a multiple of the 64 the enumeration counts in, and a fifth of the Gaussians get no pairs")))])
+def test_sh_backward_ranges(n, deg):
+    """Workgroup ranges of 256 and more Gaussians, few of them in view: the
+    gradients of those in view are those of a scene of them alone (float
+    atomics: 1e-5 of the norm), unstable rows out of view are zero, stable
+    rows are not touched."""
+    from paper_2404_19706_amd import Rasterizer
+    from tests.gpu_helpers import dev_mask, dev_params, dev_poses
+    cam = small_cam(61, 43, 60.0)
+    rng = np.random.default_rng(n + deg)
+    k, K = min(n, 700), sh.n_coef(deg)
+    sc = random_scene(rng, n, spread=0.8, unstable_frac=0.5)
+    sc["color"] = rng.standard_normal((n, K, 3)).astype(np.float32)
+    hidden = np.ones(n, bool)
+    hidden[rng.permutation(n)[:k]] = False
+    sc["pos"][hidden, 2] = -3.0
+    pose = np.concatenate([np.eye(3).ravel(), np.zeros(3)])
+    poses = np.stack([pose, pose])
+    poses[1, 9] = 0.1
+    mask = np.ones((2, 43, 61), np.uint8)
+    gC = torch.as_tensor(rng.standard_normal((2, 43, 61, 3)).astype(np.float32)).cuda()
+    gD = torch.as_tensor(rng.standard_normal((2, 43, 61)).astype(np.float32)).cuda()
+    out = {}
+    for name, s in (("all", sc), ("seen", {key: v[~hidden] for key, v in sc.items()})):
+        rast = Rasterizer(cam, len(s["pos"]), 2, sh_degree=deg)
+        params = dev_params(s)
+        C, D, T, I, ws = rast.forward(params, dev_poses(poses), dev_mask(mask))
+        grads = {key: torch.full_like(v, 7.0) for key, v in rast.alloc_grads().items()}
+        rast.backward_into(ws, params, dev_poses(poses), D, T, I, gC, gD, grads)
+        torch.cuda.synchronize()
+        out[name] = {key: v.cpu().numpy().reshape(len(s["pos"]), -1) for key, v in grads.items()}
+    un = sc["unstable"] != 0
+    for key in out["all"]:
+        g, r = out["all"][key], out["seen"][key]
+        assert (g[~un] == 7.0).all() and (g[un & hidden] == 0.0).all(), key
+        a, b = g[un & ~hidden], r[un[~hidden]]
+        assert np.linalg.norm(a - b) <= 1e-5 * np.linalg.norm(b), key
