@@ -915,3 +915,20 @@ def test_binning_per_tile_equals_the_general_path(n, size, frames, tile, cover, 
             st = rast.read_status(ws)
             assert st["overflow"] == 1 and st["pairs"] == K and st["items"] == 0 and st["status"] != 0
             assert (out[3].cpu().numpy() == -1).all() and not out[0].any()
+
+
+@pytest.mark.parametrize("ipp,share", [(1, 0), (2, 50), (7, 0), (64, 30)])
+def test_queue_with_fewer_chunks_than_waves(ipp, share):
+    """A queue over a handful of items, from one to less than one chunk per
+    wave: every item is taken (the round-robin outputs, bit for bit)."""
+    cam = small_cam(100, 75, 90.0)
+    sc, poses = _two_pose_scene(11, n=800)
+    rng = np.random.default_rng(ipp)
+    mask = (rng.random((2, 75, 100)) < 0.4).astype(np.uint8)
+    ref = gpu_forward(_rast(cam, 800, 2), sc, poses, mask)
+    got = gpu_forward(_rast(cam, 800, 2, items_per_pop=ipp, static_share=share), sc, poses, mask)
+    for k in ("color", "depth", "trans", "index"):
+        assert np.array_equal(got[k].view(np.uint32), ref[k].view(np.uint32)), k
+    assert got["status"]["blend_fwd"] == ref["status"]["blend_fwd"]
+    errs = _grad_parity(cam, sc, poses, mask, seed=5, items_per_pop=ipp, static_share=share)
+    print("queue gradients", ipp, share, fmt_stats(errs))
