@@ -29,6 +29,7 @@ struct rtg_plan {
     rtg_config cfg;
     rtg_intrinsics intr;
     Dims d;
+    bool few_blocks;   // binning blocks with small tile chunks
     size_t off[O_COUNT + 1];
 };
 
@@ -69,7 +70,9 @@ WS make_ws(const rtg_plan* p, void* base) {
     w.prec = reinterpret_cast<float4*>(b + p->off[O_PREC]);
     w.recp = reinterpret_cast<float*>(b + p->off[O_RECP]);
     w.stagec = reinterpret_cast<uint32_t*>(b + p->off[O_STAGEC]);
-    w.bfail = w.stagec + 256;
+    // (the fourth row of work counters is not written: a backward's
+    // contributions are the blends of its forward)
+    w.bfail = p->few_blocks ? reinterpret_cast<uint32_t*>(w.wcount + 3 * (size_t)kMaxWaves) : w.stagec + 256;
     w.vcnt = reinterpret_cast<uint32_t*>(b + p->off[O_VCNT]);
     w.vlist = reinterpret_cast<uint8_t*>(b + p->off[O_VLIST]);
     w.chunk = reinterpret_cast<unsigned long long*>(b + p->off[O_CHUNK]);
@@ -317,6 +320,21 @@ rtg_status rtg_plan_create(const rtg_config* cfg, const rtg_intrinsics* intr, in
             return RTG_E_INVALID;
         }
         d.rcap = (uint32_t)(cfg->stage_cap ? cfg->stage_cap : room);
+    }
+    // few ranges over many tiles: smaller chunks (down to 1,024 tiles) until
+    // there are about two workgroups per CU, since each clears, scans and
+    // writes its chunk's counters (2,821 Gaussians over 13,700 8x8 tiles:
+    // binning 112 us with 48 workgroups, 80 with 168).  From 512 workgroups on
+    // a smaller chunk only reads the ranges' records more often.  The staging
+    // regions stay as they are, and the blocks' failure words (fewer than
+    // 1,024) go where the workspace has room already, so that its size does
+    // not grow.  A plan whose caller sizes the regions keeps the blocks that
+    // it sized them for.
+    p->few_blocks = false;
+    while (cfg->stage_cap == 0 && d.chunk > 1024 && (int64_t)frames * d.nbpf * d.nchunks < 512) {
+        d.chunk = std::max(1024, d.chunk / 2);
+        d.nchunks = (d.ntiles + d.chunk - 1) / d.chunk;
+        p->few_blocks = true;
     }
     const size_t slots = (size_t)n * frames;
     const size_t ft = (size_t)frames * d.ntiles;

@@ -917,6 +917,34 @@ def test_binning_per_tile_equals_the_general_path(n, size, frames, tile, cover, 
             assert (out[3].cpu().numpy() == -1).all() and not out[0].any()
 
 
+@pytest.mark.parametrize("n,frames,tile,skew", [(700, 1, (8, 8), False), (3000, 2, (8, 8), False),
+                                                (3000, 1, (32, 8), False), (700, 1, (8, 8), True)])
+def test_few_ranges_over_many_tiles(n, frames, tile, skew):
+    """Binning blocks with tile chunks of about a thousand (few Gaussians,
+    thousands of tiles): the oracle's lists.  With most pairs in one block
+    (`skew`, and room for four times the pairs over twelve regions) its
+    staging region overflows and it enumerates them twice."""
+    size = (1142, 767)
+    cam = small_cam(*size, 0.8 * size[0])
+    sc, poses = _two_pose_scene(1, n=n)
+    poses = poses[:frames]
+    rng = np.random.default_rng(n)
+    mask = (rng.random((frames, size[1], size[0])) < 0.3).astype(np.uint8)
+    if skew:
+        mask[:, 40:] = 0
+        sc["scale"][:256, :2] *= 4.0
+        sc["scale"][256:] *= 0.02
+    P = orc.make_params(cam, tile=tile)
+    recs = orc.project(P, sc, poses)
+    pairs = len(orc.bin_pairs(P, recs, mask)["gid"])
+    rast = _rast(cam, len(sc["pos"]), frames, tile_w=tile[0], tile_h=tile[1], sort_cap=4096,
+                 **({"max_pairs": pairs + 64} if skew else {}))
+    g = gpu_forward(rast, sc, poses, mask)
+    assert g["status"]["status"] == 0
+    assert (g["status"]["restaged_blocks"] > 0) == skew
+    _check_pairs(rast, g["ws"], P, recs, mask, frames, len(sc["pos"]), g)
+
+
 @pytest.mark.parametrize("ipp,share", [(1, 0), (2, 50), (7, 0), (64, 30)])
 def test_queue_with_fewer_chunks_than_waves(ipp, share):
     """A queue over a handful of items, from one to less than one chunk per
