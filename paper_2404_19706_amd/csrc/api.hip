@@ -970,21 +970,17 @@ rtg_status rtg_select_top_error(int32_t frames, int32_t height, int32_t width, d
     const bool v4 = hw % 4 == 0 && ((reinterpret_cast<uintptr_t>(color_r) | reinterpret_cast<uintptr_t>(color_in)) & 15) == 0 &&
                     (reinterpret_cast<uintptr_t>(mask_out) & 3) == 0;
     const unsigned bx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(1024, (hw + 8191) / 8192));
-    const dim3 g(bx, frames), b256(256);
+    const dim3 g(bx, frames), gh((bx + 3) / 4, frames), b256(256), b1024(1024);
     const uint32_t* ck = keys;
-    const SelState* cst = st;
     hipLaunchKernelGGL(k_sel_init, dim3(frames), b256, 0, S(stream), frames, k, hist, st);
-    if (v4) hipLaunchKernelGGL(k_sel_keys<true>, g, b256, 0, S(stream), hw, color_r, color_in, keys, hist);
-    else hipLaunchKernelGGL(k_sel_keys<false>, g, b256, 0, S(stream), hw, color_r, color_in, keys, hist);
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        if (shift < 24) {
-            if (v4) hipLaunchKernelGGL(k_sel_hist<true>, g, b256, 0, S(stream), hw, shift, ck, hist, cst);
-            else hipLaunchKernelGGL(k_sel_hist<false>, g, b256, 0, S(stream), hw, shift, ck, hist, cst);
-        }
-        hipLaunchKernelGGL(k_sel_pick, dim3(frames), b256, 0, S(stream), shift, hist, st);
+    if (v4) hipLaunchKernelGGL(k_sel_keys<true>, g, b256, 0, S(stream), hw, color_r, color_in, keys, hist, st);
+    else hipLaunchKernelGGL(k_sel_keys<false>, g, b256, 0, S(stream), hw, color_r, color_in, keys, hist, st);
+    for (int shift = 16; shift >= 0; shift -= 8) {
+        if (v4) hipLaunchKernelGGL(k_sel_hist<true>, gh, b1024, 0, S(stream), hw, shift, ck, hist, st);
+        else hipLaunchKernelGGL(k_sel_hist<false>, gh, b1024, 0, S(stream), hw, shift, ck, hist, st);
     }
-    if (v4) hipLaunchKernelGGL(k_sel_mask<true>, g, b256, 0, S(stream), hw, ck, cst, mask_out);
-    else hipLaunchKernelGGL(k_sel_mask<false>, g, b256, 0, S(stream), hw, ck, cst, mask_out);
+    if (v4) hipLaunchKernelGGL(k_sel_mask<true>, g, b256, 0, S(stream), hw, ck, (const SelState*)st, mask_out);
+    else hipLaunchKernelGGL(k_sel_mask<false>, g, b256, 0, S(stream), hw, ck, (const SelState*)st, mask_out);
     return launched();
 }
 

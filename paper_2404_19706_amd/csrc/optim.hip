@@ -105,9 +105,9 @@ __global__ __launch_bounds__(256) void k_fuse(int64_t n, const int32_t* __restri
 // Per frame: the colour error e = (|dC0| + |dC1|) + |dC2| of every pixel
 // (binary32, as Eq. 6), its bits as an order-preserving key (e >= 0), and
 // the k-th largest key found by four 8-bit radix passes (per-frame
-// 256-bin histograms of the keys that share the prefix found so far, then
-// one workgroup per frame picks the bin holding the k-th largest); the mask
-// takes every pixel whose key is at least that value.
+// 256-bin histograms of the keys that share the prefix found so far; the
+// frame's last workgroup to add its counts picks the bin holding the k-th
+// largest); the mask takes every pixel whose key is at least that value.
 //
 // Bound by memory: 24 bytes per pixel of images once, then the 4-byte keys
 // (52 MB for 16 frames of 1200x680, in the last-level cache) for three
@@ -116,41 +116,87 @@ __global__ __launch_bounds__(256) void k_fuse(int64_t n, const int32_t* __restri
 // 16-byte aligned; it counts into 32 interleaved copies of the bins (a lane's
 // copy is its bank), since the leading digits of the errors fall into a few
 // bins; the later digits spread, and one copy does.  16 frames of 1200x680:
-// keys and first histogram 88 to 70 us (5.2 TB/s, the rate of a copy), a later
-// histogram 28 to 10 us, the mask 26 to 10 us.
+// keys and first histogram 88 to 72 us (5.1 TB/s, the rate of a copy), a later
+// histogram with its pick 33 to 12 us, the mask 26 to 11 us.
 
 struct SelState {
     uint32_t prefix;   // high bits of the k-th largest key found so far
     uint32_t rem;      // its rank among the keys with that prefix (1-based)
     uint32_t none;     // k = 0: nothing selected
-    uint32_t pad;
+    uint32_t done;     // workgroups that have added their counts
 };
 
 constexpr int kSelCopies = 32;
 
+// The bin b (counting from the top) whose keys hold the rem-th largest: the
+// prefix gains b, rem drops by the keys in higher bins, and the histogram is
+// cleared for the next digit.  256 threads or more, thread t holding bin t;
+// `suf` is 257 words of LDS.
+__device__ __forceinline__ void sel_pick(int shift, uint32_t* suf, uint32_t* hist, SelState* st) {
+    const int t = threadIdx.x;
+    const bool bin = t < 256;
+    // read where the other workgroups' adds were made, past this XCD's L2
+    const uint32_t c = bin ? __hip_atomic_load(&hist[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    const SelState s = *st;
+    // suffix sums: suf[b] = keys in bins >= b
+    if (bin) suf[t] = c;
+    if (t == 0) suf[256] = 0u;
+    __syncthreads();
+    for (int o = 1; o < 256; o <<= 1) {
+        const uint32_t add = t + o < 256 ? suf[t + o] : 0u;
+        __syncthreads();
+        if (bin) suf[t] += add;
+        __syncthreads();
+    }
+    if (!bin) return;
+    // the bin with suf[b + 1] < rem <= suf[b] (exactly one when rem <= suf[0])
+    if (!s.none && suf[t + 1] < s.rem && s.rem <= suf[t]) {
+        st->prefix = s.prefix | ((uint32_t)t << shift);
+        st->rem = s.rem - suf[t + 1];
+    }
+    hist[t] = 0u;
+    if (t == 0) st->done = 0u;
+}
+
 // The workgroup's counts (COPIES interleaved copies of 256 bins) onto the
 // frame's (thread t: bin t; the copies are read from a staggered start, a
-// different bank per lane).
+// different bank per lane; at least 258 words, used again for the pick, since
+// more than 32 KB would let a workgroup less onto a CU).  The frame's last
+// workgroup then picks the digit: with a launch of its own for it, ten in
+// all, one frame of 512x384 took 40 us and 16 of 1200x680 124, now 31 and 120.
 template <int COPIES>
-__device__ __forceinline__ void sel_flush(const uint32_t* h, uint32_t* hist) {
+__device__ __forceinline__ void sel_flush(int shift, uint32_t* h, uint32_t* hist, SelState* st) {
     __syncthreads();
     uint32_t c = 0;
+    if (threadIdx.x < 256) {
 #pragma unroll
-    for (int k = 0; k < COPIES; ++k) c += h[threadIdx.x * COPIES + ((k + threadIdx.x) & (COPIES - 1))];
-    if (c) atomicAdd(&hist[threadIdx.x], c);
+        for (int k = 0; k < COPIES; ++k) c += h[threadIdx.x * COPIES + ((k + threadIdx.x) & (COPIES - 1))];
+    }
+    if (c) __hip_atomic_fetch_add(&hist[threadIdx.x], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // Every wave waits until its adds have been made in memory, then the ticket
+    // is drawn: all that the last workgroup reads are those sums, so no cache
+    // has to be written back (a releasing ticket writes the keys back once per
+    // workgroup: 276 us).
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0)
+        h[257] = __hip_atomic_fetch_add(&st->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    __syncthreads();
+    if (h[257]) sel_pick(shift, h, hist, st);
 }
 
 __device__ __forceinline__ uint32_t sel_key(float r0, float r1, float r2, float i0, float i1, float i2) {
     return __float_as_uint((fabsf(r0 - i0) + fabsf(r1 - i1)) + fabsf(r2 - i2));
 }
 
-// Keys and the histogram of their first digit.  Grid (blocks per frame,
+// Keys, the histogram of their first digit and its pick.  Grid (blocks per frame,
 // frames).  V4: hw a multiple of 4 and 16-byte aligned arrays, four pixels
 // per thread and step.
 template <bool V4>
 __global__ __launch_bounds__(256) void k_sel_keys(int64_t hw, const float* __restrict__ color_r,
                                                   const float* __restrict__ color_in, uint32_t* __restrict__ keys,
-                                                  uint32_t* __restrict__ hist) {
+                                                  uint32_t* __restrict__ hist, SelState* __restrict__ st) {
     __shared__ __attribute__((aligned(16))) uint32_t h[256 * kSelCopies];
     for (int i = threadIdx.x; i < 64 * kSelCopies; i += 256) reinterpret_cast<uint4*>(h)[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
@@ -186,7 +232,7 @@ __global__ __launch_bounds__(256) void k_sel_keys(int64_t hw, const float* __res
             count(k);
         }
     }
-    sel_flush<kSelCopies>(h, hist + 256 * f);
+    sel_flush<kSelCopies>(24, h, hist + 256 * f, st + f);
 }
 
 __global__ __launch_bounds__(256) void k_sel_init(int32_t frames, uint32_t k, uint32_t* __restrict__ hist,
@@ -198,21 +244,23 @@ __global__ __launch_bounds__(256) void k_sel_init(int32_t frames, uint32_t k, ui
 }
 
 // The histogram of a later digit, over the keys with the prefix found so
-// far.  Grid (blocks per frame, frames).
+// far, and its pick.  Grid (blocks per frame, frames); 1024 threads, so that
+// few workgroups add their 256 counts and draw tickets (16 frames of 1200x680:
+// 17.5 us with workgroups of 256, 11.9 so).
 template <bool V4>
-__global__ __launch_bounds__(256) void k_sel_hist(int64_t hw, int shift, const uint32_t* __restrict__ keys,
-                                                  uint32_t* __restrict__ hist, const SelState* __restrict__ st) {
-    __shared__ uint32_t h[256];
+__global__ __launch_bounds__(1024) void k_sel_hist(int64_t hw, int shift, const uint32_t* __restrict__ keys,
+                                                   uint32_t* __restrict__ hist, SelState* __restrict__ st) {
+    __shared__ uint32_t h[258];
     const int f = blockIdx.y;
     const uint32_t prefix = st[f].prefix;
-    h[threadIdx.x] = 0u;
+    if (threadIdx.x < 256) h[threadIdx.x] = 0u;
     __syncthreads();
     const uint32_t hi = 0xffffffffu << (shift + 8);
     auto count = [&](uint32_t key) {
         if ((key & hi) == prefix) atomicAdd(&h[(key >> shift) & 255u], 1u);
     };
     const uint32_t* kf = keys + (int64_t)f * hw;
-    const int64_t t0 = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+    const int64_t t0 = (int64_t)blockIdx.x * 1024 + threadIdx.x, step = (int64_t)gridDim.x * 1024;
     if constexpr (V4) {
         const uint4* k4 = reinterpret_cast<const uint4*>(kf);
         for (int64_t p = t0; p < hw / 4; p += step) {
@@ -225,37 +273,7 @@ __global__ __launch_bounds__(256) void k_sel_hist(int64_t hw, int shift, const u
     } else {
         for (int64_t p = t0; p < hw; p += step) count(kf[p]);
     }
-    sel_flush<1>(h, hist + 256 * f);
-}
-
-// One workgroup of 256 per frame: the bin b (counting from the top) whose
-// keys hold the rem-th largest; prefix gains b, rem drops by the keys in
-// higher bins; the histogram is cleared for the next pass.
-__global__ __launch_bounds__(256) void k_sel_pick(int shift, uint32_t* __restrict__ hist, SelState* __restrict__ st) {
-    __shared__ uint32_t suf[257];
-    __shared__ SelState s;
-    const int f = blockIdx.x;
-    const int t = threadIdx.x;
-    // suffix sums: suf[b] = keys in bins >= b
-    const uint32_t c = hist[256 * f + t];
-    suf[t] = c;
-    if (t == 0) {
-        suf[256] = 0u;
-        s = st[f];
-    }
-    __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-        const uint32_t add = t + o < 256 ? suf[t + o] : 0u;
-        __syncthreads();
-        suf[t] += add;
-        __syncthreads();
-    }
-    // the bin with suf[b + 1] < rem <= suf[b] (exactly one when rem <= suf[0])
-    if (!s.none && suf[t + 1] < s.rem && s.rem <= suf[t]) {
-        st[f].prefix = s.prefix | ((uint32_t)t << shift);
-        st[f].rem = s.rem - suf[t + 1];
-    }
-    hist[256 * f + t] = 0u;
+    sel_flush<1>(shift, h, hist + 256 * f, st + f);
 }
 
 // Grid (blocks per frame, frames).
