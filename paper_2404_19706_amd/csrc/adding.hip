@@ -3,11 +3,11 @@
 // data-parallel steps either side of the optimisation, consumers of the
 // render's colour, depth, transmission and index images.
 //
-// Adding, three passes over the frame's pixels (no shared-address
-// atomics): mark (per pixel: the Eq. 6 mask, whether the pixel is sampled
-// and adds a Gaussian; per 256-pixel block: how many), scan (one workgroup:
-// block offsets and the total), emit (per adding pixel: its row, in raster
-// order after the existing Gaussians, and the new disc).  Threshold
+// Adding, two passes over the frame's pixels (no shared-address atomics):
+// mark (per pixel: the Eq. 6 mask, whether the pixel is sampled and adds a
+// Gaussian; per 256-pixel block: how many), emit (per adding pixel: its row,
+// in raster order after the existing Gaussians, and the new disc; a block
+// that adds sums the counts of the blocks before it, the last one the total).  Threshold
 // decisions follow a fixed binary32 sequence, vertices and normals are
 // formed in binary64 from the binary32 depth with a fixed sequence, so
 // which pixels add a Gaussian, and in which order, is reproducible bit for
@@ -126,11 +126,9 @@ __global__ __launch_bounds__(256) void k_add_mark(AddParams a, Intr c, const flo
     if (threadIdx.x == 0) counts[blockIdx.x] = (wc[0] + wc[1]) + (wc[2] + wc[3]);
 }
 
-// Exclusive scan of nb block counts by one 1024-thread workgroup (chunks of
-// 1024 with a carry); the total goes to *total.
-__global__ __launch_bounds__(1024) void k_scan_counts(const uint32_t* __restrict__ counts,
-                                                      uint32_t* __restrict__ offsets, uint32_t nb,
-                                                      unsigned long long* __restrict__ total) {
+// Exclusive scan, in place, of nb counts by one 1024-thread workgroup (chunks
+// of 1024 with a carry).
+__global__ __launch_bounds__(1024) void k_scan_counts(uint32_t* __restrict__ counts, uint32_t nb) {
     __shared__ unsigned long long s64[16];
     unsigned long long carry = 0;
     for (uint32_t b0 = 0; b0 < nb; b0 += 1024) {
@@ -138,10 +136,31 @@ __global__ __launch_bounds__(1024) void k_scan_counts(const uint32_t* __restrict
         const unsigned long long v = b < nb ? counts[b] : 0ull;
         unsigned long long t;
         const unsigned long long ex = block_excl_scan_1024<unsigned long long>(v, s64, t);
-        if (b < nb) offsets[b] = (uint32_t)(carry + ex);
+        if (b < nb) counts[b] = (uint32_t)(carry + ex);
         carry += t;
     }
-    if (threadIdx.x == 0) *total = carry;
+}
+
+// Up to this many counts, every workgroup that needs its offset sums the
+// counts before it (4 uint4 loads per thread at the most) instead of a scan
+// by one workgroup between the two passes: 1M rows and 1200x680 pixels have
+// 977 and 3,188 counts, where the scan took 5.5 us and its launch as much
+// again.  Beyond, the sums (counts times workgroups) would cost more.
+constexpr uint32_t kSumCounts = 4096;
+
+// counts[0] + ... + counts[b - 1], in every thread of 256; `s` is 4 words of
+// LDS, counts 16-byte aligned.
+__device__ __forceinline__ uint32_t sum_before(const uint32_t* __restrict__ counts, uint32_t b, uint32_t* s) {
+    uint32_t v = 0;
+    for (uint32_t k = threadIdx.x; k < b / 4; k += 256) {
+        const uint4 c = reinterpret_cast<const uint4*>(counts)[k];
+        v += (c.x + c.y) + (c.z + c.w);
+    }
+    if (threadIdx.x < (b & 3)) v += counts[(b & ~3u) + threadIdx.x];
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return (s[0] + s[1]) + (s[2] + s[3]);
 }
 
 // Unit quaternion (w, x, y, z) of the shortest rotation taking e_z to n (a
@@ -160,19 +179,22 @@ __device__ __forceinline__ void quat_z_to(const double n[3], float q[4]) {
     q[3] = (float)(z / l);
 }
 
-// Pass 3: every adding pixel writes its disc at row n_cur + rank (rank =
+// Pass 2: every adding pixel writes its disc at row n_cur + rank (rank =
 // block offset + its rank in the block, raster order), while rows remain.
+// `counts` are the blocks' counts or, if `scanned`, their offsets.  The last
+// block writes out = {rows added, pixels that qualified}.
 __global__ __launch_bounds__(256) void k_add_emit(AddParams a, Intr c, const double* __restrict__ pose,
                                                   const float* __restrict__ color_in,
                                                   const float* __restrict__ depth_in,
                                                   const uint8_t* __restrict__ codes,
-                                                  const uint32_t* __restrict__ offsets, int32_t frame_k,
+                                                  const uint32_t* __restrict__ counts, bool scanned,
+                                                  int64_t* __restrict__ out, int32_t frame_k,
                                                   int64_t n_cur, int64_t capacity, float* __restrict__ pos,
                                                   float* __restrict__ scale, float* __restrict__ rot,
                                                   float* __restrict__ opacity, float* __restrict__ color,
                                                   uint8_t* __restrict__ unstable, int32_t* __restrict__ eta,
                                                   int32_t* __restrict__ err, int32_t* __restrict__ tstamp) {
-    __shared__ uint32_t wc[4];
+    __shared__ uint32_t wc[4], sb[4];
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t np = (int64_t)c.W * c.H;
     const int code = p < np ? (int)codes[p] : 0;
@@ -180,8 +202,17 @@ __global__ __launch_bounds__(256) void k_add_emit(AddParams a, Intr c, const dou
     const uint64_t m = ballot(code != 0);
     if (lane == 0) wc[wv] = (uint32_t)__builtin_popcountll(m);
     __syncthreads();
+    const uint32_t here = (wc[0] + wc[1]) + (wc[2] + wc[3]);
+    const bool end = blockIdx.x == gridDim.x - 1;
+    if (here == 0 && !end) return;
+    const uint32_t base = scanned ? counts[blockIdx.x] : sum_before(counts, blockIdx.x, sb);
+    if (end && threadIdx.x == 0) {
+        const int64_t t = (int64_t)base + here, room = capacity > n_cur ? capacity - n_cur : 0;
+        out[0] = t < room ? t : room;
+        out[1] = t;
+    }
     if (code == 0) return;
-    uint32_t r = offsets[blockIdx.x] + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull));
+    uint32_t r = base + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull));
     for (int k = 0; k < wv; ++k) r += wc[k];
     const int64_t row = n_cur + (int64_t)r;
     if (row >= capacity) return;
@@ -289,8 +320,8 @@ __global__ __launch_bounds__(256) void k_state_apply(AddParams a, int64_t n, int
 }
 
 // Stable compaction of up to kCompactMax row arrays by a keep mask: counts
-// per 256-row block, a scan, then every kept row copies its bytes to its
-// rank.
+// per 1024 rows, then every kept row copies its bytes to its rank.  Bound by
+// the copies (1M rows of 69 bytes: 31 us, 4.4 TB/s).
 constexpr int kCompactMax = 16;
 struct CompactArrays {
     const uint8_t* src[kCompactMax];
@@ -299,28 +330,52 @@ struct CompactArrays {
     int32_t n;
 };
 
+// Kept rows among i .. i + 3 (one load where the mask is 4-byte aligned).
+__device__ __forceinline__ uint32_t kept4(const uint8_t* __restrict__ keep, int64_t i, int64_t n) {
+    if (i + 4 <= n && (reinterpret_cast<uintptr_t>(keep) & 3) == 0) {
+        const uint32_t v = *reinterpret_cast<const uint32_t*>(keep + i);
+        return (v & 255u ? 1u : 0u) + (v & 0xff00u ? 1u : 0u) + (v & 0xff0000u ? 1u : 0u) + (v >> 24 ? 1u : 0u);
+    }
+    uint32_t c = 0;
+    for (int64_t j = i; j < i + 4 && j < n; ++j) c += keep[j] ? 1u : 0u;
+    return c;
+}
+
+// One workgroup per 1024 rows.
 __global__ __launch_bounds__(256) void k_compact_count(int64_t n, const uint8_t* __restrict__ keep,
                                                        uint32_t* __restrict__ counts) {
     __shared__ uint32_t wc[4];
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const bool k = i < n && keep[i] != 0;
-    const uint32_t c = (uint32_t)__builtin_popcountll(ballot(k));
-    if ((threadIdx.x & 63) == 0) wc[threadIdx.x >> 6] = c;
+    uint32_t v = kept4(keep, (int64_t)blockIdx.x * 1024 + 4 * threadIdx.x, n);
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) wc[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0) counts[blockIdx.x] = (wc[0] + wc[1]) + (wc[2] + wc[3]);
 }
 
+// One workgroup per 256 rows.  `counts` are the kept rows of every 1024 or,
+// if `scanned`, their offsets; what the workgroup's own 1024 rows hold before
+// its 256 is counted again.  The last workgroup writes the total.
 __global__ __launch_bounds__(256) void k_compact_move(int64_t n, const uint8_t* __restrict__ keep,
-                                                      const uint32_t* __restrict__ offsets, CompactArrays A) {
-    __shared__ uint32_t wc[4];
+                                                      const uint32_t* __restrict__ counts, bool scanned,
+                                                      int64_t* __restrict__ n_out, CompactArrays A) {
+    __shared__ uint32_t wc[4], sb[4], sg[4];
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const bool k = i < n && keep[i] != 0;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const uint32_t grp = blockIdx.x >> 2;
     const uint64_t m = ballot(k);
-    if (lane == 0) wc[wv] = (uint32_t)__builtin_popcountll(m);
+    uint32_t v = threadIdx.x < 64 * (blockIdx.x & 3) ? kept4(keep, 1024 * (int64_t)grp + 4 * threadIdx.x, n) : 0u;
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (lane == 0) {
+        wc[wv] = (uint32_t)__builtin_popcountll(m);
+        sg[wv] = v;
+    }
     __syncthreads();
+    const uint32_t before = scanned ? counts[grp] : sum_before(counts, grp, sb);
+    const int64_t base = (int64_t)before + ((sg[0] + sg[1]) + sg[2]);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *n_out = base + ((wc[0] + wc[1]) + (wc[2] + wc[3]));
     if (!k) return;
-    int64_t r = (int64_t)offsets[blockIdx.x] + (int64_t)__builtin_popcountll(m & ((1ull << lane) - 1ull));
+    int64_t r = base + (int64_t)__builtin_popcountll(m & ((1ull << lane) - 1ull));
     for (int w = 0; w < wv; ++w) r += wc[w];
     for (int a = 0; a < A.n; ++a) {
         const int rb = A.rb[a];

@@ -168,33 +168,18 @@ bool intr_ok(const rtg_intrinsics* c) {
 
 Intr to_intr(const rtg_intrinsics* c) { return Intr{c->fx, c->fy, c->cx, c->cy, c->width, c->height}; }
 
-// workspace of the adding passes: per-pixel codes, per-block counts and
-// offsets, the candidate total
+// workspace of the adding passes: per-pixel codes, per-block counts (and as
+// much again as their offsets and the total took)
 struct AddWs {
-    size_t codes, counts, offsets, total, bytes;
+    size_t codes, counts, bytes;
 };
 AddWs add_ws(int64_t np) {
     const size_t nb = (size_t)((np + 255) / 256);
     AddWs w;
     w.codes = 0;
     w.counts = align256((size_t)np);
-    w.offsets = w.counts + align256(4 * nb);
-    w.total = w.offsets + align256(4 * nb);
-    w.bytes = w.total + 256;
+    w.bytes = w.counts + 2 * align256(4 * nb) + 256;
     return w;
-}
-
-__global__ void k_add_counts(const unsigned long long* total, int64_t n_cur, int64_t capacity, int64_t* out) {
-    if (threadIdx.x == 0) {
-        const int64_t t = (int64_t)*total;
-        const int64_t room = capacity > n_cur ? capacity - n_cur : 0;
-        out[0] = t < room ? t : room;
-        out[1] = t;
-    }
-}
-
-__global__ void k_copy_count(const unsigned long long* total, int64_t* out) {
-    if (threadIdx.x == 0) out[0] = (int64_t)*total;
 }
 
 }  // namespace
@@ -812,19 +797,16 @@ rtg_status rtg_add_gaussians(const rtg_intrinsics* intr, const rtg_adding_params
     char* b = static_cast<char*>(ws);
     uint8_t* codes = reinterpret_cast<uint8_t*>(b + L.codes);
     uint32_t* cnt = reinterpret_cast<uint32_t*>(b + L.counts);
-    uint32_t* off = reinterpret_cast<uint32_t*>(b + L.offsets);
-    unsigned long long* tot = reinterpret_cast<unsigned long long*>(b + L.total);
     const AddParams a = add_params(prm);
     const Intr c = to_intr(intr);
     const unsigned nb = grid_for(np, 256);
     hipLaunchKernelGGL(k_add_mark, dim3(nb), dim3(256), 0, S(stream), a, c, color_in, depth_in, color_r, depth_r,
                        trans_r, index_r, rnd, (const uint8_t*)unstable, n_cur, codes, mask_out, cnt);
-    hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, S(stream), (const uint32_t*)cnt, off, (uint32_t)nb, tot);
+    const bool scanned = nb > kSumCounts;
+    if (scanned) hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, S(stream), cnt, (uint32_t)nb);
     hipLaunchKernelGGL(k_add_emit, dim3(nb), dim3(256), 0, S(stream), a, c, pose, color_in, depth_in,
-                       (const uint8_t*)codes, (const uint32_t*)off, frame_k, n_cur, capacity, pos, scale, rot,
-                       opacity, color, unstable, eta, err, tstamp);
-    hipLaunchKernelGGL(k_add_counts, dim3(1), dim3(64), 0, S(stream), (const unsigned long long*)tot, n_cur,
-                       capacity, counts);
+                       (const uint8_t*)codes, (const uint32_t*)cnt, scanned, counts, frame_k, n_cur, capacity, pos,
+                       scale, rot, opacity, color, unstable, eta, err, tstamp);
     return launched();
 }
 
@@ -878,15 +860,12 @@ rtg_status rtg_compact_rows(int64_t n, const uint8_t* keep, int32_t n_arrays, vo
     const size_t nb = (size_t)((n + 255) / 256);
     if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255) || ws_bytes < rtg_compact_workspace_bytes(n))
         return RTG_E_INVALID;
-    char* b = static_cast<char*>(ws);
-    uint32_t* cnt = reinterpret_cast<uint32_t*>(b);
-    uint32_t* off = reinterpret_cast<uint32_t*>(b + align256(4 * nb));
-    unsigned long long* tot = reinterpret_cast<unsigned long long*>(b + 2 * align256(4 * nb));
-    const unsigned g = (unsigned)std::max<size_t>(nb, 1);
-    hipLaunchKernelGGL(k_compact_count, dim3(g), dim3(256), 0, S(stream), n, keep, cnt);
-    hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, S(stream), (const uint32_t*)cnt, off, (uint32_t)g, tot);
-    hipLaunchKernelGGL(k_compact_move, dim3(g), dim3(256), 0, S(stream), n, keep, (const uint32_t*)off, A);
-    hipLaunchKernelGGL(k_copy_count, dim3(1), dim3(64), 0, S(stream), (const unsigned long long*)tot, n_out);
+    uint32_t* cnt = static_cast<uint32_t*>(ws);
+    const unsigned g = (unsigned)std::max<size_t>(nb, 1), gc = (g + 3) / 4;
+    const bool scanned = gc > kSumCounts;
+    hipLaunchKernelGGL(k_compact_count, dim3(gc), dim3(256), 0, S(stream), n, keep, cnt);
+    if (scanned) hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, S(stream), cnt, (uint32_t)gc);
+    hipLaunchKernelGGL(k_compact_move, dim3(g), dim3(256), 0, S(stream), n, keep, (const uint32_t*)cnt, scanned, n_out, A);
     return launched();
 }
 

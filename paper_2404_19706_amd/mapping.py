@@ -55,7 +55,7 @@ def add_gaussians(cam, prm, pose, color_in, depth_in, color_r, depth_r, trans_r,
     tensor [rows added, pixels that qualified]."""
     intr = intrinsics(cam)
     ws = torch.empty(int(lib().rtg_adding_workspace_bytes(ctypes.byref(intr))), dtype=torch.uint8, device="cuda")
-    counts = torch.zeros(2, dtype=torch.int64, device="cuda")
+    counts = torch.empty(2, dtype=torch.int64, device="cuda")
     cap = state["pos"].shape[0]
     check(lib().rtg_add_gaussians(ctypes.byref(intr), ctypes.byref(prm), _p(pose), _p(color_in), _p(depth_in),
                                   _p(color_r), _p(depth_r), _p(trans_r), _p(index_r), _p(rand), int(frame_k),
@@ -94,7 +94,7 @@ def compact_rows(n, keep, src, dst):
     D = (ctypes.c_void_p * k)(*[t.data_ptr() for t in dst])
     rb = (ctypes.c_int32 * k)(*[t[0].numel() * t.element_size() if t.dim() > 1 else t.element_size() for t in src])
     ws = torch.empty(int(lib().rtg_compact_workspace_bytes(int(n))), dtype=torch.uint8, device="cuda")
-    out = torch.zeros(1, dtype=torch.int64, device="cuda")
+    out = torch.empty(1, dtype=torch.int64, device="cuda")
     check(lib().rtg_compact_rows(int(n), _p(keep), k, S, D, rb, _p(out), _p(ws), ws.numel(), _s()),
           "rtg_compact_rows")
     return out

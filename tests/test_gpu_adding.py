@@ -137,3 +137,55 @@ def test_confidence_count_matches_reference():
     M.confidence_count(n, _t(un), _t(g), te)
     torch.cuda.synchronize()
     assert np.array_equal(te.cpu().numpy(), A.confidence_count(un, g, eta))
+
+
+@pytest.mark.parametrize("n,offset", [(0, 0), (1, 0), (255, 0), (257, 0), (768, 0), (1023, 0), (1025, 0), (9001, 0),
+                                      (9001, 1), (5, 3), (4097 * 1024 + 5, 0)])
+def test_compaction_at_the_edges(n, offset):
+    """Groups of 1024 and workgroups of 256 rows and their remainders, a keep
+    mask off 4-byte alignment, and more groups than a workgroup sums: the
+    rows the mask keeps, in order."""
+    from paper_2404_19706_amd import mapping as M
+    rng = np.random.default_rng(n)
+    buf = torch.zeros(max(n, 1) + offset, dtype=torch.uint8, device="cuda")
+    keep = buf[offset:]
+    kn = np.where(rng.random(n) < 0.7, rng.integers(1, 256, n), 0).astype(np.uint8)
+    keep[:n] = torch.as_tensor(kn)
+    src = [_t(rng.integers(0, 1 << 30, (n, 3)).astype(np.int32)), _t(rng.integers(0, 256, n).astype(np.uint8))]
+    if n == 0:
+        src = src[:0]
+    dst = [torch.zeros_like(a) for a in src]
+    nout = M.compact_rows(n, keep, src, dst)
+    torch.cuda.synchronize()
+    m = int(nout.item())
+    assert m == int((kn != 0).sum())
+    for a, d in zip(src, dst):
+        assert np.array_equal(d[:m].cpu().numpy(), a.cpu().numpy()[kn != 0])
+        assert not d[m:].any()
+
+
+@pytest.mark.parametrize("W,H,nothing", [(1, 1, False), (16, 16, False), (257, 3, False), (1100, 960, False),
+                                         (64, 48, True)])
+def test_adding_over_few_and_many_blocks(W, H, nothing):
+    """One block of 256 pixels, remainders, more blocks than a workgroup sums
+    counts of, and no pixel to add: rows, order and counts of the oracle."""
+    from paper_2404_19706_amd import mapping as M
+    cam, pose, C, D, Cr, Dr, Tr, I, un, rand = _frame(31 + W, W, H)
+    n_cur, rate = len(un), 0.3
+    if nothing:
+        rand[:] = 0.9
+    cap = n_cur + W * H
+    ref = A.add_gaussians(cam, A.params(rate=rate), pose, C, D, Cr, Dr, Tr, I, un, rand, 11, n_cur, cap)
+    st = M.alloc_state(cap)
+    st["unstable"][:n_cur] = _t(un)
+    counts = M.add_gaussians(cam, M.adding_params(rate=rate), _t(pose, torch.float64), _t(C), _t(D), _t(Cr), _t(Dr),
+                             _t(Tr), _t(I), _t(rand), 11, n_cur, st)
+    torch.cuda.synchronize()
+    n_add, n_cand = (int(v) for v in counts.cpu())
+    assert n_cand == len(ref["candidates"]) and n_add == ref["n_added"]
+    assert n_add > 0 or nothing or W * H <= 256
+    sl = slice(n_cur, n_cur + n_add)
+    assert np.array_equal(st["color"][sl].cpu().numpy(), np.asarray(ref["rows"]["color"], np.float32).reshape(-1, 3))
+    np.testing.assert_allclose(st["pos"][sl].cpu().numpy(), np.asarray(ref["rows"]["pos"]).reshape(-1, 3), rtol=1e-6,
+                               atol=1e-6)
+    assert not st["tstamp"][n_cur + n_add:].any()
