@@ -198,6 +198,14 @@ rtg_status rtg_bin(const rtg_plan* plan, void* ws, const uint8_t* mask, void* st
 rtg_status rtg_render(const rtg_plan* plan, void* ws, float* color, float* depth, float* trans,
                       int32_t* index, void* stream);
 
+/* The images as rtg_render expects pixels that it does not render to be set
+ * (colour 0, depth -1, transmission 1, index -1), and the gradients of a
+ * backward as zeros, each in one launch. */
+rtg_status rtg_clear_outputs(const rtg_plan* plan, float* color, float* depth, float* trans, int32_t* index,
+                             void* stream);
+rtg_status rtg_clear_grads(const rtg_plan* plan, float* d_pos, float* d_scale, float* d_rot, float* d_opacity,
+                           float* d_color, void* stream);
+
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): steps a1-a5 as
  * rtg_project + rtg_bin + rtg_render, with the workspace taken from a fixed

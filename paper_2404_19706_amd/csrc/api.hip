@@ -92,6 +92,22 @@ unsigned fill_grid(size_t n) { return (unsigned)std::max<size_t>(1, std::min<siz
 
 unsigned grid_for(int64_t n, int per_block) { return (unsigned)((n + per_block - 1) / per_block); }
 
+// One launch over the arrays of A (pointers 4-byte aligned where there are
+// words to write).
+rtg_status clear_arrays(ClearArrays& A, hipStream_t s) {
+    int64_t nb = 0;
+    for (int k = 0; k < kClearMax; ++k) {
+        if (A.n[k] > 0 && (!A.p[k] || (reinterpret_cast<uintptr_t>(A.p[k]) & 3))) return RTG_E_INVALID;
+        A.first[k] = (uint32_t)nb;
+        nb += (A.n[k] + kClearWords - 1) / kClearWords;
+        if (nb > 0x7fffffff) return RTG_E_INVALID;
+    }
+    A.first[kClearMax] = (uint32_t)nb;
+    if (nb == 0) return RTG_OK;
+    hipLaunchKernelGGL(k_clear, dim3((unsigned)nb), dim3(256), 0, s, A);
+    return launched();
+}
+
 // Persistent-grid size per device (CU count x resident blocks per CU).
 struct DevInfo {
     int cus = 0;
@@ -544,6 +560,28 @@ rtg_status bin_impl(const rtg_plan* p, void* ws, const uint8_t* mask, void* stre
 }
 
 }  // namespace
+
+rtg_status rtg_clear_outputs(const rtg_plan* p, float* color, float* depth, float* trans, int32_t* index,
+                             void* stream) {
+    if (!p) return RTG_E_INVALID;
+    const int64_t px = (int64_t)p->d.F * p->d.H * p->d.W;
+    ClearArrays A{{(uint32_t*)color, (uint32_t*)depth, (uint32_t*)trans, (uint32_t*)index, nullptr},
+                  {3 * px, px, px, px, 0},
+                  {0u, 0xbf800000u, 0x3f800000u, 0xffffffffu, 0u},   // 0, -1, 1 as floats; -1
+                  {}};
+    return clear_arrays(A, S(stream));
+}
+
+rtg_status rtg_clear_grads(const rtg_plan* p, float* d_pos, float* d_scale, float* d_rot, float* d_opacity,
+                           float* d_color, void* stream) {
+    if (!p) return RTG_E_INVALID;
+    const int64_t n = p->d.N, k = (p->cfg.sh_degree + 1) * (p->cfg.sh_degree + 1);
+    ClearArrays A{{(uint32_t*)d_pos, (uint32_t*)d_scale, (uint32_t*)d_rot, (uint32_t*)d_opacity, (uint32_t*)d_color},
+                  {3 * n, 3 * n, 4 * n, n, 3 * k * n},
+                  {},
+                  {}};
+    return clear_arrays(A, S(stream));
+}
 
 rtg_status rtg_render(const rtg_plan* p, void* ws, float* color, float* depth, float* trans, int32_t* index,
                       void* stream) {

@@ -8,18 +8,16 @@ import ctypes
 import torch
 
 from ._lib import AddingParams, Intrinsics, check, lib
+from ._lib import ptr as _p, stream as _s
 
 STATE_FIELDS = (("pos", torch.float32, 3), ("scale", torch.float32, 3), ("rot", torch.float32, 4),
                 ("opacity", torch.float32, 0), ("color", torch.float32, 3), ("unstable", torch.uint8, 0),
                 ("eta", torch.int32, 0), ("err", torch.int32, 0), ("tstamp", torch.int32, 0))
 
 
-def _p(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
-
-
-def _s():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _row(t):
+    """Elements of a row (of t[0], without making it)."""
+    return t.numel() // t.shape[0] if t.shape[0] else t[0].numel()
 
 
 def adding_params(**kw):
@@ -69,7 +67,7 @@ def add_gaussians(cam, prm, pose, color_in, depth_in, color_r, depth_r, trans_r,
 def confidence_count(n, unstable, d_color, eta):
     """eta + 1 for unstable rows with a non-zero colour gradient row
     (d_color of shape (n, 3) for RGB or (n, K, 3) for SH)."""
-    width = int(d_color[0].numel()) if n > 0 else 3
+    width = _row(d_color) if n > 0 else 3
     check(lib().rtg_confidence_count(int(n), width, _p(unstable), _p(d_color), _p(eta), _s()),
           "rtg_confidence_count")
 
@@ -92,7 +90,7 @@ def compact_rows(n, keep, src, dst):
     k = len(src)
     S = (ctypes.c_void_p * k)(*[t.data_ptr() for t in src])
     D = (ctypes.c_void_p * k)(*[t.data_ptr() for t in dst])
-    rb = (ctypes.c_int32 * k)(*[t[0].numel() * t.element_size() if t.dim() > 1 else t.element_size() for t in src])
+    rb = (ctypes.c_int32 * k)(*[_row(t) * t.element_size() if t.dim() > 1 else t.element_size() for t in src])
     ws = torch.empty(int(lib().rtg_compact_workspace_bytes(int(n))), dtype=torch.uint8, device="cuda")
     out = torch.empty(1, dtype=torch.int64, device="cuda")
     check(lib().rtg_compact_rows(int(n), _p(keep), k, S, D, rb, _p(out), _p(ws), ws.numel(), _s()),
@@ -117,7 +115,7 @@ def fuse(eta_prev, eta_cur, prev, cur):
     """rtg_fuse (Eq. 9): fuses cur ("pos", "scale", "rot", "color"; updated in
     place) with prev, weighted by the confidence counts."""
     n = int(eta_cur.shape[0])
-    width = int(cur["color"][0].numel()) if n > 0 else 3
+    width = _row(cur["color"]) if n > 0 else 3
     check(lib().rtg_fuse(n, width, _p(eta_prev), _p(eta_cur), _p(prev["pos"]), _p(prev["scale"]), _p(prev["rot"]),
                          _p(prev["color"]), _p(cur["pos"]), _p(cur["scale"]), _p(cur["rot"]), _p(cur["color"]),
                          _s()), "rtg_fuse")

@@ -11,16 +11,18 @@ import ctypes
 import torch
 
 from ._lib import Intrinsics, check, default_config, lib
+from ._lib import ptr as _ptr, stream as _stream
 
 GRAD_NAMES = ("pos", "scale", "rot", "opacity", "color")
 
 
-def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
-
-
-def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _one_launch(t):
+    """Whether a clearing kernel of the library may write t in place of torch's
+    fills: a plain tensor on the current device, with nothing that records or
+    replaces torch's own operations."""
+    return (type(t) is torch.Tensor and t.is_cuda and t.get_device() == torch.cuda.current_device()
+            and torch._C._len_torch_dispatch_stack() == 0 and torch._C._get_tracing_state() is None
+            and not torch.compiler.is_compiling())
 
 
 def _req(t, dtype, shape, name):
@@ -113,11 +115,20 @@ class Rasterizer:
         check(lib().rtg_bin(self._plan, _ptr(ws), _ptr(mask), _stream()), "rtg_bin")
 
     def alloc_outputs(self, device="cuda"):
-        F, H, W = self.frames, self.H, self.W
-        return (torch.zeros((F, H, W, 3), dtype=torch.float32, device=device),
-                torch.full((F, H, W), -1.0, dtype=torch.float32, device=device),
-                torch.ones((F, H, W), dtype=torch.float32, device=device),
-                torch.full((F, H, W), -1, dtype=torch.int32, device=device))
+        shape = (self.frames, self.H, self.W)
+        color = torch.empty((*shape, 3), dtype=torch.float32, device=device)
+        depth = torch.empty(shape, dtype=torch.float32, device=device)
+        trans = torch.empty(shape, dtype=torch.float32, device=device)
+        index = torch.empty(shape, dtype=torch.int32, device=device)
+        if _one_launch(color):
+            check(lib().rtg_clear_outputs(self._plan, _ptr(color), _ptr(depth), _ptr(trans), _ptr(index), _stream()),
+                  "rtg_clear_outputs")
+        else:
+            color.zero_()
+            depth.fill_(-1.0)
+            trans.fill_(1.0)
+            index.fill_(-1)
+        return color, depth, trans, index
 
     def render_into(self, ws, color, depth, trans, index):
         F, H, W = self.frames, self.H, self.W
@@ -137,9 +148,17 @@ class Rasterizer:
 
     def alloc_grads(self, device="cuda"):
         n = self.n
-        return {"pos": torch.zeros((n, 3), device=device), "scale": torch.zeros((n, 3), device=device),
-                "rot": torch.zeros((n, 4), device=device), "opacity": torch.zeros((n,), device=device),
-                "color": torch.zeros(self.color_shape, device=device)}
+        g = {"pos": torch.empty((n, 3), dtype=torch.float32, device=device),
+             "scale": torch.empty((n, 3), dtype=torch.float32, device=device),
+             "rot": torch.empty((n, 4), dtype=torch.float32, device=device),
+             "opacity": torch.empty((n,), dtype=torch.float32, device=device),
+             "color": torch.empty(self.color_shape, dtype=torch.float32, device=device)}
+        if _one_launch(g["pos"]):
+            check(lib().rtg_clear_grads(self._plan, *map(_ptr, g.values()), _stream()), "rtg_clear_grads")
+        else:
+            for t in g.values():
+                t.zero_()
+        return g
 
     def alloc_adam_state(self, device="cuda"):
         """Zeroed Adam moments m, v of shape (n, 10 + 3K) and the step counter."""

@@ -8,11 +8,8 @@ import ctypes
 import torch
 
 from ._lib import IcpParams, check, lib
+from ._lib import ptr as _p, stream as _s
 from .mapping import intrinsics
-
-
-def _p(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
 
 
 def icp_params(levels=None, iters=None, dist=None, sin_angle=None):
@@ -46,5 +43,5 @@ def icp(cam, depth_in, depth_model, normal_model, pose_model, pose_init, prm=Non
     tr = (torch.empty if n_it else torch.zeros)((max(n_it, 1), 48), dtype=torch.float64, device="cuda") if trace else None
     check(lib().rtg_icp(ctypes.byref(intr), ctypes.byref(prm), _p(depth_in), _p(depth_model), _p(normal_model),
                         _p(pose_model), _p(pose_init), _p(pose), _p(tr), _p(ws), nb,
-                        ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)), "rtg_icp")
+                        _s()), "rtg_icp")
     return (pose, tr) if trace else pose

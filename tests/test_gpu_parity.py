@@ -960,3 +960,35 @@ def test_queue_with_fewer_chunks_than_waves(ipp, share):
     assert got["status"]["blend_fwd"] == ref["status"]["blend_fwd"]
     errs = _grad_parity(cam, sc, poses, mask, seed=5, items_per_pop=ipp, static_share=share)
     print("queue gradients", ipp, share, fmt_stats(errs))
+
+
+@pytest.mark.parametrize("n,frames,size,sh", [(0, 1, (1, 1), 0), (1, 1, (3, 1), 0), (1365, 1, (64, 64), 0),
+                                              (1366, 3, (61, 47), 1), (5000, 2, (127, 65), 3)])
+def test_cleared_images_and_gradients(n, frames, size, sh):
+    """One launch clears all images or gradients: every word, at array sizes
+    around a workgroup's 4096, also under a hook on torch's operations (where
+    torch's own fills do it) and from a stream of the caller's."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Seen(TorchDispatchMode):
+        def __torch_dispatch__(self, f, types, args=(), kwargs=None):
+            return f(*args, **(kwargs or {}))
+
+    from contextlib import nullcontext
+    rast = _rast(small_cam(*size, 50.0), n, frames, sh_degree=sh)
+    s = torch.cuda.Stream()
+    for ctx in (nullcontext(), Seen(), torch.cuda.stream(s)):
+        for _ in range(2):   # the second allocation gets memory that was written
+            with ctx:
+                out = rast.alloc_outputs()
+                g = rast.alloc_grads()
+                torch.cuda.synchronize()
+                assert [tuple(t.shape) for t in out] == [(frames, size[1], size[0], 3)] + 3 * [(frames, size[1], size[0])]
+                for t, v in zip(out, (0, -1, 1, -1)):
+                    assert bool((t == v).all()) and t.dtype == (torch.int32 if t is out[3] else torch.float32)
+                for k, t in g.items():
+                    assert t.shape[0] == n and t.dtype == torch.float32 and not bool(t.any()), k
+                for t in (*out, *g.values()):
+                    t.fill_(7)
+                del out, g, t
+    assert tuple(rast.alloc_grads("cpu")["rot"].shape) == (n, 4)
