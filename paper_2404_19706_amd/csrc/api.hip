@@ -513,8 +513,12 @@ rtg_status bin_impl(const rtg_plan* p, void* ws, const uint8_t* mask, void* stre
     } else {
         const unsigned nch = (unsigned)((nft + 4095) / 4096);
         hipLaunchKernelGGL(k_tile_chunk_sums, dim3(nch), dim3(1024), 0, S(stream), d, w);
-        hipLaunchKernelGGL(k_tile_chunk_scan, dim3(1), dim3(1024), 0, S(stream), d, w, (int)nch);
-        hipLaunchKernelGGL(k_tile_chunk_emit, dim3(nch), dim3(1024), 0, S(stream), d, w);
+        if (nch <= (unsigned)kSumChunks) {
+            hipLaunchKernelGGL(k_tile_chunk_emit<true>, dim3(nch), dim3(1024), 0, S(stream), d, w, (int)nch);
+        } else {
+            hipLaunchKernelGGL(k_tile_chunk_scan, dim3(1), dim3(1024), 0, S(stream), d, w, (int)nch);
+            hipLaunchKernelGGL(k_tile_chunk_emit<false>, dim3(nch), dim3(1024), 0, S(stream), d, w, (int)nch);
+        }
         hipLaunchKernelGGL(k_tile_big_order, dim3(1), dim3(1024), 0, S(stream), d, w);
     }
     // staged pairs: about 1024 of capacity per placing workgroup, at most

@@ -496,6 +496,43 @@ __device__ __forceinline__ T block_excl_scan_1024(T v, T* ws, T& total) {
     return ex;
 }
 
+// Four of these scans side by side, with one exchange of the 64 wave totals
+// (`ws`: 64 words, wave w's total of scan k at ws[16 k + w]) between two
+// barriers, where one after the other they had twelve.
+__device__ __forceinline__ void block_excl_scan4_1024(const unsigned long long v[4], unsigned long long* ws,
+                                                      unsigned long long ex[4], unsigned long long total[4]) {
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned long long inc[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) inc[k] = v[k];
+    for (int o = 1; o < 64; o <<= 1) {
+        unsigned long long u[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) u[k] = __shfl_up(inc[k], o);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (lane >= o) inc[k] += u[k];
+    }
+    if (lane == 63) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) ws[16 * k + wv] = inc[k];
+    }
+    __syncthreads();
+    // every wave: lane 16 k + w the totals of waves 0..w in scan k
+    unsigned long long t = ws[lane];
+    for (int o = 1; o < 16; o <<= 1) {
+        const unsigned long long u = __shfl_up(t, o, 16);
+        if ((lane & 15) >= o) t += u;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        total[k] = __shfl(t, 16 * k + 15);
+        const unsigned long long b = __shfl(t, 16 * k + max(wv - 1, 0));
+        ex[k] = inc[k] - v[k] + (wv > 0 ? b : 0ull);
+    }
+    __syncthreads();
+}
+
 // Pair ranges [start, end) of every (frame, tile) from the counts, the
 // total K and the capacity check (on overflow nothing is scattered, sorted
 // or rendered); the work items (packs of up to 64 masked pixels) with the
@@ -504,8 +541,8 @@ __device__ __forceinline__ T block_excl_scan_1024(T v, T* ws, T& total) {
 // consecutive ones per thread of a 1024-thread workgroup, so the loads and
 // stores of a wave are contiguous.  Up to one chunk in all, one workgroup
 // does everything (k_tile_offsets); beyond, the chunks run in parallel:
-// their totals, one workgroup scanning them into per-chunk bases, the
-// chunks' ranges and items, then the long-list order.
+// their totals, per-chunk bases from these, the chunks' ranges and items, then
+// the long-list order.
 //
 // Items go out longest list first, in eight classes of list length (>= 2048,
 // >= 1024, ..., >= 32, shorter), frame and tile order inside a class: the
@@ -559,12 +596,11 @@ __device__ __forceinline__ QuadScan quad_scans(const TileQuad& t, uint32_t cap, 
         if (t.cls[k] < 4) lc0 += pk;
         else lc1 += pk;
     }
-    QuadScan r;
-    r.op = block_excl_scan_1024<unsigned long long>(lp, s64, r.tp);
-    r.oib = block_excl_scan_1024<unsigned long long>(
-        ((unsigned long long)li << kPkI) | ((unsigned long long)lx << kPkX) | lb, s64, r.tib);
-    r.oc0 = block_excl_scan_1024<unsigned long long>(lc0, s64, r.tc0);
-    r.oc1 = block_excl_scan_1024<unsigned long long>(lc1, s64, r.tc1);
+    const unsigned long long v[4] = {lp, ((unsigned long long)li << kPkI) | ((unsigned long long)lx << kPkX) | lb, lc0,
+                                     lc1};
+    unsigned long long ex[4], tot[4];
+    block_excl_scan4_1024(v, s64, ex, tot);
+    const QuadScan r = {ex[0], tot[0], ex[1], tot[1], ex[2], tot[2], ex[3], tot[3]};
     return r;
 }
 
@@ -574,22 +610,34 @@ __device__ __forceinline__ uint32_t class_field(unsigned long long lo, unsigned 
 
 // The work items of tile e, the k-th of this thread's quad, given the
 // per-class item bases.
-__device__ __forceinline__ void emit_items(const Dims& d, const WS& w, int64_t e, int k, const TileQuad& t,
-                                           const QuadScan& s, const uint32_t* cbase) {
+template <typename Item>
+__device__ __forceinline__ void emit_items(const Dims& d, int64_t e, int k, const TileQuad& t, const QuadScan& s,
+                                           const uint32_t* cbase, Item* items) {
     const uint32_t packs = (t.q[k] + 63) >> 6;
     const int c = t.cls[k];
     uint32_t oi = cbase[c] + class_field(s.oc0, s.oc1, c);
 #pragma unroll
     for (int j = 0; j < 3; ++j)
         if (j < k && t.cls[j] == c) oi += (t.q[j] + 63) >> 6;
-    for (uint32_t pk = 0; pk < packs; ++pk) w.items[oi + pk] = (uint32_t)e * (uint32_t)d.ppt + pk;
+    for (uint32_t pk = 0; pk < packs; ++pk) items[oi + pk] = (Item)((uint32_t)e * (uint32_t)d.ppt + pk);
+}
+
+// Where one workgroup writes the items of all (up to 4096) tiles, it collects
+// them in LDS and stores them in order: their places are scattered by class,
+// and scattered stores of one CU took half of the kernel (13k items of a
+// 1200x680 frame: 12.8 us, 8.0 so).
+constexpr int kLdsItems = 16384;
+__device__ __forceinline__ void store_items(const WS& w, const uint16_t* items, uint32_t n) {
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n; i += 1024) w.items[i] = items[i];
 }
 
 // Pair ranges, long lists and work items of this thread's four tiles, given
 // the chunk's pair base co, long-list base cb and per-class item bases.
+template <typename Item>
 __device__ __forceinline__ void emit_quad(const Dims& d, const WS& w, int64_t e0, int64_t total, const TileQuad& t,
                                           const QuadScan& s, unsigned long long co, const uint32_t* cbase,
-                                          uint32_t cb, bool overflow) {
+                                          uint32_t cb, bool overflow, Item* items) {
     const uint32_t cap = (uint32_t)d.sort_cap;
     unsigned long long o = co + s.op;
     uint32_t ob = cb + (uint32_t)(s.oib & kPkBMask);
@@ -601,7 +649,7 @@ __device__ __forceinline__ void emit_quad(const Dims& d, const WS& w, int64_t e0
             w.tile_start[e] = st;
             w.tile_end[e] = overflow ? 0u : st + t.v[k];
             if (!overflow && t.v[k] > cap) w.bigl[ob++] = (uint32_t)e;
-            emit_items(d, w, e, k, t, s, cbase);
+            emit_items(d, e, k, t, s, cbase, items);
         }
         o += t.v[k];
     }
@@ -667,7 +715,8 @@ __device__ __forceinline__ void write_header(const WS& w, unsigned long long K, 
 // Frames of at most 4096 tiles in all: one workgroup scans the single chunk
 // and writes everything.
 __global__ __launch_bounds__(1024) void k_tile_offsets(Dims d, WS w) {
-    __shared__ unsigned long long s64[16];
+    __shared__ unsigned long long s64[64];
+    __shared__ uint16_t it[kLdsItems];
     const int tid = threadIdx.x;
     const int64_t total = (int64_t)d.F * d.ntiles;
     const int64_t e0 = 4 * tid;
@@ -682,7 +731,8 @@ __global__ __launch_bounds__(1024) void k_tile_offsets(Dims d, WS w) {
         cbase[c] = acc;
         acc += class_field(s.tc0, s.tc1, c);
     }
-    emit_quad(d, w, e0, total, t, s, 0ull, cbase, 0u, overflow);
+    emit_quad(d, w, e0, total, t, s, 0ull, cbase, 0u, overflow, it);
+    store_items(w, it, (uint32_t)(s.tib >> kPkI));
     const uint32_t nbig = overflow ? 0u : (uint32_t)(s.tib & kPkBMask);
     __syncthreads();
     if (nbig) order_big(d, w, nbig, s64);
@@ -693,7 +743,7 @@ __global__ __launch_bounds__(1024) void k_tile_offsets(Dims d, WS w) {
 // More tiles: chunks of 4096 in parallel.  1: each chunk's totals
 // (workgroup per chunk) into chunk[16 c + 0..3].
 __global__ __launch_bounds__(1024) void k_tile_chunk_sums(Dims d, WS w) {
-    __shared__ unsigned long long s64[16];
+    __shared__ unsigned long long s64[64];
     const int64_t total = (int64_t)d.F * d.ntiles;
     TileQuad t;
     load_quad(w, (int64_t)blockIdx.x * 4096 + 4 * threadIdx.x, total, t);
@@ -707,7 +757,7 @@ __global__ __launch_bounds__(1024) void k_tile_chunk_sums(Dims d, WS w) {
     }
 }
 
-// 2: one workgroup scans the chunk totals: per chunk its pair base
+// 2 (beyond 64 chunks): one workgroup scans the chunk totals: per chunk its pair base
 // (chunk[16 c + 4]), long-list base (+5) and item base per class (+6..13,
 // classes in order, each class after all items of the classes before it);
 // the total K decides the overflow; the header gets the totals.
@@ -784,19 +834,64 @@ __global__ __launch_bounds__(1024) void k_tile_chunk_scan(Dims d, WS w, int nchu
     if (tid == 0) write_header(w, K, overflow, (uint32_t)cx, (uint32_t)(cib >> 32), (uint32_t)(cib & 0xffffffffull));
 }
 
-// 3: each chunk's ranges, long lists and items from its bases.
-__global__ __launch_bounds__(1024) void k_tile_chunk_emit(Dims d, WS w) {
-    __shared__ unsigned long long s64[16];
+// 3: each chunk's ranges, long lists and items from its bases.  With SUMS
+// (up to 64 chunks, a lane each) every workgroup forms its bases from the
+// chunks' totals itself, a wave per quantity, and the first writes the header:
+// step 2 takes 14 us for thirteen chunks, waiting on its twenty block scans
+// (14.7 + 10.2 us with it, 10.1 so).
+constexpr int kSumChunks = 64;
+
+template <bool SUMS>
+__global__ __launch_bounds__(1024) void k_tile_chunk_emit(Dims d, WS w, int nchunk) {
+    __shared__ unsigned long long s64[64];
+    __shared__ unsigned long long all[kCls + 4], before[kCls + 4];   // classes; pairs, long lists, items, pixels
     const int64_t total = (int64_t)d.F * d.ntiles;
     const int64_t e0 = (int64_t)blockIdx.x * 4096 + 4 * threadIdx.x;
+    if constexpr (SUMS) {
+        const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+        if (q < kCls + 4) {
+            const unsigned long long* ch = w.chunk + 16ull * (lane < nchunk ? lane : 0);
+            const unsigned long long tib = ch[1];
+            unsigned long long v = q < kCls        ? class_field(ch[2], ch[3], q)
+                                   : q == kCls     ? ch[0]
+                                   : q == kCls + 1 ? tib & kPkBMask
+                                   : q == kCls + 2 ? tib >> kPkI
+                                                   : (tib >> kPkX) & kPkXMask;
+            if (lane >= nchunk) v = 0ull;
+            unsigned long long p = lane < (int)blockIdx.x ? v : 0ull;
+            for (int o = 32; o > 0; o >>= 1) {
+                v += __shfl_xor(v, o);
+                p += __shfl_xor(p, o);
+            }
+            if (lane == 0) {
+                all[q] = v;
+                before[q] = p;
+            }
+        }
+    }
     TileQuad t;
     load_quad(w, e0, total, t);
-    const QuadScan s = quad_scans(t, (uint32_t)d.sort_cap, s64);
-    const unsigned long long* ch = w.chunk + 16ull * blockIdx.x;
+    const QuadScan s = quad_scans(t, (uint32_t)d.sort_cap, s64);   // (its barriers order the sums too)
     uint32_t cbase[kCls];
+    if constexpr (SUMS) {
+        const unsigned long long K = all[kCls];
+        const bool overflow = K > (unsigned long long)d.max_pairs;
+        uint32_t acc = 0;
 #pragma unroll
-    for (int k = 0; k < kCls; ++k) cbase[k] = (uint32_t)ch[6 + k];
-    emit_quad(d, w, e0, total, t, s, ch[4], cbase, (uint32_t)ch[5], w.hdr->overflow != 0u);
+        for (int k = 0; k < kCls; ++k) {
+            cbase[k] = acc + (uint32_t)before[k];
+            acc += (uint32_t)all[k];
+        }
+        emit_quad(d, w, e0, total, t, s, before[kCls], cbase, (uint32_t)before[kCls + 1], overflow, w.items);
+        if (blockIdx.x == 0 && threadIdx.x == 0)
+            write_header(w, K, overflow, (uint32_t)all[kCls + 3], (uint32_t)all[kCls + 2],
+                         overflow ? 0u : (uint32_t)all[kCls + 1]);
+    } else {
+        const unsigned long long* ch = w.chunk + 16ull * blockIdx.x;
+#pragma unroll
+        for (int k = 0; k < kCls; ++k) cbase[k] = (uint32_t)ch[6 + k];
+        emit_quad(d, w, e0, total, t, s, ch[4], cbase, (uint32_t)ch[5], w.hdr->overflow != 0u, w.items);
+    }
 }
 
 // 4: the long lists longest first.
@@ -1433,7 +1528,8 @@ __global__ __launch_bounds__(256) void k_tile_gather(Dims d, WS w, const uint8_t
 // tile_end; the pair counter is cleared for the next binning of this
 // projection.
 __global__ __launch_bounds__(1024) void k_tile_items(Dims d, WS w) {
-    __shared__ unsigned long long s64[16];
+    __shared__ unsigned long long s64[64];
+    __shared__ uint16_t it[kLdsItems];
     const int tid = threadIdx.x;
     const int64_t total = (int64_t)d.F * d.ntiles, e0 = 4 * tid;
     TileQuad t;
@@ -1453,10 +1549,11 @@ __global__ __launch_bounds__(1024) void k_tile_items(Dims d, WS w) {
         if (e < total) {
             w.tile_start[e] = overflow ? 0u : o;
             w.tile_end[e] = overflow ? 0u : o + t.v[k];
-            emit_items(d, w, e, k, t, s, cbase);
+            emit_items(d, e, k, t, s, cbase, it);
         }
         o += t.v[k];
     }
+    store_items(w, it, (uint32_t)(s.tib >> kPkI));
     if (tid == 0) {
         write_header(w, K, overflow, (uint32_t)((s.tib >> kPkX) & kPkXMask), (uint32_t)(s.tib >> kPkI),
                      overflow ? 0u : (uint32_t)(s.tib & kPkBMask));

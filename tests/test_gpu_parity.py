@@ -992,3 +992,32 @@ def test_cleared_images_and_gradients(n, frames, size, sh):
                     t.fill_(7)
                 del out, g, t
     assert tuple(rast.alloc_grads("cpu")["rot"].shape) == (n, 4)
+
+
+@pytest.mark.parametrize("frames,max_pairs", [(19, 0), (20, 0), (19, 1000)])
+def test_tile_ranges_over_sixty_four_chunks(frames, max_pairs):
+    """19 frames of 143 x 96 tiles are 64 chunks of 4096, 20 are 68 (where one
+    workgroup scans the chunks' totals): the oracle's lists and totals; with
+    too little room the overflow is reported and nothing is listed."""
+    size, n = (1142, 767), 300
+    cam = small_cam(*size, 0.8 * size[0])
+    sc, poses = _two_pose_scene(1, n=n)
+    poses = poses[np.arange(frames) % 2]
+    mask = (np.random.default_rng(3).random((frames, size[1], size[0])) < 0.01).astype(np.uint8)
+    rast = _rast(cam, n, frames, tile_w=8, tile_h=8, **({"max_pairs": max_pairs} if max_pairs else {}))
+    ws = rast.new_workspace()
+    rast.project(ws, *dev_params(sc), dev_poses(poses))
+    rast.bin(ws, dev_mask(mask))
+    st = rast.read_status(ws)
+    P = orc.make_params(cam, tile=(8, 8))
+    recs = orc.project(P, sc, poses)
+    b = orc.bin_pairs(P, recs, mask)
+    assert st["pairs"] == len(b["gid"]) and st["pixels"] == int(mask.sum())
+    pad = np.zeros((frames, 768, 1144), np.uint8)
+    pad[:, :767, :1142] = mask
+    if max_pairs:
+        assert st["overflow"] == 1 and st["items"] == 0
+        assert not ws_view(rast, ws, "tile_end", torch.int32, frames * 143 * 96).any()
+        return
+    assert st["items"] == int((pad.reshape(frames, 96, 8, 143, 8).sum((2, 4)) > 0).sum())
+    _check_pairs(rast, ws, P, recs, mask, frames, n, {"status": st})
