@@ -333,7 +333,7 @@ rtg_status rtg_plan_create(const rtg_config* cfg, const rtg_intrinsics* intr, in
     // it sized them for.
     p->few_blocks = false;
     while (cfg->stage_cap == 0 && d.chunk > 1024 && (int64_t)frames * d.nbpf * d.nchunks < 512) {
-        d.chunk = std::max(1024, d.chunk / 2);
+        d.chunk = std::max(1024, (d.chunk + 1) / 2);
         d.nchunks = (d.ntiles + d.chunk - 1) / d.chunk;
         p->few_blocks = true;
     }
@@ -418,54 +418,14 @@ rtg_status rtg_unstable_mask(const rtg_plan* p, void* ws, uint8_t* mask_out, voi
 
 namespace {
 
-// Side stream of a device: the short-list and long-list sorts of rtg_bin
-// run on it beside the mid-length sorts on the caller's stream (the run
-// sorts and merges of the few long lists are launches that would otherwise
-// leave much of the chip idle).  Created at the first eager
-// binning call on the device and kept until the process ends; the lock
-// orders the fork and join enqueues of concurrent callers.
-struct SideStream {
-    hipStream_t s = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
-};
-constexpr int kMaxSideDevices = 64;
-constexpr int64_t kSideFrom = 16384;   // (frame, tile)s from which the sorts fork
-std::mutex g_side_mu;
-SideStream* g_side[kMaxSideDevices] = {};
-
-// The current device's side stream, or nullptr (serial launches) when it
-// does not exist yet and `caller` is being captured, or cannot be made.
-SideStream* side_stream(hipStream_t caller) {
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxSideDevices) return nullptr;
-    if (g_side[dev]) return g_side[dev];
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(caller, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return nullptr;
-    SideStream* ss = new (std::nothrow) SideStream;
-    if (!ss) return nullptr;
-    bool ok = hipStreamCreateWithFlags(&ss->s, hipStreamNonBlocking) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&ss->fork, hipEventDisableTiming) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&ss->join, hipEventDisableTiming) == hipSuccess;
-    if (!ok) {
-        if (ss->join) (void)hipEventDestroy(ss->join);
-        if (ss->fork) (void)hipEventDestroy(ss->fork);
-        if (ss->s) (void)hipStreamDestroy(ss->s);
-        delete ss;
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    g_side[dev] = ss;
-    return ss;
-}
-
-rtg_status bin_impl(const rtg_plan* p, void* ws, const uint8_t* mask, void* stream, bool allow_side);
+constexpr int64_t kMaxSortGrid = int64_t(1) << 23;   // workgroups of 256 in one launch of k_tile_sort
 
 // Binning by one workgroup per tile (k_tile_gather).  Measured against the
 // general path, us per step of one frame unless said (Gaussians, tiles):
-// 2,000, 48: 52 / 68; 10,000, 117: 55 / 68; 2,000, 1,000: 69 / 76; 20,000,
-// 300: 66 / 72; 3 frames of 10,000, 741: 73 / 78; 16,000, 640: 70 / 74;
-// 30,000, 300: 73 / 74; 10,000, 1,000: 78 / 77; 40,000, 300: 80 / 77; 30,000,
-// 1,000: 100 / 82.  (The configurations of the sort and of the staging mean
+// 2,000, 48: 50 / 62; 16,000, 117: 58 / 65; 2,000, 1,000: 66 / 72; 20,000,
+// 300: 65 / 68; 3 frames of 10,000, 741: 73 / 76; 16,000, 640: 72 / 72; 10,000,
+// 1,000: 73 / 73; 30,000, 300: 73 / 71; 40,000, 300: 80 / 72.  (The
+// configurations of the sort and of the staging mean
 // the general path.)
 bool bin_gathers(const rtg_plan* p) {
     const int64_t nft = (int64_t)p->d.F * p->d.ntiles;
@@ -476,12 +436,6 @@ bool bin_gathers(const rtg_plan* p) {
 }  // namespace
 
 rtg_status rtg_bin(const rtg_plan* p, void* ws, const uint8_t* mask, void* stream) {
-    return bin_impl(p, ws, mask, stream, true);
-}
-
-namespace {
-
-rtg_status bin_impl(const rtg_plan* p, void* ws, const uint8_t* mask, void* stream, bool allow_side) {
     if (!ws_ok(p, ws) || !mask) return RTG_E_INVALID;
     WS w = make_ws(p, ws);
     const Dims& d = p->d;
@@ -534,36 +488,18 @@ rtg_status bin_impl(const rtg_plan* p, void* ws, const uint8_t* mask, void* stre
     const int64_t jobs_max = (int64_t)d.max_pairs / d.big_chunk + std::min<int64_t>(big_max, nft);
     const unsigned jgrid = (unsigned)std::min<int64_t>(jobs_max, 1024);
     const int64_t big_grid = std::min<int64_t>(std::min<int64_t>(nft, 512), big_max);
-    // the short lists, the run-sort jobs and the long-list merges on the
-    // side stream, the mid-length lists on the caller's: they write
-    // disjoint lists
-    std::unique_lock<std::mutex> lock(g_side_mu, std::defer_lock);
-    SideStream* side = nullptr;
-    // (a small problem's sorts are short: there the cross-queue
-    // synchronisation would cost more than the overlap gains)
-    if (allow_side && nft >= kSideFrom) {
-        lock.lock();
-        side = side_stream(S(stream));
-    }
-    const hipStream_t sa = S(stream), sb = side ? side->s : sa;
-    if (side && (hipEventRecord(side->fork, sa) != hipSuccess || hipStreamWaitEvent(sb, side->fork, 0) != hipSuccess))
-        return RTG_E_HIP;
-    hipLaunchKernelGGL(k_tile_sort_small, dim3((unsigned)((nft + 3) / 4)), dim3(256), 0, sb, d, w, (uint32_t)nft);
-    if (side) {
-        hipLaunchKernelGGL(k_tile_sort_runs, dim3(jgrid), dim3(256), 0, sb, d, w);
-        hipLaunchKernelGGL(k_tile_sort_big, dim3((unsigned)big_grid), dim3(1024), 0, sb, d, w);
-        hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)nft), dim3(256), 0, sa, d, w, 0u);
-    } else {
-        // one launch for the jobs and the mid-length lists, then the merges
-        hipLaunchKernelGGL(k_tile_sort, dim3(jgrid + (unsigned)nft), dim3(256), 0, sa, d, w, jgrid);
-        hipLaunchKernelGGL(k_tile_sort_big, dim3((unsigned)big_grid), dim3(1024), 0, sa, d, w);
-    }
-    if (side && (hipEventRecord(side->join, sb) != hipSuccess || hipStreamWaitEvent(sa, side->join, 0) != hipSuccess))
-        return RTG_E_HIP;
+    // one launch for the jobs, the mid-length and the short lists (several
+    // beyond a grid's 2^32 threads), then the merges.  On a stream each (the
+    // short lists, jobs and merges beside the mid-length lists) the sorts of
+    // 8 frames of 1200x680 with 1M Gaussians ended 16 us later, those of two
+    // with 25,500 8x8 tiles each 18.
+    const int64_t groups = (int64_t)jgrid + nft + (nft + 3) / 4;
+    for (int64_t g0 = 0; g0 < groups; g0 += kMaxSortGrid)
+        hipLaunchKernelGGL(k_tile_sort, dim3((unsigned)std::min(groups - g0, kMaxSortGrid)), dim3(256), 0, S(stream), d,
+                           w, (uint32_t)g0, jgrid, (uint32_t)nft);
+    hipLaunchKernelGGL(k_tile_sort_big, dim3((unsigned)big_grid), dim3(1024), 0, S(stream), d, w);
     return launched();
 }
-
-}  // namespace
 
 rtg_status rtg_clear_outputs(const rtg_plan* p, float* color, float* depth, float* trans, int32_t* index,
                              void* stream) {
@@ -618,8 +554,7 @@ rtg_status rtg_forward_static(const rtg_plan* p, const float* pos, const float* 
     // projection clears the header (counters, overflow and error flags);
     // nothing else in the workspace is read before this call writes it
     if ((st = rtg_project(p, ws, pos, scale, rot, opacity, color, unstable, poses, stream)) != RTG_OK) return st;
-    // (binning without the side stream: this call creates nothing)
-    if ((st = bin_impl(p, ws, mask, stream, false)) != RTG_OK) return st;
+    if ((st = rtg_bin(p, ws, mask, stream)) != RTG_OK) return st;
     if ((st = rtg_render(p, ws, out_color, out_depth, out_trans, out_index, stream)) != RTG_OK) return st;
     if (status_out) {
         WS w = make_ws(p, ws);

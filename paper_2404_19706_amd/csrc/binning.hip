@@ -1137,7 +1137,7 @@ __device__ __forceinline__ void put_sorted_run(const WS& w, const unsigned long 
 
 // Lists of at most kWaveSort pairs: one wave, rank sort (every key counts
 // the smaller keys of its list, read as LDS broadcasts; keys are unique, so
-// ranks are the positions), in k_tile_sort_small.  k_tile_sort: one
+// ranks are the positions), in the last workgroups of k_tile_sort.  The others: one
 // workgroup per (frame, tile), the longer lists up to sort_cap, whole
 // workgroup, LDS bitonic sort.
 constexpr int kWaveSort = 256;
@@ -1199,17 +1199,16 @@ __device__ __forceinline__ void wave_sort_list(const WS& w, unsigned long long* 
 }
 
 // Lists of at most kWaveSort (and sort_cap) pairs: one wave each, four
-// (frame, tile)s per workgroup, each wave with its own 2 KB of LDS keys (so
-// that many such workgroups share a CU).
-__global__ __launch_bounds__(256) void k_tile_sort_small(Dims d, WS w, uint32_t nft) {
-    __shared__ unsigned long long K[4][kWaveSort];
+// (frame, tile)s per workgroup, each wave with its own 2 KB of LDS keys.
+__device__ __forceinline__ void sort_small(const Dims& d, const WS& w, unsigned long long* K, uint32_t block,
+                                           uint32_t nft) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const uint32_t ft = 4u * blockIdx.x + (uint32_t)wv;
+    const uint32_t ft = 4u * block + (uint32_t)wv;
     if (ft >= nft) return;
     const uint32_t start = w.tile_start[ft];
     const uint32_t n = w.tile_end[ft] - start;
     if (n == 0u || n > (uint32_t)kWaveSort || n > (uint32_t)d.sort_cap) return;
-    wave_sort_list(w, K[wv], w.keys + start, start, n, (ft / (uint32_t)d.ntiles) * (uint32_t)d.N, lane);
+    wave_sort_list(w, K + wv * kWaveSort, w.keys + start, start, n, (ft / (uint32_t)d.ntiles) * (uint32_t)d.N, lane);
 }
 
 // Run-sort jobs of the lists longer than sort_cap: the runs of big_chunk
@@ -1247,17 +1246,25 @@ __device__ __forceinline__ void run_sort_jobs(const Dims& d, const WS& w, unsign
     }
 }
 
-// Workgroups below jgrid: run-sort jobs (when the jobs are not launched on
-// their own); the others one (frame, tile) each, the lists of kWaveSort+1
-// to sort_cap keys (the short lists are sorted by k_tile_sort_small, the
-// longer ones by the jobs and k_tile_sort_big).
-__global__ __launch_bounds__(256) void k_tile_sort(Dims d, WS w, uint32_t jgrid) {
+// Workgroups (of the launches together, this one's from `first` on) below
+// jgrid: run-sort jobs; then nft of one (frame, tile) each, the lists of
+// kWaveSort+1 to sort_cap keys (the longer ones are sorted by the jobs and
+// k_tile_sort_big); from jgrid + nft on the short lists.  All three in one
+// launch, the longest work first: each kind alone leaves much of the chip idle
+// (1200x680 view of 500k Gaussians: short lists 17.0 us and mid-length ones
+// 15.8, 19.7 together).
+__global__ __launch_bounds__(256) void k_tile_sort(Dims d, WS w, uint32_t first, uint32_t jgrid, uint32_t nft) {
     __shared__ unsigned long long K[kSortLds];
-    if (blockIdx.x < jgrid) {
-        run_sort_jobs(d, w, K, blockIdx.x, jgrid);
+    const uint32_t b = first + blockIdx.x;
+    if (b < jgrid) {
+        run_sort_jobs(d, w, K, b, jgrid);
         return;
     }
-    const uint32_t ft = blockIdx.x - jgrid;
+    const uint32_t ft = b - jgrid;
+    if (ft >= nft) {
+        sort_small(d, w, K, ft - nft, nft);
+        return;
+    }
     const uint32_t start = w.tile_start[ft];
     const uint32_t n = w.tile_end[ft] - start;
     if (n <= (uint32_t)kWaveSort || n > (uint32_t)d.sort_cap) return;
@@ -1266,16 +1273,10 @@ __global__ __launch_bounds__(256) void k_tile_sort(Dims d, WS w, uint32_t jgrid)
     put_sorted_run(w, K, start, n, fbase, threadIdx.x, blockDim.x);
 }
 
-// The run-sort jobs on their own (beside the mid-length lists).
-__global__ __launch_bounds__(256) void k_tile_sort_runs(Dims d, WS w) {
-    __shared__ unsigned long long K[kSortLds];
-    run_sort_jobs(d, w, K, blockIdx.x, gridDim.x);
-}
-
 // ---- lists longer than sort_cap ---------------------------------------------
 //
 // The runs of big_chunk keys of every long list were sorted in place by the
-// run-sort workgroups of k_tile_sort_runs.  Here one 1024-thread workgroup per
+// run-sort workgroups of k_tile_sort.  Here one 1024-thread workgroup per
 // listed tile merges them pairwise (merge path: the co-ranks of an output
 // window's ends are found by binary search, the window's inputs are staged
 // in LDS, and every thread merges its share after its own co-rank search in
@@ -1392,7 +1393,7 @@ __global__ __launch_bounds__(1024) void k_tile_sort_big(Dims d, WS w) {
 // ---- few tiles, few Gaussians: one workgroup per tile -----------------------
 //
 // Where a launch costs more than its work (about 3.5 us of host time and 5 us
-// in a chain of dependent ones), the eight launches above become three.  1:
+// in a chain of dependent ones), the seven launches above become three.  1:
 // every (frame, tile) lists its masked pixels and tests all of the frame's
 // Gaussians: their rectangle (12 bytes each, coalesced), then the thinning
 // rule for those it holds; it sorts its keys in LDS and leaves them at a place

@@ -1021,3 +1021,30 @@ def test_tile_ranges_over_sixty_four_chunks(frames, max_pairs):
         return
     assert st["items"] == int((pad.reshape(frames, 96, 8, 143, 8).sum((2, 4)) > 0).sum())
     _check_pairs(rast, ws, P, recs, mask, frames, n, {"status": st})
+
+
+def test_sorts_over_more_workgroups_than_a_launch():
+    """32 frames of 512 x 512 tiles: the sorts take two launches (8.4M
+    workgroups in the first); the last frame's lists are those of a plan of
+    one frame, the total 32 times its."""
+    need_gpu()
+    size, n, F, nt = (4096, 4096), 200, 32, 512 * 512
+    cam = small_cam(*size, 0.8 * size[0])
+    sc, poses = _two_pose_scene(1, n=n)
+    m = torch.zeros((1, size[1], size[0]), dtype=torch.uint8, device="cuda")
+    m[:, 3::64, 5::16] = 1
+    got = []
+    for f in (1, F):
+        rast = _rast(cam, n, f, tile_w=8, tile_h=8, sort_cap=4096)
+        ws = rast.new_workspace()
+        rast.project(ws, *dev_params(sc), dev_poses(poses[np.zeros(f, int)]))
+        rast.bin(ws, m.expand(f, -1, -1).contiguous())
+        st = rast.read_status(ws)
+        end = ws_view(rast, ws, "tile_end", torch.int32, f * nt)[-nt:].cpu().numpy()
+        start = ws_view(rast, ws, "tile_start", torch.int32, f * nt)[-nt:].cpu().numpy()
+        pairs = ws_view(rast, ws, "pairs", torch.int32, st["pairs"]).cpu().numpy()
+        got.append((st["pairs"], st["items"], end - start, pairs[-(st["pairs"] // f):] - (f - 1) * n))
+        del ws, rast
+    (k1, i1, c1, p1), (kF, iF, cF, pF) = got
+    assert k1 > 10000 and kF == F * k1 and iF == F * i1
+    assert np.array_equal(c1, cF) and np.array_equal(p1, pF)
