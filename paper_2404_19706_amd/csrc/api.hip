@@ -530,7 +530,6 @@ rtg_status rtg_render(const rtg_plan* p, void* ws, float* color, float* depth, f
     rtg_status st = dev_info(di);
     if (st != RTG_OK) return st;
     WS w = make_ws(p, ws);
-    if (p->d.fwd_items_per_pop) hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, S(stream), &w.hdr->q_fwd);
     if (p->d.depth_mode == 0)
         hipLaunchKernelGGL(k_raster_fwd<0>, dim3(di.fwd_blocks[0]), dim3(256), 0, S(stream), p->d, w, color, depth,
                            trans, index);
@@ -590,7 +589,6 @@ rtg_status rtg_backward_raster(const rtg_plan* p, void* ws, const float* out_dep
     if (st != RTG_OK) return st;
     WS w = make_ws(p, ws);
     const L1Up up = {nullptr, nullptr, nullptr, 0};
-    if (p->d.items_per_pop) hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, S(stream), &w.hdr->q_bwd);
     if (p->d.depth_mode == 0)
         hipLaunchKernelGGL(k_raster_bwd<0>, dim3(di.bwd_blocks[0]), dim3(256), 0, S(stream), p->d, w, out_depth,
                            out_trans, out_index, d_color, d_depth, up);
@@ -614,7 +612,6 @@ rtg_status rtg_backward_raster_l1(const rtg_plan* p, void* ws, const float* out_
     if (st != RTG_OK) return st;
     WS w = make_ws(p, ws);
     const L1Up up = {out_color, color_gt, depth_gt, 1};
-    if (p->d.items_per_pop) hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(64), 0, S(stream), &w.hdr->q_bwd);
     if (p->d.depth_mode == 0)
         hipLaunchKernelGGL(k_raster_bwd<0>, dim3(di.bwd_blocks[0]), dim3(256), 0, S(stream), p->d, w, out_depth,
                            out_trans, out_index, (const float*)nullptr, (const float*)nullptr, up);

@@ -50,8 +50,8 @@ struct Hdr {
     uint32_t overflow;     // K > max_pairs
     uint32_t n_big;        // tiles sorted on the long-list path
     uint32_t err;          // device error bits
-    uint32_t q_fwd, pad_fwd;   // queue heads of the compositing kernels, cleared
-    uint32_t q_bwd, pad_bwd;   // by k_queue_reset before each launch that pops
+    uint32_t q_fwd, pad_fwd;   // queue heads of the compositing kernels: zero from
+    uint32_t q_bwd, pad_bwd;   // the projection on, and again after every launch that pops
     float loss_c, loss_d;  // L1 sums
     uint32_t cnt_m, cnt_md;
     uint32_t q_big;        // next entry of the long-list queue

@@ -1048,3 +1048,35 @@ def test_sorts_over_more_workgroups_than_a_launch():
     (k1, i1, c1, p1), (kF, iF, cF, pF) = got
     assert k1 > 10000 and kF == F * k1 and iF == F * i1
     assert np.array_equal(c1, cF) and np.array_equal(p1, pF)
+
+
+@pytest.mark.parametrize("ipp,share,fwd", [(1, 0, -1), (2, 50, 4), (64, 0, 1), (7, 30, 0)])
+def test_queue_heads_serve_repeated_launches(ipp, share, fwd):
+    """The last pop of a launch clears its queue head: renders and backwards
+    repeated on one binning, and after another binning (also an empty one),
+    take every item again."""
+    cam = small_cam(160, 120, 144.0)
+    sc, poses = _two_pose_scene(5, n=900)
+    rng = np.random.default_rng(2)
+    mask = (rng.random((2, 120, 160)) < 0.5).astype(np.uint8)
+    rast = _rast(cam, 900, 2, items_per_pop=ipp, static_share=share, fwd_items_per_pop=fwd)
+    prm, ps = dev_params(sc), dev_poses(poses)
+    ws = rast.new_workspace()
+    rast.project(ws, *prm, ps)
+    up = torch.ones((2, 120, 160, 3), device="cuda"), torch.ones((2, 120, 160), device="cuda")
+    ref = None
+    for k, m in enumerate((mask, mask, np.zeros_like(mask), mask)):
+        rast.bin(ws, dev_mask(m))
+        for _ in range(2):
+            out = rast.alloc_outputs()
+            rast.render_into(ws, *out)
+            rast.backward_raster(ws, *out[1:], *up)
+            st = rast.read_status(ws)
+            got = [t.cpu().numpy() for t in out] + [st["blend_fwd"], st["walk_bwd"]]
+            if not m.any():
+                assert st["items"] == 0 and st["blend_fwd"] == 0 and bool((out[2] == 1).all())
+                continue
+            ref = ref or got
+            for a, b in zip(got, ref):
+                assert np.array_equal(a, b), k
+    print("queue heads", ipp, share, fwd, ref[-2:])
