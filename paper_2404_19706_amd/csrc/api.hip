@@ -418,6 +418,11 @@ rtg_status rtg_unstable_mask(const rtg_plan* p, void* ws, uint8_t* mask_out, voi
 
 namespace {
 
+// Gaussians per binning range from which k_pair_hist collects those with an
+// active row: with 256 a wave has one group of 64, nothing to collect, and the
+// loads that then come one after the other are its time.
+constexpr int32_t kQueueFrom = 512;
+
 constexpr int64_t kMaxSortGrid = int64_t(1) << 23;   // workgroups of 256 in one launch of k_tile_sort
 
 // Binning by one workgroup per tile (k_tile_gather).  Measured against the
@@ -457,7 +462,8 @@ rtg_status rtg_bin(const rtg_plan* p, void* ws, const uint8_t* mask, void* strea
     hipLaunchKernelGGL(k_tile_pixels, dim3(grid_for(nft, 4)), dim3(256), 0, S(stream), d, w, m);
     const unsigned nbb = (unsigned)((int64_t)d.F * d.nbpf * d.nchunks);
     const size_t lds = 4 * ((size_t)d.chunk + (d.chunk + 31) / 32);
-    hipLaunchKernelGGL(k_pair_hist, dim3(nbb), dim3(256), lds, S(stream), d, w);
+    if (d.gpb >= kQueueFrom) hipLaunchKernelGGL(k_pair_hist<true>, dim3(nbb), dim3(256), lds, S(stream), d, w);
+    else hipLaunchKernelGGL(k_pair_hist<false>, dim3(nbb), dim3(256), lds, S(stream), d, w);
     if (nft >= kScanWideFrom)
         hipLaunchKernelGGL(k_hist_scan<64>, dim3(grid_for(nft, 64)), dim3(kScanThreads), 0, S(stream), d, w);
     else

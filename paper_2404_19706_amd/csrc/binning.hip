@@ -281,56 +281,124 @@ __device__ __forceinline__ void row_span(const Dims& d, const Conic& k, int a0, 
 // robin, a lane finding the owning Gaussian by a binary search over the
 // scan (only rows whose rectangle columns hold an active tile count); the
 // lane then walks the active tiles of the row's kept run.
-template <typename Fn>
-__device__ __forceinline__ void block_pairs(const Dims& d, const WS& w, const Chunk& c, const uint32_t* act, Fn fn) {
+//
+// With QUEUE, the Gaussians that have a row are collected in LDS and taken 64
+// at a time: under a mask most visible Gaussians have none, and a round of row
+// numbers, binary64 spans and walks costs the same for ten rows as for 64; the
+// others' conics and depths aren't loaded either.  k_pair_hist over 16 frames
+// with masks of 5-61 % (5M Gaussians): 660 to 474 us; five frames of 8x8 tiles
+// (90k), binning 123 to 104; a full frame (500k), where all have rows, 25.9 to
+// 26.7.
+struct PairQueue {
+    uint64_t rows[128];
+    short4 rect[128];   // tile columns, tile rows (inside the chunk)
+    uint32_t slot[128];
+};
+
+template <bool QUEUE, typename Fn>
+__device__ __forceinline__ void block_pairs(const Dims& d, const WS& w, const Chunk& c, const uint32_t* act,
+                                            PairQueue* pq, Fn fn) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const uint64_t below = (1ull << lane) - 1ull;
     const int64_t ngb = (int64_t)(d.gpb >> 6);
     const int64_t gr0 = (int64_t)c.b * ngb, gr1 = min(gr0 + ngb, d.ngrp);
     const uint32_t* vc = w.vcnt + (int64_t)c.f * d.ngrp;
     const uint8_t* vl = w.vlist + (int64_t)c.f * d.ngrp * 64;
     const int ry0 = c.t0 / d.tx, ry1 = (c.t1 - 1) / d.tx;
     const int ct = c.t1 - c.t0;
-    for (int64_t wb = gr0 + wv; wb < gr1; wb += 256) {
+    int held = 0;   // wave-uniform, entries of pq
+    for (int64_t wb = gr0 + wv;; wb += 256) {
+        // (past the range one more round takes what is still held)
+        const bool last = wb >= gr1;
+        if (last && (!QUEUE || held == 0)) break;
         const int64_t mine = wb + 4 * lane;
         const uint32_t cnt = mine < gr1 ? vc[mine] : 0u;
         const uint32_t ginc = wave_incl_scan(cnt, lane);
         const uint32_t V = (uint32_t)__shfl((int)ginc, 63);
-        for (uint32_t v0 = 0; v0 < V; v0 += 64u) {
+        for (uint32_t v0 = 0; v0 < V || (QUEUE && last && held > 0); v0 += 64u) {
             const uint32_t idx = v0 + (uint32_t)lane;
             bool ok = idx < V;
-            // group: the number of lanes whose inclusive count is <= idx
-            int gs = 0;
-#pragma unroll
-            for (int st = 32; st > 0; st >>= 1)
-                if ((uint32_t)__shfl((int)ginc, gs + st - 1) <= idx) gs += st;
-            gs = min(gs, 63);
-            const uint32_t gex = (uint32_t)__shfl((int)(ginc - cnt), gs);
-            int64_t i = 0;
-            if (ok) {
-                const int64_t gr = wb + 4 * gs;
-                i = gr * 64 + vl[gr * 64 + (idx - gex)];
-            }
             int a0 = 0, a1 = -1, y0 = 0, y1 = -1;
             uint32_t slot = 0, zb = 0;
             Conic k = {0.f, 0.f, 0.f, 0.f, 0.f};
-            if (ok) {
-                slot = (uint32_t)((int64_t)c.f * d.N + i);
-                tile_range(d, w.rect[slot], a0, a1, y0, y1);
-                y0 = max(y0, ry0);
-                y1 = min(y1, ry1);
-                ok = y0 <= y1;
+            auto load_rec = [&]() {
                 const float4 r0 = w.rec[4ull * slot], r1 = w.rec[4ull * slot + 1];
                 k = Conic{r0.x, r0.y, r0.z, r0.w, r1.x};
                 zb = __float_as_uint(w.zkey[slot]);
+            };
+            if (!QUEUE || !last) {
+                // group: the number of lanes whose inclusive count is <= idx
+                int gs = 0;
+#pragma unroll
+                for (int st = 32; st > 0; st >>= 1)
+                    if ((uint32_t)__shfl((int)ginc, gs + st - 1) <= idx) gs += st;
+                gs = min(gs, 63);
+                const uint32_t gex = (uint32_t)__shfl((int)(ginc - cnt), gs);
+                if (ok) {
+                    const int64_t gr = wb + 4 * gs;
+                    slot = (uint32_t)((int64_t)c.f * d.N + gr * 64 + vl[gr * 64 + (idx - gex)]);
+                    tile_range(d, w.rect[slot], a0, a1, y0, y1);
+                    y0 = max(y0, ry0);
+                    y1 = min(y1, ry1);
+                    ok = y0 <= y1;
+                    if (!QUEUE) load_rec();
+                }
             }
             // the rows whose rectangle columns hold an active tile of the
             // chunk (bit y - y0); a rectangle of more than 64 rows keeps
             // them all
-            const bool tall = ok && y1 - y0 >= 64;
+            bool tall = ok && y1 - y0 >= 64;
             uint64_t rows = 0ull;
             if (ok && !tall)
                 for (int y = y0; y <= y1; ++y)
                     if (next_active(act, ct, y * d.tx - c.t0, a0, a1) <= a1) rows |= 1ull << (y - y0);
+            if constexpr (QUEUE) {
+                const bool has = tall || rows != 0ull;
+                const uint64_t m = ballot(has);
+                if (has) {
+                    const int at = held + __builtin_popcountll(m & below);
+                    pq->rows[at] = rows;
+                    pq->rect[at] = make_short4((short)a0, (short)a1, (short)y0, (short)y1);
+                    pq->slot[at] = slot;
+                }
+                held += __builtin_popcountll(m);
+                if (held < 64 && !last) continue;
+                wave_lds_sync();
+                ok = lane < held;
+                rows = 0ull;
+                a0 = y0 = 0;
+                a1 = y1 = -1;
+                if (ok) {
+                    rows = pq->rows[lane];
+                    const short4 r = pq->rect[lane];
+                    slot = pq->slot[lane];
+                    a0 = r.x;
+                    a1 = r.y;
+                    y0 = r.z;
+                    y1 = r.w;
+                    load_rec();
+                }
+                tall = ok && y1 - y0 >= 64;
+                // the rest (fewer than 64) to the front
+                held = max(held - 64, 0);
+                if (held > 0) {
+                    uint64_t tr = 0ull;
+                    short4 tc = make_short4(0, 0, 0, 0);
+                    uint32_t ts = 0;
+                    if (lane < held) {
+                        tr = pq->rows[64 + lane];
+                        tc = pq->rect[64 + lane];
+                        ts = pq->slot[64 + lane];
+                    }
+                    wave_lds_sync();
+                    if (lane < held) {
+                        pq->rows[lane] = tr;
+                        pq->rect[lane] = tc;
+                        pq->slot[lane] = ts;
+                    }
+                }
+                wave_lds_sync();
+            }
             const int n = tall ? y1 - y0 + 1 : __builtin_popcountll(rows);
             const int incl = wave_incl_scan(n, lane);
             const int excl = incl - n;
@@ -377,9 +445,11 @@ __device__ __forceinline__ void block_pairs(const Dims& d, const WS& w, const Ch
 constexpr int kStageBuf = 128;
 
 // LDS: [chunk] per-tile counters, then the active bits.
+template <bool QUEUE>
 __global__ __launch_bounds__(256) void k_pair_hist(Dims d, WS w) {
     extern __shared__ uint32_t lds[];
     __shared__ uint4 sbuf[4][kStageBuf];
+    __shared__ PairQueue pq[QUEUE ? 4 : 1];
     __shared__ uint32_t sfail;
     const Chunk c = chunk_of_block(d);
     const int ct = c.t1 - c.t0;
@@ -408,7 +478,7 @@ __global__ __launch_bounds__(256) void k_pair_hist(Dims d, WS w) {
         held = 0;
         wave_lds_sync();
     };
-    block_pairs(d, w, c, act, [&](bool emit, int t, unsigned long long key) {
+    block_pairs<QUEUE>(d, w, c, act, pq + (QUEUE ? wv : 0), [&](bool emit, int t, unsigned long long key) {
         const uint64_t m = ballot(emit);
         if (m == 0) return;
         if (emit) {
@@ -953,7 +1023,7 @@ __global__ __launch_bounds__(256) void k_pair_scatter(Dims d, WS w, uint32_t nbb
     load_active(d, w, c, act);
     __syncthreads();
     if (overflow) return;
-    block_pairs(d, w, c, act, [&](bool emit, int t, unsigned long long key) {
+    block_pairs<false>(d, w, c, act, nullptr, [&](bool emit, int t, unsigned long long key) {
         if (emit) {
             uint32_t pos = atomicAdd(&cur[t], 1u);
             w.keys[pos] = key;

@@ -1080,3 +1080,28 @@ def test_queue_heads_serve_repeated_launches(ipp, share, fwd):
             for a, b in zip(got, ref):
                 assert np.array_equal(a, b), k
     print("queue heads", ipp, share, fwd, ref[-2:])
+
+
+@pytest.mark.parametrize("n,cover", [(66000, 0.0003), (66000, 0.3), (140000, 0.002)])
+def test_collected_rows_give_the_same_pairs(n, cover):
+    """Binning ranges of 512 and 768 Gaussians, whose waves collect the
+    Gaussians with an active row: few and many of them, some rectangles of
+    more than 64 tile rows, and rounds of fewer than 64: the oracle's lists."""
+    size = (1142, 767)
+    cam = small_cam(*size, 0.8 * size[0])
+    sc, poses = _two_pose_scene(1, n=n)
+    sc["scale"] *= 0.05
+    sc["scale"][::9001, :2] *= 400.0
+    rng = np.random.default_rng(4)
+    mask = (rng.random((1, size[1], size[0])) < cover).astype(np.uint8)
+    rast = _rast(cam, n, 1, tile_w=8, tile_h=8)
+    ws = rast.new_workspace()
+    rast.project(ws, *dev_params(sc), dev_poses(poses[:1]))
+    rast.bin(ws, dev_mask(mask))
+    st = rast.read_status(ws)
+    assert st["status"] == 0 and st["restaged_blocks"] == 0
+    P = orc.make_params(cam, tile=(8, 8))
+    recs = orc.project(P, sc, poses[:1])
+    _check_pairs(rast, ws, P, recs, mask, 1, n, {"status": st})
+    rect = ws_view(rast, ws, "rect", torch.int16, 4 * n).cpu().numpy().reshape(n, 4)[recs["visible"][0] != 0]
+    assert ((rect[:, 3] // 8 - rect[:, 2] // 8) >= 64).any()
