@@ -491,7 +491,10 @@ size_t rtg_icp_workspace_bytes(const rtg_intrinsics* intr, int32_t levels);
  * the normals' angle is within sin_angle; residual r = (p - q) . n,
  * Jacobian [p x n, n] for the update T <- exp(xi) T; the normal equations
  * are summed in binary64 in a fixed order and solved by Cholesky (no
- * update with fewer than 6 pairs or a non-positive pivot).  trace_out
+ * update with fewer than 6 pairs or a non-positive pivot).  Where the pairs
+ * do not fix all six degrees (one or two planes in view), the last pivots
+ * are rounding noise: the pose then stays or moves far by its sign, the same
+ * on every call with the same inputs; the trace's A shows it.  trace_out
  * (device double[total iterations][48], or NULL): per iteration the pose it
  * used (12), sum r^2, the pair count, A's upper triangle (21, row-major) and
  * b (6).  All on `stream`, no host synchronisation. */

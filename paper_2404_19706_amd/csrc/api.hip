@@ -951,7 +951,7 @@ namespace {
 struct IcpLayout {
     int W[3], H[3];
     size_t off_d[3], off_dm[3], off_nm[3], off_part, total;
-    int nblk0;
+    int rows0;
 };
 
 bool icp_layout(const rtg_intrinsics* intr, int levels, IcpLayout& L) {
@@ -972,9 +972,12 @@ bool icp_layout(const rtg_intrinsics* intr, int levels, IcpLayout& L) {
             o = align256(o + 12 * n);
         }
     }
-    L.nblk0 = (int)grid_for((int64_t)L.W[0] * L.H[0], 256);
+    // two sets of up to 256 partial rows and a pose (at least a row per 256
+    // level-0 pixels, which is more from 131,072 pixels on)
+    const size_t nblk = grid_for((int64_t)L.W[0] * L.H[0], 256);
+    L.rows0 = (int)std::min<size_t>(nblk, 256);
     L.off_part = o;
-    o = align256(o + 8 * (size_t)kIcpTerms * L.nblk0);
+    o = align256(o + 8 * std::max<size_t>(kIcpTerms * nblk, 2 * kIcpTerms * L.rows0 + 12));
     L.total = o;
     return true;
 }
@@ -1033,35 +1036,30 @@ rtg_status rtg_icp(const rtg_intrinsics* intr, const rtg_icp_params* prm, const 
         const int64_t cells = (int64_t)((L.W[1] + 1) / 2) * ((L.H[1] + 1) / 2);
         hipLaunchKernelGGL(k_icp_pyramid, dim3(grid_for(cells, 256)), dim3(256), 0, S(stream), P);
     }
-    // The partial rows take the space of one row per 256 level-0 pixels: two
-    // sets of up to max_rows rows, then one pose; the other place of a pose
-    // is pose_out, the first pass writing the workspace's (pose_out may be
-    // pose_init, which that pass reads).  An image too small for that takes
-    // one workgroup, which may overwrite what it has read.
+    // Two sets of partial rows, then one pose; the other place of a pose is
+    // pose_out, the first pass writing the workspace's (pose_out may be
+    // pose_init, which that pass reads).
     double* part = reinterpret_cast<double*>(b + L.off_part);
-    const int max_rows = std::min(256, std::max(1, (kIcpTerms * L.nblk0 - 12) / (2 * kIcpTerms)));
-    const bool one = max_rows == 1;
-    double* part_of[2] = {part, one ? part : part + (int64_t)max_rows * kIcpTerms};
-    double* pose_of[2] = {one ? pose_out : part + 2 * (int64_t)max_rows * kIcpTerms, pose_out};
+    double* part_of[2] = {part, part + (int64_t)L.rows0 * kIcpTerms};
+    double* pose_of[2] = {part + 2 * (int64_t)L.rows0 * kIcpTerms, pose_out};
     IcpPrev prev{nullptr, 0, pose_init, nullptr};
     int row = 0;
     for (int l = prm->levels - 1; l >= 0; --l) {
         const double s = (double)(1 << l);
         const IcpLevel lv{L.W[l], L.H[l], intr->fx / s, intr->fy / s, intr->cx / s, intr->cy / s, D[l], Dm[l], Nm[l]};
-        // rows of strips of 64 columns, at least one per wave
-        const int strips = (L.W[l] - 1 + 63) / 64;
-        const int64_t units = (int64_t)strips * (L.H[l] - 1), per = kIcpThreads / 64;
-        const int nblk = (int)std::min<int64_t>(max_rows, (units + per - 1) / per);
+        // the blocks that the sums are ordered by; two per workgroup beyond 256
+        const int blocks = (int)std::min<unsigned>(grid_for((int64_t)L.W[l] * L.H[l], 256), 512u);
+        const int rows = std::min(blocks, 256);
         for (int it = 0; it < prm->iters[l]; ++it, ++row) {
             double* Tk = pose_of[row & 1];
             double* pk = part_of[row & 1];
             if (L.W[l] + L.H[l] <= kIcpTable)
-                hipLaunchKernelGGL(k_icp_pass<true>, dim3(nblk), dim3(kIcpThreads), 8 * (size_t)(L.W[l] + L.H[l]),
-                                   S(stream), lv, prev, pose_model, prm->dist, prm->sin_angle, strips, Tk, pk);
+                hipLaunchKernelGGL(k_icp_pass<true>, dim3(rows), dim3(kIcpThreads), 8 * (size_t)(L.W[l] + L.H[l]),
+                                   S(stream), lv, prev, pose_model, prm->dist, prm->sin_angle, blocks, Tk, pk);
             else
-                hipLaunchKernelGGL(k_icp_pass<false>, dim3(nblk), dim3(kIcpThreads), 0, S(stream), lv, prev,
-                                   pose_model, prm->dist, prm->sin_angle, strips, Tk, pk);
-            prev = IcpPrev{pk, nblk, Tk, trace_out ? trace_out + (int64_t)kIcpTrace * row : nullptr};
+                hipLaunchKernelGGL(k_icp_pass<false>, dim3(rows), dim3(kIcpThreads), 0, S(stream), lv, prev,
+                                   pose_model, prm->dist, prm->sin_angle, blocks, Tk, pk);
+            prev = IcpPrev{pk, rows, Tk, trace_out ? trace_out + (int64_t)kIcpTrace * row : nullptr};
         }
     }
     hipLaunchKernelGGL(k_icp_finish, dim3(1), dim3(kIcpThreads), 0, S(stream), prev, pose_out);

@@ -11,6 +11,16 @@
 // equations (A upper triangle, b, r^2, count) in a fixed tree.  A last launch
 // solves for the result, so the whole iteration schedule is enqueued without
 // a host round trip.
+//
+// The order of the sums is part of the result: a view that does not fix all
+// six degrees (one wall fills the image) has a singular system, whose last
+// pivots are rounding noise, and the sign of that noise decides whether the
+// pose moves.  Products and sums are separate operations.  A level's pixels
+// are dealt to B = min(ceil(pixels / 256), 512) blocks of 256 threads, pixel p
+// to thread p mod 256 of block (p / 256) mod B; a thread adds its kept pairs
+// in pixel order; a block's waves add their lanes that differ in bit 5, then 4,
+// 3, 2, 1, 0, and the block (w0 + w1) + (w2 + w3).  The blocks' rows are added
+// by 256 threads, thread s rows s and s + 256, in the same tree.
 #include "rtg_common.h"
 
 namespace rtg {
@@ -174,12 +184,12 @@ __device__ void se3_exp(const double* xi, double* R, double* t) {
     for (int i = 0; i < 3; ++i) t[i] = (Vm[3 * i] * xi[3] + Vm[3 * i + 1] * xi[4]) + Vm[3 * i + 2] * xi[5];
 }
 
-// Reduce-scatter of 32 binary64 values over the wave: every lane returns the
-// wave total of slot icp_slot(lane).  Lane bits 5 and 4 by the permlane
-// swaps (each half keeps its own slot's partial sum after one add), bits 3
-// and 2 by the row mirrors (partners that agree on the bits already reduced),
-// bit 1 within the quads, then the pair sum over bit 0: 31 exchanges
-// where a butterfly per value takes 174 for the 29 terms.
+// Reduce-scatters of 2^m binary64 values over the wave, in the tree of a
+// butterfly that adds lanes differing in bit 5, then 4, 3, 2, 1, 0: while
+// several values are left, each half keeps its own one's partial sum after
+// one add (lane bits 5 and 4 by the permlane swaps, 3 and below by DPP moves).
+// 31 exchanges for 32 values where a butterfly per value takes 174 for the
+// 29 terms; the same additions, so the same bits.
 __device__ __forceinline__ double f64_of(uint32_t lo, uint32_t hi) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
@@ -212,32 +222,54 @@ __device__ __forceinline__ double dpp_mov64(double v) {
     hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, CTRL, 0xf, 0xf, false);
     return f64_of(lo, hi);
 }
-template <int CTRL>
-__device__ __forceinline__ double pair_sum64(double a, double b, bool hi) {
-    const double send = hi ? a : b, keep = hi ? b : a;
-    return keep + dpp_mov64<CTRL>(send);
+// The value of lane ^ 8 (row rotation by 8), ^ 4 (half-row mirror, then the
+// quad reversed), ^ 2 and ^ 1.
+template <int BIT>
+__device__ __forceinline__ double lane_xor64(double v) {
+    if constexpr (BIT == 8) return dpp_mov64<0x128>(v);
+    else if constexpr (BIT == 4) return dpp_mov64<0x1B>(dpp_mov64<0x141>(v));
+    else if constexpr (BIT == 2) return dpp_mov64<0x4E>(v);
+    else return dpp_mov64<0xB1>(v);
 }
+template <int BIT>
+__device__ __forceinline__ double pair_sum64(double a, double b, int lane) {
+    const bool hi = (lane & BIT) != 0;
+    const double send = hi ? a : b, keep = hi ? b : a;
+    return keep + lane_xor64<BIT>(send);
+}
+// Every lane returns the wave total of value icp_slot(lane) of 32.
 __device__ __forceinline__ double reduce_scatter32(double (&t)[32], int lane) {
 #pragma unroll
     for (int j = 0; j < 16; ++j) t[j] = swap32_sum64(t[2 * j], t[2 * j + 1]);
 #pragma unroll
     for (int j = 0; j < 8; ++j) t[j] = swap16_sum64(t[2 * j], t[2 * j + 1]);
-    const bool b3 = (lane >> 3) & 1, b2 = (lane >> 2) & 1, b1 = (lane >> 1) & 1;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) t[j] = pair_sum64<0x140>(t[2 * j], t[2 * j + 1], b3);   // row mirror
+    for (int j = 0; j < 4; ++j) t[j] = pair_sum64<8>(t[2 * j], t[2 * j + 1], lane);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) t[j] = pair_sum64<0x141>(t[2 * j], t[2 * j + 1], b2);   // half-row mirror
-    const double r = pair_sum64<0x4E>(t[0], t[1], b1);                                  // quad [2,3,0,1]
-    return r + dpp_mov64<0xB1>(r);                                                      // quad [1,0,3,2]
+    for (int j = 0; j < 2; ++j) t[j] = pair_sum64<4>(t[2 * j], t[2 * j + 1], lane);
+    const double r = pair_sum64<2>(t[0], t[1], lane);
+    return r + lane_xor64<1>(r);
+}
+// The same of 16: value icp_slot(lane) & 15.
+__device__ __forceinline__ double reduce_scatter16(double (&t)[16], int lane) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t[j] = swap32_sum64(t[2 * j], t[2 * j + 1]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t[j] = swap16_sum64(t[2 * j], t[2 * j + 1]);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) t[j] = pair_sum64<8>(t[2 * j], t[2 * j + 1], lane);
+    double r = pair_sum64<4>(t[0], t[1], lane);
+    r += lane_xor64<2>(r);
+    return r + lane_xor64<1>(r);
 }
 __device__ __forceinline__ int icp_slot(int lane) {
     return ((lane >> 5) & 1) + 2 * ((lane >> 4) & 1) + 4 * ((lane >> 3) & 1) + 8 * ((lane >> 2) & 1) +
            16 * ((lane >> 1) & 1);
 }
 
-// What a pass starts from: the normal equations of the pass before it (as
-// per-workgroup partial rows) and the pose that pass used, or, for the first
-// one (part == nullptr), the initial pose itself.
+// What a pass starts from: the normal equations of the pass before it (partial
+// sums, `rows` (at most 256) per term) and the pose that pass used, or, for the
+// first one (part == nullptr), the initial pose itself.
 struct IcpPrev {
     const double* part;
     int rows;
@@ -246,31 +278,33 @@ struct IcpPrev {
 };
 
 // The pose after the previous pass, into T (LDS) for the whole workgroup of
-// kIcpThreads: the partial rows added in a fixed order (every workgroup
-// gets the same bits), the 6x6 solve by Cholesky (no update with fewer than
-// 6 pairs or a non-positive pivot) and T <- exp(xi) T.  `write`: this workgroup
-// also writes the trace row (pose used, r^2, count, A, b).
-constexpr int kIcpThreads = 768;
+// kIcpThreads: the partial sums added in their fixed order (every workgroup
+// gets the same bits; the first four waves take terms 0-14, the others 15-28),
+// the 6x6 solve by Cholesky (no update with fewer than 6 pairs or a
+// non-positive pivot) and T <- exp(xi) T.  `write`: this workgroup also writes
+// the trace row (pose used, r^2, count, A, b).
+constexpr int kIcpThreads = 512;   // two blocks of 256
+constexpr int kIcpHalf = 15;
 
-__device__ void icp_next_pose(const IcpPrev& v, bool write, double (&red)[kIcpThreads / 64][32], double (&T)[12]) {
+__device__ void icp_next_pose(const IcpPrev& v, bool write, double (&red)[8][32], double (&T)[12]) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     if (!v.part) {
         if (tid < 12) T[tid] = v.T[tid];
         __syncthreads();
         return;
     }
-    // thread (row group tid / 32, term tid % 32)
-    const int k = tid & 31;
-    double s = 0.0;
-    if (k < kIcpTerms)
-        for (int b = tid >> 5; b < v.rows; b += kIcpThreads / 32) s += v.part[(int64_t)b * kIcpTerms + k];
-    s += __shfl_xor(s, 32);
-    if (lane < 32) red[wv][lane] = s;
+    double s[16];
+    const int slot = tid & 255;
+    const double* p = v.part + (int64_t)(wv < 4 ? 0 : kIcpHalf) * v.rows + slot;
+    const int terms = wv < 4 ? kIcpHalf : kIcpTerms - kIcpHalf;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = slot < v.rows && i < terms ? p[i * v.rows] : 0.0;
+    const double sum = reduce_scatter16(s, lane);
+    if ((lane & 3) == 0) red[wv][icp_slot(lane)] = sum;
     __syncthreads();
     if (wv == 0) {
-        double t = 0.0;
-#pragma unroll
-        for (int w = 0; w < kIcpThreads / 64; ++w) t += red[w][lane & 31];
+        const int k = min(lane, kIcpTerms - 1), w = k < kIcpHalf ? 0 : 4, kk = k < kIcpHalf ? k : k - kIcpHalf;
+        const double t = (red[w][kk] + red[w + 1][kk]) + (red[w + 2][kk] + red[w + 3][kk]);
         double tot[kIcpTerms];
 #pragma unroll
         for (int i = 0; i < kIcpTerms; ++i) tot[i] = __shfl(t, i);
@@ -343,7 +377,7 @@ __device__ __forceinline__ double uniform64(double v) {
 
 // Rays of the level's columns and rows, from a table in LDS (TAB) or formed
 // where they are needed.
-constexpr int kIcpTable = 7168;   // entries (56 KB of the 64 KB a workgroup has by default): columns, then rows
+constexpr int kIcpTable = 7168;   // entries (56 KB): columns, then rows
 
 template <bool TAB>
 struct IcpRays {
@@ -372,25 +406,20 @@ struct IcpCand {
 // 19 us, most of it one thread working from scratch memory), then the
 // input pixels' pairs (Eq. 10, projective association) under that estimate
 // T of the input frame's camera-to-world pose against the model rendered at
-// Tm.  The image is cut into strips of 64 columns; numbered strip by strip,
-// the rows of the strips are dealt to the waves in equal contiguous shares,
-// and the lanes take their pixels two at a time, staggered: the depths of
-// the row after next and the model's entries of the next pixel are loaded
-// while the present one is summed (three waves per SIMD, all the 29 binary64
-// sums allow, do not hide those two dependent loads).  The rays come from a
-// table in LDS where image width + height fit it, which takes the binary64
-// divisions per pixel from ten to two; the sums are fused multiply-adds, the
-// decisions keep their unfused sequence.  Bound by binary64 issue (344
-// instructions per pixel); a level-0 pass at 1200x680 takes 19 us, 6 of them
-// the launch and the solve, where a pass and its solve took 18 + 19 us on
-// average over the levels (the whole call 730 to 296 us).  The partial rows of
-// consecutive passes and the poses alternate between two places, so no workgroup
-// overwrites what another still reads.
+// Tm.  Workgroup b holds blocks b and b + 256 of the order above, so that the
+// sum of the two is one of the rows' first additions.  The lanes take their
+// pixels two at a time, staggered: the depths of the pixel after next and the
+// model's entries of the next one are loaded while the present one is summed
+// (two waves per SIMD, all that the order leaves, do not hide those two
+// dependent loads).  The rays come from a table in LDS where image width +
+// height fit it, which takes the binary64 divisions per pixel from ten to two.
+// The partial sums of consecutive passes and the poses alternate between two
+// places, so no workgroup overwrites what another still reads.
 template <bool TAB>
 __global__ __launch_bounds__(kIcpThreads) void k_icp_pass(IcpLevel L, IcpPrev prev, const double* __restrict__ Tm,
-                                                          double dist, double sin_a, int strips,
+                                                          double dist, double sin_a, int blocks,
                                                           double* __restrict__ T_out, double* __restrict__ partials) {
-    __shared__ double red[kIcpThreads / 64][32];
+    __shared__ double red[8][32];
     __shared__ double sT[12];
     extern __shared__ double ray_tab[];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -409,33 +438,40 @@ __global__ __launch_bounds__(kIcpThreads) void k_icp_pass(IcpLevel L, IcpPrev pr
     double t[32];
 #pragma unroll
     for (int k = 0; k < 32; ++k) t[k] = 0.0;
-    // (the last row and column have no forward difference)
-    const int h = L.H - 1;
-    const uint64_t units = (uint64_t)strips * (uint32_t)h, nw = (uint64_t)gridDim.x * (kIcpThreads / 64);
-    const uint64_t wid = (uint64_t)blockIdx.x * (kIcpThreads / 64) + (uint32_t)readfirstlane(wv);
-    const int u0 = (int)(wid * units / nw), u1 = (int)((wid + 1) * units / nw);
-    // pixel of a unit in this lane: its depths are read in advance
+    // this wave's block, its first pixel and its number of pixels per lane
+    const int block = (int)blockIdx.x + (wv < 4 ? 0 : 256), np = L.W * L.H, step = blocks * 256;
+    const int first = readfirstlane(block * 256 + (wv & 3) * 64);
+    const int n = block < blocks && first < np ? (np - 1 - first) / step + 1 : 0;
+    // pixel of the next load: its depths are read in advance (the last row and
+    // column have no forward difference; past the image: nothing)
+    const int sx = step % L.W, sy = step / L.W;
+    int qy = (first + lane) / L.W, qx = first + lane - qy * L.W;
     struct Row {
         float D, Dr, Dd;
         int x, y;
     };
-    auto load_row = [&](int u) {
+    auto load_row = [&]() {
+        const bool in = qx < L.W - 1 && qy < L.H - 1;
         Row r;
-        const int strip = u / h, x = strip * 64 + lane;
-        r.y = u - strip * h;
-        r.x = x;
-        const float* p = L.D + (int64_t)r.y * L.W + (x < L.W - 1 ? x : 0);
-        r.D = x < L.W - 1 ? p[0] : 0.f;
+        r.x = in ? qx : 0;
+        r.y = in ? qy : 0;
+        const float* p = L.D + (r.y * L.W + r.x);
+        r.D = in ? p[0] : 0.f;
         r.Dr = p[1];
         r.Dd = p[L.W];
+        qx += sx;
+        qy += sy;
+        if (qx >= L.W) {
+            qx -= L.W;
+            ++qy;
+        }
         return r;
     };
     auto candidate = [&](const Row& rw) {
         IcpCand c;
         c.ok = rw.D > 0.f && rw.Dr > 0.f && rw.Dd > 0.f;
         const double D = rw.D, Dr = rw.Dr, Dd = rw.Dd;
-        const int x = c.ok ? rw.x : 0;
-        const double rx = rays.x(L, x), rxr = rays.x(L, x + 1), ry = rays.y(L, rw.y), ryd = rays.y(L, rw.y + 1);
+        const double rx = rays.x(L, rw.x), rxr = rays.x(L, rw.x + 1), ry = rays.y(L, rw.y), ryd = rays.y(L, rw.y + 1);
         const double V[3] = {D * rx, D * ry, D};
         const double a[3] = {Dr * rxr - V[0], Dr * ry - V[1], Dr - V[2]};
         const double b[3] = {Dd * rx - V[0], Dd * ryd - V[1], Dd - V[2]};
@@ -479,38 +515,38 @@ __global__ __launch_bounds__(kIcpThreads) void k_icp_pass(IcpLevel L, IcpPrev pr
 #pragma unroll
         for (int i = 0; i < 6; ++i)
 #pragma unroll
-            for (int j = i; j < 6; ++j, ++k) t[k] = __builtin_fma(J[i], J[j], t[k]);
+            for (int j = i; j < 6; ++j, ++k) t[k] += J[i] * J[j];
 #pragma unroll
-        for (int i = 0; i < 6; ++i) t[21 + i] = __builtin_fma(J[i], r, t[21 + i]);
-        t[27] = __builtin_fma(r, r, t[27]);
+        for (int i = 0; i < 6; ++i) t[21 + i] += J[i] * r;
+        t[27] += r * r;
         t[28] += 1.0;
     };
-    if (u0 < u1) {
-        Row rw = load_row(u0);
+    if (n > 0) {
+        Row rw = load_row();
         IcpCand c = candidate(rw);
-        rw = load_row(min(u0 + 1, u1 - 1));
-        for (int u = u0; u < u1; ++u) {
+        rw = load_row();
+        for (int u = 0; u < n; ++u) {
             IcpCand nx = candidate(rw);   // pixel u + 1 (past the end: dropped)
-            rw = load_row(min(u + 2, u1 - 1));
+            rw = load_row();
             add_pair(c);
             c = nx;
         }
     }
-    // fixed-order reduction: the wave's reduce-scatter, then the waves in order
+    // the wave's reduce-scatter, the four waves of each block, the two blocks
+    // (a block or wave without pixels adds zeros)
     const double s = reduce_scatter32(t, lane);
     if ((lane & 1) == 0) red[wv][icp_slot(lane)] = s;
     __syncthreads();
     if (threadIdx.x < kIcpTerms) {
-        double o = 0.0;
-#pragma unroll
-        for (int w = 0; w < kIcpThreads / 64; ++w) o += red[w][threadIdx.x];
-        partials[(int64_t)blockIdx.x * kIcpTerms + threadIdx.x] = o;
+        const int k = threadIdx.x;
+        partials[(int64_t)k * gridDim.x + blockIdx.x] = ((red[0][k] + red[1][k]) + (red[2][k] + red[3][k])) +
+                                                        ((red[4][k] + red[5][k]) + (red[6][k] + red[7][k]));
     }
 }
 
 // The pose after the last pass (one workgroup).
 __global__ __launch_bounds__(kIcpThreads) void k_icp_finish(IcpPrev prev, double* __restrict__ T_out) {
-    __shared__ double red[kIcpThreads / 64][32];
+    __shared__ double red[8][32];
     __shared__ double sT[12];
     icp_next_pose(prev, true, red, sT);
     if (threadIdx.x < 12) T_out[threadIdx.x] = sT[threadIdx.x];

@@ -155,3 +155,134 @@ def test_icp_pass_edges(w, h, levels):
             assert not trace[row, 41:].any()
             row += 1
     assert row == len(trace) and np.isfinite(pose.cpu().numpy()).all()
+
+
+def _plane_maps(cam, pose, planes):
+    """Depth and camera-frame normals of the nearest plane n . x = d."""
+    R, t = pose[:9].reshape(3, 3), pose[9:]
+    y, x = np.mgrid[: cam["height"], : cam["width"]] + 0.5
+    ray = np.stack([(x - cam["cx"]) / cam["fx"], (y - cam["cy"]) / cam["fy"], np.ones_like(x)], -1)
+    D, N = np.full(x.shape, np.inf), np.zeros(ray.shape)
+    for n, d in planes:
+        nc = np.asarray(n, np.float64) @ R
+        with np.errstate(divide="ignore"):
+            z = (d - np.dot(n, t)) / (ray @ nc)
+        near = (z > 0) & (z < D)
+        D[near], N[near] = z[near], nc
+    N[(N * ray).sum(-1) > 0] *= -1
+    return np.where(np.isfinite(D), D, 0).astype(np.float32), N.astype(np.float32)
+
+
+def _halves(v):
+    """The sum over the last axis (64 lanes), lane l and l ^ 32 first."""
+    while v.shape[-1] > 1:
+        o = v.shape[-1] // 2
+        v = v[..., :o] + v[..., o:]
+    return v[..., 0]
+
+
+def _ordered_sums(ok, p, q, n):
+    """The 29 terms of the normal equations in the library's order: pixel i
+    to thread i % 256 of block (i // 256) % B, whose sums run in pixel order;
+    then lanes, waves and blocks in their fixed tree."""
+    r = oicp._dot(p - q, n)
+    J = np.concatenate([oicp._cross(p, n), n], -1)
+    cols = [J[..., i] * J[..., j] for i in range(6) for j in range(i, 6)]
+    cols += [J[..., i] * r for i in range(6)] + [r * r, np.ones_like(r)]
+    px = ok.size
+    B = min(-(-px // 256), 512)
+    rounds = -(-px // (256 * B))
+    t = np.zeros((29, rounds * B * 256))
+    t[:, :px] = [np.where(ok, c, 0.0).ravel() for c in cols]
+    s = np.zeros((29, B, 4, 64))
+    for k in range(rounds):
+        s = s + t.reshape(29, rounds, B, 4, 64)[:, k]
+    w = _halves(s)
+    rows = np.zeros((29, 512))
+    rows[:, :B] = (w[..., 0] + w[..., 1]) + (w[..., 2] + w[..., 3])
+    w = _halves((rows[:, :256] + rows[:, 256:]).reshape(29, 4, 64))
+    return (w[:, 0] + w[:, 1]) + (w[:, 2] + w[:, 3])
+
+
+def _ordered_solve(tot):
+    """xi of the Cholesky solve in its fixed order, or None (no update)."""
+    A = np.zeros((6, 6))
+    A[np.triu_indices(6)] = tot[:21]
+    L = np.zeros((6, 6))
+    if tot[28] < 6:
+        return None
+    for i in range(6):
+        for j in range(i + 1):
+            acc = A[j, i]
+            for m in range(j):
+                acc = acc - L[i, m] * L[j, m]
+            if i == j and not acc > 0.0:
+                return None
+            L[i, j] = np.sqrt(acc) if i == j else acc / L[j, j]
+    y, xi = np.zeros(6), np.zeros(6)
+    for i in range(6):
+        acc = tot[21 + i]
+        for m in range(i):
+            acc = acc - L[i, m] * y[m]
+        y[i] = acc / L[i, i]
+    for i in range(5, -1, -1):
+        acc = y[i]
+        for m in range(i + 1, 6):
+            acc = acc - L[m, i] * xi[m]
+        xi[i] = acc / L[i, i]
+    return -xi
+
+
+@pytest.mark.parametrize("w,h,levels", [(33, 17, 1), (97, 66, 3), (131, 97, 2), (640, 400, 2)])
+@pytest.mark.parametrize("view", ["wall", "slanted", "two planes", "corner"])
+def test_views_that_do_not_fix_the_pose(view, w, h, levels):
+    """Where fewer than three independent normals are in view, the last
+    pivots of the 6x6 system are rounding noise, and whether the pose moves,
+    and where to, follows the order of every sum: the trace holds the sums of
+    the stated order bit for bit, and each pose is the one before it, bit for
+    bit, where that order refuses a pivot, else exp(xi) of it.  Tolerance of
+    the latter: a library's sin and cos within a unit in the last place each,
+    through 1 - cos over th^2, a dozen roundings beside."""
+    from paper_2404_19706_amd import tracking
+    cam = small_cam(w, h, 0.9 * w)
+    pose_m = np.concatenate([np.eye(3).ravel(), [0.1, 0.2, 0.0]])
+    planes = {"wall": [((0, 0, 1), 2.0)], "slanted": [((0.3, -0.2, 1.0), 2.0)],
+              "two planes": [((0, 0, 1), 2.0), ((0, 1, 0.2), 0.9)],
+              "corner": [((0, 0, 1), 2.0), ((0, 1, 0.2), 0.7), ((1, 0, 0.3), 0.8)]}[view]
+    rng = np.random.default_rng(w)
+    Dm, Nm = _plane_maps(cam, pose_m, planes)
+    Din, _ = _plane_maps(cam, _motion(pose_m, [0.004, -0.003, 0.002, 0.006, -0.005, 0.004]), planes)
+    Din = Din * (1 + 0.002 * rng.standard_normal(Din.shape)) * (rng.random(Din.shape) > 0.03)
+    Din = Din.astype(np.float32)
+    iters = (4, 3, 2)
+    pose, trace = tracking.icp(cam, _t(Din), _t(Dm), _t(Nm), _t(pose_m), _t(pose_m),
+                               tracking.icp_params(levels, iters), trace=True)
+    torch.cuda.synchronize()
+    pose, trace = pose.cpu().numpy(), trace.cpu().numpy()
+    lv = oicp.levels_of(cam, Din, Dm, Nm, levels)
+    eps = np.finfo(np.float64).eps
+    row, moved = 0, 0
+    for l in range(levels - 1, -1, -1):
+        lin, lmo, K = lv[l]
+        for _ in range(iters[l]):
+            T = trace[row, :12]
+            with np.errstate(all="ignore"):
+                tot = _ordered_sums(*oicp.associate(lin, lmo, K, T, pose_m, 0.1, 0.3420201433256687))
+                xi = _ordered_solve(tot)
+            assert np.array_equal(trace[row, 14:41], tot[:27]) and np.array_equal(trace[row, 12:14], tot[27:]), row
+            row += 1
+            got = trace[row, :12] if row < len(trace) else pose
+            if xi is None:
+                assert np.array_equal(got, T), row
+                continue
+            moved += 1
+            th = np.sqrt((xi[0] * xi[0] + xi[1] * xi[1]) + xi[2] * xi[2])
+            W = np.array([[0, -xi[2], xi[1]], [xi[2], 0, -xi[0]], [-xi[1], xi[0], 0]])
+            a, b, c = np.sin(th) / th, (1 - np.cos(th)) / (th * th), (th - np.sin(th)) / (th * th * th)
+            R, V = np.eye(3) + a * W + b * (W @ W), np.eye(3) + b * W + c * (W @ W)
+            R0, t0 = T[:9].reshape(3, 3), T[9:]
+            ref = np.concatenate([(R @ R0).ravel(), R @ t0 + V @ xi[3:]])
+            lim = 32 * eps * (1 + np.abs(T[9:]).max() + np.abs(xi[3:]).max() * (1 + 1 / th))
+            assert np.abs(got - ref).max() <= lim, (row, np.abs(got - ref).max(), lim)
+    print(view, (w, h), "updates", moved, "of", row, "moved %.3g" % np.abs(pose - pose_m).max())
+    assert row == len(trace)
