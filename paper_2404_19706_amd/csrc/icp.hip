@@ -544,8 +544,9 @@ __global__ __launch_bounds__(kIcpThreads) void k_icp_pass(IcpLevel L, IcpPrev pr
     }
 }
 
-// The pose after the last pass (one workgroup).
-__global__ __launch_bounds__(kIcpThreads) void k_icp_finish(IcpPrev prev, double* __restrict__ T_out) {
+// The pose after the last pass (one workgroup; T_out may be the place of the
+// pose that the pass used).
+__global__ __launch_bounds__(kIcpThreads) void k_icp_finish(IcpPrev prev, double* T_out) {
     __shared__ double red[8][32];
     __shared__ double sT[12];
     icp_next_pose(prev, true, red, sT);
