@@ -367,7 +367,10 @@ __device__ __forceinline__ float eval_f_precise(const float4& A, float alpha, co
 // One wave's compacted batch in LDS: {mu.x, mu.y, Q.xx, 2 Q.xy}, {Q.yy,
 // alpha', hit bound, c.r}, {c.g, c.b, e0, e1} per surviving record in list
 // order, then kPad records whose d^2 is NaN at every pixel (no comparison
-// holds), so that the passes work in whole groups.
+// holds), so that the passes work in whole groups.  In the alpha-blended depth
+// mode they carry the index of a record of the list: the depth that the passes
+// read by it, with weight zero, must be a number, and the word of a Gaussian
+// that the frame does not see is never written.
 constexpr int kPad = 3;
 struct Slice {
     float4 r[3][64 + kPad];
@@ -377,7 +380,7 @@ struct Slice {
 
 // Pack-cull the batch and compact the survivors into the wave's slice;
 // returns the lanes that hold one.
-template <bool BWD>
+template <bool BWD, int DM>
 __device__ __forceinline__ uint64_t compact_batch(const Batch& B, uint32_t j0, Slice& S, int lane, const PackBox& pb,
                                                   float cut) {
     const bool keep = B.ok && pack_keeps(B.r0, B.r1.x, pb, cut);
@@ -392,11 +395,13 @@ __device__ __forceinline__ uint64_t compact_batch(const Batch& B, uint32_t j0, S
         S.pos[q] = BWD ? __float_as_uint(B.r2.w) : j0 + (uint32_t)lane;
         S.gid[q] = __float_as_uint(B.r2.z);
     }
+    // (lane 0 holds a record of the list, kept or not)
+    const uint32_t listed = DM == 1 ? rdl_u(__float_as_uint(B.r2.z), 0) & kGidMask : 0u;
     if (lane < kPad) {
         S.r[0][n + lane] = make_float4(__builtin_nanf(""), 0.f, 1.f, 0.f);
         S.r[1][n + lane] = make_float4(0.f, 0.f, -1.f, 0.f);
         S.r[2][n + lane] = make_float4(0.f, 0.f, 0.f, 0.f);
-        S.gid[n + lane] = 0u;
+        S.gid[n + lane] = listed;
     }
     return m;
 }
@@ -434,7 +439,7 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
         const float* zf = w.zkey + (int64_t)readfirstlane(p.f) * d.N;
         for (uint32_t b = p.rs; b < p.re; b += 64) {
             const bool prec = B.ok && rec_precise(B.r2);
-            const uint64_t kept = compact_batch<false>(B, b, S, lane, pb, cut);
+            const uint64_t kept = compact_batch<false, DM>(B, b, S, lane, pb, cut);
             const uint32_t nb = (uint32_t)__builtin_popcountll(kept);
             const bool anyp = (ballot(prec) & kept) != 0;
             wave_lds_sync();
@@ -813,7 +818,7 @@ __global__ RTG_BWD_BOUNDS void k_raster_bwd(Dims d, WS w, const float* __restric
                 pb = pack_box(p, lim != 0u);
                 boxed = open;
             }
-            const uint64_t kept = compact_batch<true>(B, b0, S, lane, pb, cut);
+            const uint64_t kept = compact_batch<true, DM>(B, b0, S, lane, pb, cut);
             const int nk = __builtin_popcountll(kept);
             const int kl = __builtin_popcountll(lim >= 64u ? kept : kept & ((1ull << lim) - 1ull));
             wave_lds_sync();

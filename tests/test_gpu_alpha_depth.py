@@ -10,8 +10,8 @@ import torch
 from oracle import alpha_depth as ad
 from oracle import oracle as orc
 from rtg_synth import random_upstream
-from tests.gpu_helpers import (GRAD_GAMMA, PRECISE_KAPPA, T_EPS, assert_parity, compare_forward,
-                               dev_poses, err_stats, fmt_stats, gpu_forward, grad_stats, need_gpu)
+from tests.gpu_helpers import (GRAD_GAMMA, PRECISE_KAPPA, T_EPS, assert_parity, compare_forward, dev_mask,
+                               dev_params, dev_poses, err_stats, fmt_stats, gpu_forward, grad_stats, need_gpu)
 from tests.scenes_small import random_pose, random_scene, small_cam
 
 pytestmark = pytest.mark.gpu
@@ -109,4 +109,45 @@ def test_alpha_depth_l1_step_through_the_separate_calls():
     ref, bnd = ad.backward(P, recs, sc, poses, pix, gC, gD, bound=(GRAD_GAMMA, T_EPS, PRECISE_KAPPA))
     errs = grad_stats(grads, ref, sc["unstable"], bnd)
     print("alpha-blended depth, L1 step", fmt_stats(errs))
+    assert_parity(errs)
+
+
+@pytest.mark.parametrize("tile", [(16, 16), (8, 8), (32, 8)])
+def test_hidden_gaussians_leave_nothing_in_the_blended_depth(tile):
+    """Words that no call has written (Gaussian 0 is behind both cameras, the
+    workspace full of NaN bit patterns beforehand): the depth and the
+    gradients are those of the oracle, whatever the length of a batch."""
+    from paper_2404_19706_amd import Rasterizer
+    cam = small_cam(100, 75, 90.0)
+    sc, poses = _scene(84 + tile[0], n=700)
+    sc["pos"][0] = poses[0, 9:] - 5.0 * poses[0, :9].reshape(3, 3)[:, 2]
+    F, N = poses.shape[0], len(sc["pos"])
+    mask = (np.random.default_rng(85).random((F, 75, 100)) < 0.5).astype(np.uint8)
+    rast = Rasterizer(cam, N, F, tile_w=tile[0], tile_h=tile[1], depth_mode=1)
+    params, dp = dev_params(sc), dev_poses(poses)
+    ws = rast.new_workspace()
+    ws.fill_(255)
+    rast.project(ws, *params, dp)
+    rast.bin(ws, dev_mask(mask))
+    out = rast.alloc_outputs()
+    rast.render_into(ws, *out)
+    gC, gD = random_upstream(mask, seed=86)
+    grads = rast.alloc_grads()
+    rast.backward_into(ws, params, dp, *out[1:], torch.as_tensor(gC).cuda(), torch.as_tensor(gD).cuda(), grads)
+    torch.cuda.synchronize()
+    P = orc.make_params(cam, tile=tile)
+    recs = orc.project(P, sc, poses)
+    assert not recs["visible"][:, 0].any()
+    pix = orc.masked_pixels(mask)
+    f, x, y = pix[:, 0], pix[:, 1], pix[:, 2]
+    ref = ad.render(P, recs, sc, pix)
+    g = dict(zip(("color", "depth", "trans", "index"), (t.cpu().numpy() for t in out)))
+    errs = compare_forward(g, pix, ref)
+    zmax = float(recs["pc"][..., 2][recs["visible"] != 0].max())
+    errs["depth"] = err_stats(g["depth"][f, y, x], ref["depth"], floor=2e4 * T_EPS * zmax)
+    gref, bnd = ad.backward(P, recs, sc, poses, pix, gC[f, y, x], gD[f, y, x],
+                            bound=(GRAD_GAMMA, T_EPS, PRECISE_KAPPA))
+    errs.update(grad_stats(grads, gref, sc["unstable"], bnd))
+    print("blended depth beside hidden Gaussians", tile, fmt_stats(errs))
+    assert errs["index_mismatch"] == 0
     assert_parity(errs)
