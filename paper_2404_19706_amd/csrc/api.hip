@@ -300,8 +300,10 @@ rtg_status rtg_plan_create(const rtg_config* cfg, const rtg_intrinsics* intr, in
         }
         // small problems: halve the ranges (down to 256) while the count
         // matrix stays within 2^21 entries, so more workgroups share the
-        // latency-bound enumeration
-        while (gpb > 256 && (int64_t)frames * 2 * nb * d.ntiles <= (int64_t(1) << 21)) {
+        // latency-bound enumeration, and while the half is a whole number of
+        // the groups of 64 Gaussians that the enumeration counts in (1,280
+        // ends at 320: with 160 the last 32 of every range had no pairs)
+        while (gpb > 256 && gpb % 128 == 0 && (int64_t)frames * 2 * nb * d.ntiles <= (int64_t(1) << 21)) {
             gpb /= 2;
             nb = (n + gpb - 1) / gpb;
         }

@@ -1105,3 +1105,27 @@ def test_collected_rows_give_the_same_pairs(n, cover):
     _check_pairs(rast, ws, P, recs, mask, 1, n, {"status": st})
     rect = ws_view(rast, ws, "rect", torch.int16, 4 * n).cpu().numpy().reshape(n, 4)[recs["visible"][0] != 0]
     assert ((rect[:, 3] // 8 - rect[:, 2] // 8) >= 64).any()
+
+
+@pytest.mark.parametrize("n,frames,size,tile", [
+    (262_145, 1, (128, 96), 16), (321_587, 1, (128, 96), 16), (393_217, 1, (64, 48), 16), (458_752, 1, (61, 43), 16),
+    (567_209, 2, (144, 96), 16), (589_825, 1, (200, 150), 8)])
+def test_every_gaussian_of_a_binning_range_is_listed(n, frames, size, tile):
+    """Ranges of an odd multiple of 256 Gaussians, halved as often as a small
+    image lets them be: the oracle's lists, with the Gaussians in view spread
+    over the whole set."""
+    cam = small_cam(*size, 0.9 * size[0])
+    rng = np.random.default_rng(n)
+    sc = random_scene(rng, n, spread=0.8, smin=0.002, smax=0.02, unstable_frac=0.5)
+    sc["pos"][rng.random(n) > 0.02, 2] = -3.0      # behind the camera
+    poses = np.repeat(identity_pose(), frames, 0)
+    poses[:, 9] += 0.05 * np.arange(frames)
+    mask = (rng.random((frames, size[1], size[0])) < 0.7).astype(np.uint8)
+    rast = _rast(cam, n, frames, tile_w=tile, tile_h=tile, max_pairs=1 << 20)
+    ws = rast.new_workspace()
+    rast.project(ws, *dev_params(sc), dev_poses(poses))
+    rast.bin(ws, dev_mask(mask))
+    st = rast.read_status(ws)
+    assert st["status"] == 0 and st["pairs"] > 1000
+    P = orc.make_params(cam, tile=(tile, tile))
+    _check_pairs(rast, ws, P, orc.project(P, sc, poses), mask, frames, n, {"status": st})

@@ -196,11 +196,7 @@ def test_sh_rows_of_added_gaussians():
     assert (got[:, 1:, :] == 0).all()
 
 
-@pytest.mark.parametrize("n,deg", [
-    (1, 1), (255, 3), (257, 2), (150_000, 3), (330_000, 1),
-    pytest.param(270_000, 1, marks=pytest.mark.xfail(strict=True, reason=(
-        "known defect of rtg_plan_create, older than this test: halving binning ranges of 1,280 Gaussians gives 160, "
-        "not a multiple of the 64 the enumeration counts in, and a fifth of the Gaussians get no pairs")))])
+@pytest.mark.parametrize("n,deg", [(1, 1), (255, 3), (257, 2), (150_000, 3), (330_000, 1), (270_000, 1)])
 def test_sh_backward_ranges(n, deg):
     """Workgroup ranges of 256 and more Gaussians, few of them in view: the
     gradients of those in view are those of a scene of them alone (float
