@@ -125,8 +125,8 @@ rtg_status dev_info(DevInfo& out) {
         int cus = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
             return RTG_E_UNSUPPORTED;
-        const void* kf[2] = {reinterpret_cast<const void*>(k_raster_fwd<0>),
-                             reinterpret_cast<const void*>(k_raster_fwd<1>)};
+        const void* kf[2] = {reinterpret_cast<const void*>(k_raster_fwd<0, false>),
+                             reinterpret_cast<const void*>(k_raster_fwd<1, false>)};
         const void* kb[2] = {reinterpret_cast<const void*>(k_raster_bwd<0>),
                              reinterpret_cast<const void*>(k_raster_bwd<1>)};
         for (int m = 0; m < 2; ++m) {
@@ -538,12 +538,10 @@ rtg_status rtg_render(const rtg_plan* p, void* ws, float* color, float* depth, f
     rtg_status st = dev_info(di);
     if (st != RTG_OK) return st;
     WS w = make_ws(p, ws);
-    if (p->d.depth_mode == 0)
-        hipLaunchKernelGGL(k_raster_fwd<0>, dim3(di.fwd_blocks[0]), dim3(256), 0, S(stream), p->d, w, color, depth,
-                           trans, index);
-    else
-        hipLaunchKernelGGL(k_raster_fwd<1>, dim3(di.fwd_blocks[1]), dim3(256), 0, S(stream), p->d, w, color, depth,
-                           trans, index);
+    const int dm = p->d.depth_mode;
+    const auto k = p->d.t_eps > 1.f ? (dm == 0 ? k_raster_fwd<0, true> : k_raster_fwd<1, true>)
+                                    : (dm == 0 ? k_raster_fwd<0, false> : k_raster_fwd<1, false>);
+    hipLaunchKernelGGL(k, dim3(di.fwd_blocks[dm]), dim3(256), 0, S(stream), p->d, w, color, depth, trans, index);
     return launched();
 }
 

@@ -409,8 +409,10 @@ __device__ __forceinline__ uint64_t compact_batch(const Batch& B, uint32_t j0, S
 // DM = 0: the depth of Eq. 4-5 (first hit, disc plane or centre); DM = 1:
 // the alpha-blended depth sum_i z_i f_i T_i of the depth-rendering ablation
 // (z_i the record's binary32 camera depth, -1 where nothing blends), with
-// the index map still by the first hit.
-template <int DM>
+// the index map still by the first hit.  ONCE: for a threshold t_eps above 1,
+// where a pixel blends the first record that reaches it and stops, whatever its
+// transmission then is (a variant, since the test costs the others registers).
+template <int DM, bool ONCE>
 __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ out_c,
                                                  float* __restrict__ out_d, float* __restrict__ out_t,
                                                  int* __restrict__ out_i) {
@@ -477,7 +479,11 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
                     const float T0 = T;
 #pragma unroll
                     for (int u = 0; u < G; ++u) {
-                        const bool take = ddq[u] <= cut && !(T < teps);
+                        bool take = ddq[u] <= cut && !(T < teps);
+                        if constexpr (ONCE) {
+                            take = ddq[u] <= cut && p.act && last == p.re && lastk < 0;
+                            if (take) lastk = (int)(k0 + u);
+                        }
                         const float fv = take ? fvq[u] : 0.f;
                         const float wgt = fv * T;
                         C0 = __builtin_fmaf(Bq[u].w, wgt, C0);
@@ -514,7 +520,9 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
                 }
                 return false;
             };
-            const bool all_done = anyp ? groups(std::true_type{}) : groups(std::false_type{});
+            bool all_done;
+            if constexpr (ONCE) all_done = groups(std::true_type{});
+            else all_done = anyp ? groups(std::true_type{}) : groups(std::false_type{});
             // list positions of this batch's last blend and depth hit, and the
             // hit's normal and plane offset, before the slice is reused
             if (lastk >= 0) {

@@ -1129,3 +1129,45 @@ def test_every_gaussian_of_a_binning_range_is_listed(n, frames, size, tile):
     assert st["status"] == 0 and st["pairs"] > 1000
     P = orc.make_params(cam, tile=(tile, tile))
     _check_pairs(rast, ws, P, orc.project(P, sc, poses), mask, frames, n, {"status": st})
+
+
+@pytest.mark.parametrize("flat,t_eps", [(0.0, 1.5), (0.0, float("inf")), (1e-6, 1.5)])
+def test_threshold_above_one_blends_one_gaussian(flat, t_eps):
+    """A transmission threshold above 1: a pixel blends the first Gaussian
+    of its list that reaches it and stops, whatever that one's opacity; the
+    depth and the index still come from the first hit.  Where every opacity
+    counts, the outputs are those of the threshold 1, at which any blend ends
+    a pixel; with a Gaussian of opacity zero in front of everything, no
+    colour is left."""
+    cam = small_cam(100, 75, 90.0)
+    sc, poses = _two_pose_scene(51, n=3000)
+    if flat:
+        sc["scale"][:, 2] = flat                   # needle footprints among them
+    rng = np.random.default_rng(52)
+    mask = (rng.random((2, 75, 100)) < 0.6).astype(np.uint8)
+    runs = []
+    for e in (1.0, t_eps):
+        rast = _rast(cam, 3000, 2, t_eps=e)
+        g = gpu_forward(rast, sc, poses, mask)
+        gC, gD = random_upstream(mask, seed=53)
+        grads = rast.alloc_grads()
+        rast.backward_into(g["ws"], g["params"], dev_poses(poses), *g["tensors"][1:], torch.as_tensor(gC).cuda(),
+                           torch.as_tensor(gD).cuda(), grads)
+        torch.cuda.synchronize()
+        runs.append((g, {k: v.cpu().numpy() for k, v in grads.items()}))
+    (g0, a), (g1, b) = runs
+    assert g1["status"]["blend_fwd"] == g0["status"]["blend_fwd"] > 0
+    for k in ("color", "depth", "trans", "index"):
+        assert np.array_equal(g0[k].view(np.uint32), g1[k].view(np.uint32)), k
+    for k in a:
+        assert np.linalg.norm(a[k] - b[k]) <= 1e-5 * np.linalg.norm(a[k]), k
+    # an invisible disc over everything, 0.3 m ahead of the first camera
+    n = poses[0, :9].reshape(3, 3)[:, 2]
+    front = {k: np.concatenate([v[:1], v]) for k, v in sc.items()}
+    front["pos"][0], front["scale"][0], front["opacity"][0] = poses[0, 9:] + 0.3 * n, 2.0, 0.0
+    g2 = gpu_forward(_rast(cam, 3001, 2, t_eps=t_eps), front, poses, mask)
+    ref = gpu_forward(_rast(cam, 3001, 2), front, poses, mask)
+    on = mask[0] != 0
+    assert not g2["color"][0].any() and (g2["trans"][0] == 1).all()
+    assert np.array_equal(g2["index"], ref["index"]) and np.array_equal(g2["depth"], ref["depth"])
+    assert (ref["color"][0][on] > 0).any() and g2["status"]["blend_fwd"] >= on.sum()
