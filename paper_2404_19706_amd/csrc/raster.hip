@@ -431,7 +431,7 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
         // a pixel is done with its colour once T < t_eps; lanes without one
         // start there
         float T = p.act ? 1.f : -1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, Da = 0.f;
-        uint32_t last = p.re, hitpos = 0;
+        uint32_t last = p.rs, hitpos = 0;
         int hitk = -1, lastk = -1;
         bool ddone = !p.act, blended = false;
         Batch B = {};
@@ -462,7 +462,7 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
                         Cc[u] = S.r[2][k0 + u];
                     }
                     // independent part: decision, value, opacity
-                    float fvq[G], ddq[G], Tn[G];
+                    float fvq[G], ddq[G];
 #pragma unroll
                     for (int u = 0; u < G; ++u) {
                         float dx, dy;
@@ -476,14 +476,11 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
                         }
                     }
                     // sequential part: compositing in list order
-                    const float T0 = T;
 #pragma unroll
                     for (int u = 0; u < G; ++u) {
                         bool take = ddq[u] <= cut && !(T < teps);
-                        if constexpr (ONCE) {
-                            take = ddq[u] <= cut && p.act && last == p.re && lastk < 0;
-                            if (take) lastk = (int)(k0 + u);
-                        }
+                        if constexpr (ONCE) take = ddq[u] <= cut && p.act && last == p.rs && lastk < 0;
+                        lastk = take ? (int)(k0 + u) : lastk;
                         const float fv = take ? fvq[u] : 0.f;
                         const float wgt = fv * T;
                         C0 = __builtin_fmaf(Bq[u].w, wgt, C0);
@@ -496,16 +493,9 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
                             blended = blended || take;
                         }
                         T = __builtin_fmaf(-fv, T, T);
-                        Tn[u] = T;
                         cnt_blend += (unsigned long long)__builtin_popcountll(ballot(take));
                     }
-                    // (uniform branches: a pixel's colour ends and its depth
-                    // hit comes once)
-                    if (ballot(!(T0 < teps) && T < teps) != 0) {
-#pragma unroll
-                        for (int u = G - 1; u >= 0; --u)
-                            if (!(T0 < teps) && Tn[u] < teps) lastk = (int)(k0 + u);
-                    }
+                    // (a uniform branch: a pixel's depth hit comes once)
                     bool h = false;
 #pragma unroll
                     for (int u = 0; u < G; ++u) h = h || ddq[u] < Bq[u].z;
@@ -542,7 +532,8 @@ __global__ RTG_FWD_BOUNDS void k_raster_fwd(Dims d, WS w, float* __restrict__ ou
                 boxed = live;
             }
         }
-        cnt_eval += p.act ? (float)(max(last, hitpos ? hitpos : p.re) - p.rs) : 0.f;
+        const uint32_t cterm = T < teps ? last : p.re;
+        cnt_eval += p.act ? (float)(max(cterm, hitpos ? hitpos : p.re) - p.rs) : 0.f;
         if (p.act) {
             size_t pix = ((size_t)p.f * d.H + p.py) * d.W + p.px;
             out_c[3 * pix + 0] = C0;

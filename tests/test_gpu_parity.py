@@ -12,7 +12,7 @@ from rtg_synth import make_config, random_upstream
 from tests.gpu_helpers import (assert_parity, compare_forward, dev_mask, dev_params, dev_poses, fmt_stats,
                                gpu_forward, grad_stats, need_gpu, oracle_forward, oracle_grads, rel_err, ws_view)
 from tests.scenes_small import (edge_on_surfels, footprint_condition, identity_pose, random_pose, random_scene,
-                                small_cam)
+                                small_cam, scene_from)
 
 pytestmark = pytest.mark.gpu
 
@@ -1171,3 +1171,34 @@ def test_threshold_above_one_blends_one_gaussian(flat, t_eps):
     assert not g2["color"][0].any() and (g2["trans"][0] == 1).all()
     assert np.array_equal(g2["index"], ref["index"]) and np.array_equal(g2["depth"], ref["depth"])
     assert (ref["color"][0][on] > 0).any() and g2["status"]["blend_fwd"] >= on.sum()
+
+
+def _two_sided_tile(k):
+    """One 16x16 tile: a Gaussian on the left in front of k on the right,
+    none of which reaches the other side."""
+    cam = small_cam(16, 16, 20.0)
+    x, z = np.full(k + 1, 0.5), 2.0 + 0.01 * np.arange(k + 1)
+    x[0] = -0.5
+    pos = np.stack([x * z / 2.0, np.full(k + 1, 0.05), z], 1)
+    sc = scene_from(pos, np.full((k + 1, 3), 0.05), np.tile([1.0, 0, 0, 0], (k + 1, 1)), np.full(k + 1, 0.05),
+                    np.full((k + 1, 3), 0.5))
+    return cam, sc
+
+
+@pytest.mark.parametrize("k", [1, 63, 64, 200])
+def test_walk_counter_ends_at_the_last_blend(k):
+    """A pixel walks back from the last Gaussian it blended, wherever its
+    list ends: one entry for the pixel on the left, all k + 1 for the one on
+    the right."""
+    cam, sc = _two_sided_tile(k)
+    mask = np.zeros((1, 16, 16), np.uint8)
+    mask[0, 8, 3] = mask[0, 8, 12] = 1
+    rast = _rast(cam, k + 1)
+    params, dp = dev_params(sc), dev_poses(identity_pose())
+    C, D, T, I, ws = rast.forward(params, dp, dev_mask(mask))
+    up = torch.ones_like(C), torch.ones_like(D)
+    rast.backward_into(ws, params, dp, D, T, I, *up, rast.alloc_grads())
+    st = rast.read_status(ws)
+    assert st["pairs"] == k + 1 and st["eval_fwd"] == 2 * (k + 1)
+    assert st["blend_fwd"] == st["part_bwd"] == k + 1
+    assert st["walk_bwd"] == 1 + (k + 1)
