@@ -70,9 +70,9 @@ WS make_ws(const rtg_plan* p, void* base) {
     w.prec = reinterpret_cast<float4*>(b + p->off[O_PREC]);
     w.recp = reinterpret_cast<float*>(b + p->off[O_RECP]);
     w.stagec = reinterpret_cast<uint32_t*>(b + p->off[O_STAGEC]);
-    // (the fourth row of work counters is not written: a backward's
-    // contributions are the blends of its forward)
-    w.bfail = p->few_blocks ? reinterpret_cast<uint32_t*>(w.wcount + 3 * (size_t)kMaxWaves) : w.stagec + 256;
+    // (a row of L1 sums has a word per workgroup of a backward, of which there
+    // are at most kMaxWaves / 4)
+    w.bfail = p->few_blocks ? reinterpret_cast<uint32_t*>(w.lwave + kMaxWaves / 2) : w.stagec + 256;
     w.vcnt = reinterpret_cast<uint32_t*>(b + p->off[O_VCNT]);
     w.vlist = reinterpret_cast<uint8_t*>(b + p->off[O_VLIST]);
     w.chunk = reinterpret_cast<unsigned long long*>(b + p->off[O_CHUNK]);

@@ -66,16 +66,17 @@ __global__ void k_status_out(WS w, int32_t* out) {
 // Sums of the per-wave work counters of the last render and backward
 // launches, and the count of the last binning's blocks that fell back to a
 // second enumeration (nbb blocks), into the header (one workgroup; no
-// host-side reduction).  A record takes part in a pixel's backward exactly
-// where the forward blended it, so the contributions of a backward launch are
-// the blends of the render it followed.
+// host-side reduction).  The contributions of a backward launch are the blends
+// of the render it followed.
 __global__ __launch_bounds__(1024) void k_sum_counters(WS w, uint32_t nbb) {
-    __shared__ unsigned long long part[3][16];
+    __shared__ unsigned long long part[4][16];
     __shared__ uint32_t nfail[16];
-    const uint32_t nw[2] = {min(w.hdr->fwd_waves, (uint32_t)kMaxWaves), min(w.hdr->bwd_waves, (uint32_t)kMaxWaves)};
-    for (int c = 0; c < 3; ++c) {
+    const uint32_t fw = min(w.hdr->fwd_waves, (uint32_t)kMaxWaves), bw = min(w.hdr->bwd_waves, (uint32_t)kMaxWaves);
+    const uint32_t rb = w.hdr->blend_row, rp = w.hdr->part_row;
+    const uint32_t row[4] = {0u, rb, 2u, rp}, nw[4] = {fw, rb ? fw : 0u, bw, rp ? fw : 0u};
+    for (int c = 0; c < 4; ++c) {
         unsigned long long v = 0;
-        for (uint32_t k = threadIdx.x; k < nw[c / 2]; k += blockDim.x) v += w.wcount[(size_t)c * kMaxWaves + k];
+        for (uint32_t k = threadIdx.x; k < nw[c]; k += blockDim.x) v += w.wcount[(size_t)row[c] * kMaxWaves + k];
         for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
         if ((threadIdx.x & 63) == 0) part[c][threadIdx.x >> 6] = v;
     }
@@ -87,10 +88,9 @@ __global__ __launch_bounds__(1024) void k_sum_counters(WS w, uint32_t nbb) {
     }
     __syncthreads();
     if (threadIdx.x < 4) {
-        const int c = threadIdx.x < 3 ? (int)threadIdx.x : 1;
         unsigned long long t = 0;
-        for (int k = 0; k < 16; ++k) t += part[c][k];
-        w.hdr->sums[threadIdx.x] = threadIdx.x < 3 || nw[1] ? t : 0ull;
+        for (int k = 0; k < 16; ++k) t += part[threadIdx.x][k];
+        w.hdr->sums[threadIdx.x] = t;
     }
     if (threadIdx.x == 4) {
         uint32_t t = 0;

@@ -59,7 +59,9 @@ struct Hdr {
     uint32_t fwd_waves, bwd_waves;   // waves of the last render / backward launch
     uint32_t n_restaged;             // binning blocks whose staging overflowed (rtg_read_status)
     uint32_t n_alloc;                // pairs claimed by k_tile_gather (0 outside a binning)
-    uint32_t pad2[4];
+    uint32_t blend_row, part_row;    // rows of wcount with the last render's blends and those the last backward
+                                     // followed (1 or 3; 0: none)
+    uint32_t pad2[2];
     unsigned long long sums[4];      // per-wave work counters summed (rtg_read_status)
 };
 static_assert(sizeof(Hdr) == 128, "header layout");

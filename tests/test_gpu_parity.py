@@ -1202,3 +1202,27 @@ def test_walk_counter_ends_at_the_last_blend(k):
     assert st["pairs"] == k + 1 and st["eval_fwd"] == 2 * (k + 1)
     assert st["blend_fwd"] == st["part_bwd"] == k + 1
     assert st["walk_bwd"] == 1 + (k + 1)
+
+
+@pytest.mark.parametrize("kw", [{}, dict(items_per_pop=2, static_share=50), dict(depth_mode=1)])
+def test_contribution_counter_is_the_last_backwards(kw):
+    """A render after the backward, on another binning, moves the blend
+    counter and leaves the backward's contributions and walk; a new
+    projection clears them."""
+    cam = small_cam(100, 75, 90.0)
+    sc, poses = _two_pose_scene(61, n=900)
+    rng = np.random.default_rng(62)
+    masks = [dev_mask((rng.random((2, 75, 100)) < c).astype(np.uint8)) for c in (0.7, 0.2)]
+    rast = _rast(cam, 900, 2, **kw)
+    params, dp = dev_params(sc), dev_poses(poses)
+    C, D, T, I, ws = rast.forward(params, dp, masks[0])
+    rast.backward_into(ws, params, dp, D, T, I, torch.ones_like(C), torch.ones_like(D), rast.alloc_grads())
+    a = rast.read_status(ws)
+    assert a["part_bwd"] == a["blend_fwd"] > 0
+    rast.bin(ws, masks[1])
+    rast.render_into(ws, C, D, T, I)
+    b = rast.read_status(ws)
+    assert (b["part_bwd"], b["walk_bwd"]) == (a["part_bwd"], a["walk_bwd"]) and 0 < b["blend_fwd"] < a["blend_fwd"]
+    rast.project(ws, *params, dp)
+    c = rast.read_status(ws)
+    assert c["blend_fwd"] == c["part_bwd"] == c["walk_bwd"] == 0
