@@ -444,13 +444,18 @@ __device__ __forceinline__ void block_pairs(const Dims& d, const WS& w, const Ch
 // not fit marks the block failed (what fits is still written, and skipped).
 constexpr int kStageBuf = 128;
 
-// LDS: [chunk] per-tile counters, then the active bits.
+// LDS: [chunk] per-tile counters, then the active bits: up to 50.7 KB beside
+// 18.4 KB of staging and collected rows.  A workgroup of gfx950 can have 160 KB
+// and the runtime launches it without an attribute; two such workgroups share a
+// CU, as two of the 59 KB without the rows do.
 template <bool QUEUE>
 __global__ __launch_bounds__(256) void k_pair_hist(Dims d, WS w) {
     extern __shared__ uint32_t lds[];
     __shared__ uint4 sbuf[4][kStageBuf];
     __shared__ PairQueue pq[QUEUE ? 4 : 1];
     __shared__ uint32_t sfail;
+    static_assert(4 * (kHistChunk + (kHistChunk + 31) / 32) + sizeof(sbuf) + sizeof(pq) + sizeof(sfail) <= 80 * 1024,
+                  "two workgroups per CU at the widest chunk");
     const Chunk c = chunk_of_block(d);
     const int ct = c.t1 - c.t0;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;

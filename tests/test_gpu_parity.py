@@ -1226,3 +1226,22 @@ def test_contribution_counter_is_the_last_backwards(kw):
     rast.project(ws, *params, dp)
     c = rast.read_status(ws)
     assert c["blend_fwd"] == c["part_bwd"] == c["walk_bwd"] == 0
+
+
+def test_collected_rows_in_the_widest_tile_chunk():
+    """Two frames of 143 x 96 tiles in ranges of 512 Gaussians: enough
+    binning blocks that a chunk keeps 12,288 tiles, 69 KB of LDS with the
+    collected rows: the oracle's lists."""
+    size, n, frames = (1142, 767), 66_000, 2
+    cam = small_cam(*size, 0.8 * size[0])
+    sc, poses = _two_pose_scene(1, n=n)
+    sc["scale"] *= 0.05
+    mask = (np.random.default_rng(5).random((frames, size[1], size[0])) < 0.05).astype(np.uint8)
+    rast = _rast(cam, n, frames, tile_w=8, tile_h=8, max_pairs=1 << 22)
+    ws = rast.new_workspace()
+    rast.project(ws, *dev_params(sc), dev_poses(poses))
+    rast.bin(ws, dev_mask(mask))
+    st = rast.read_status(ws)
+    assert st["status"] == 0 and st["restaged_blocks"] == 0
+    P = orc.make_params(cam, tile=(8, 8))
+    _check_pairs(rast, ws, P, orc.project(P, sc, poses), mask, frames, n, {"status": st})
