@@ -9,7 +9,7 @@ import torch
 
 from oracle import oracle as orc
 from rtg_synth import make_config, random_upstream
-from tests.gpu_helpers import (assert_parity, compare_forward, dev_mask, dev_params, dev_poses, fmt_stats,
+from tests.gpu_helpers import (T_EPS, assert_parity, compare_forward, dev_mask, dev_params, dev_poses, fmt_stats,
                                gpu_forward, grad_stats, need_gpu, oracle_forward, oracle_grads, rel_err, ws_view)
 from tests.scenes_small import (edge_on_surfels, footprint_condition, identity_pose, random_pose, random_scene,
                                 small_cam, scene_from)
@@ -1245,3 +1245,39 @@ def test_collected_rows_in_the_widest_tile_chunk():
     assert st["status"] == 0 and st["restaged_blocks"] == 0
     P = orc.make_params(cam, tile=(8, 8))
     _check_pairs(rast, ws, P, orc.project(P, sc, poses), mask, frames, n, {"status": st})
+
+
+def _open_strip_scene(n_far=5000, n_near=1800):
+    """Opaque surfels in front of all but a strip at the left, and thousands
+    of faint Gaussians behind: a few pixels of a pack keep compositing
+    through a list that the others have closed."""
+    rng = np.random.default_rng(71)
+    near = random_scene(rng, n_near, smin=0.03, smax=0.07, opaque_frac=1.0, unstable_frac=0.5)
+    z = rng.uniform(0.9, 1.1, n_near)
+    near["pos"] = np.stack([rng.uniform(-0.33, 0.6, n_near) * z, rng.uniform(-0.45, 0.45, n_near) * z, z], 1).astype(np.float32)
+    far = random_scene(rng, n_far, smin=0.02, smax=0.1, opaque_frac=0.0, unstable_frac=0.5)
+    z = rng.uniform(1.5, 3.0, n_far)
+    far["pos"] = np.stack([rng.uniform(-0.55, 0.55, n_far) * z, rng.uniform(-0.42, 0.42, n_far) * z, z], 1).astype(np.float32)
+    far["opacity"] = rng.uniform(0.005, 0.02, n_far).astype(np.float32)
+    return {k: np.concatenate([near[k], far[k]]) for k in near}
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(tile_w=8, tile_h=8), dict(tile_w=32, tile_h=8),
+                                dict(items_per_pop=1, static_share=30)])
+def test_culling_follows_the_open_pixels(kw):
+    """Packs whose later batches are culled for a few open pixels: image,
+    index, depth branch and gradients against the oracle."""
+    cam, sc, poses = small_cam(64, 48, 60.0), _open_strip_scene(), identity_pose()
+    mask = np.ones((1, 48, 64), np.uint8)
+    rast = _rast(cam, len(sc["pos"]), **kw)
+    g = gpu_forward(rast, sc, poses, mask)
+    P, recs, pix, out = oracle_forward(cam, sc, poses, mask)
+    errs = compare_forward(g, pix, out, recs)
+    closed = out["trans"].reshape(48, 64) < T_EPS
+    assert closed.mean() > 0.2 and (~closed).mean() > 0.1
+    few = closed.reshape(6, 8, 8, 8).sum((1, 3))                # closed pixels per 8x8 pack
+    assert ((few >= 40) & (few < 64)).any()
+    errs.update(_grad_parity(cam, sc, poses, mask, seed=72, **kw))
+    print("open strip", kw, fmt_stats(errs))
+    assert errs["index_mismatch"] == 0
+    assert_parity(errs)
