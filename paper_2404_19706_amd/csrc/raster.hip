@@ -739,6 +739,19 @@ __device__ __forceinline__ void depth_hits(const Dims& d, const WS& w, const Pix
     }
 }
 
+// The records of the slice (bit k) that reach a pixel of the pack before its
+// last entry: the first kl of this lane's.
+__device__ __forceinline__ uint64_t reached(const Slice& S, const PixelOfItem& p, int kl, float cut) {
+    uint64_t m = 0;
+#pragma unroll 1
+    for (int k = 0; ballot(k < kl) != 0; ++k) {
+        float dx, dy;
+        const float dd = eval_dd(S.r[0][k], S.r[1][k].x, p.ux, p.uy, dx, dy);
+        if (ballot(dd <= cut && k < kl) != 0) m |= 1ull << k;
+    }
+    return m;
+}
+
 template <int DM>
 __global__ RTG_BWD_BOUNDS void k_raster_bwd(Dims d, WS w, const float* __restrict__ out_d,
                                                  const float* __restrict__ out_t,
@@ -802,6 +815,10 @@ __global__ RTG_BWD_BOUNDS void k_raster_bwd(Dims d, WS w, const float* __restric
         if (jend > p.rs) B = load_batch(w, jend - p.rs > 64u ? jend - 64u : p.rs, jend, lane);
         GQ.px[lane] = make_float4(p.ux, p.uy, g0, g1);
         GQ.px2[lane] = make_float2(g2, gd);
+        // an upstream that is no number times a weight of zero is none either:
+        // then a record that reaches no pixel must not be summed
+        const float big = fmaxf(fmaxf(fabsf(g0), fabsf(g1)), fmaxf(fabsf(g2), fabsf(gd)));
+        const bool wild = ballot(!(big <= 3.4028235e38f) || g0 != g0 || g1 != g1 || g2 != g2 || gd != gd) != 0;
         // alpha-blended depth: the depth path follows the colour's
         if constexpr (DM == 0) depth_hits(d, w, p, lane, hitpos, gd, D, grad);
         // the upstream-weighted colour (and blended depth) behind: only g . A
@@ -827,7 +844,9 @@ __global__ RTG_BWD_BOUNDS void k_raster_bwd(Dims d, WS w, const float* __restric
             const int kl = __builtin_popcountll(lim >= 64u ? kept : kept & ((1ull << lim) - 1ull));
             wave_lds_sync();
             const uint32_t gwl = lane < nk ? S.gid[lane] : 0u;
-            const uint64_t um = ballot((gwl & kUnstableBit) != 0u), pm = ballot((gwl & kPreciseBit) != 0u);
+            uint64_t um = ballot((gwl & kUnstableBit) != 0u);
+            const uint64_t pm = ballot((gwl & kPreciseBit) != 0u);
+            if (wild) um &= reached(S, p, kl, cut);
             qprec = qprec || pm != 0;
             if (b0 > p.rs) B = load_batch(w, b0 - p.rs > 64u ? b0 - 64u : p.rs, b0, lane);
             // groups of G records, specialised on whether the batch holds a

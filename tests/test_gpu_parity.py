@@ -1281,3 +1281,34 @@ def test_culling_follows_the_open_pixels(kw):
     print("open strip", kw, fmt_stats(errs))
     assert errs["index_mismatch"] == 0
     assert_parity(errs)
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("depth_mode", [0, 1])
+def test_upstream_that_is_no_number_stays_with_the_gaussians_reached(bad, depth_mode):
+    """A pack of two pixels with a Gaussian on each and one between them that
+    reaches neither: a NaN or an infinity upstream of one pixel leaves the
+    gradients of the one between at zero."""
+    cam = small_cam(16, 16, 20.0)
+    x = np.array([-0.5, 0.0, 0.5])
+    sc = scene_from(np.stack([x, np.full(3, 0.05), np.full(3, 2.0)], 1), np.full((3, 3), 0.05),
+                    np.tile([1.0, 0, 0, 0], (3, 1)), np.full(3, 0.5), np.full((3, 3), 0.5))
+    mask = np.zeros((1, 16, 16), np.uint8)
+    mask[0, 8, 3] = mask[0, 8, 12] = 1
+    rast = _rast(cam, 3, depth_mode=depth_mode)
+    params, dp = dev_params(sc), dev_poses(identity_pose())
+    C, D, T, I, ws = rast.forward(params, dp, dev_mask(mask))
+    got = []
+    for v in (1.0, bad):
+        gC, gD = torch.ones_like(C), torch.ones_like(D)
+        gC[0, 8, 12], gD[0, 8, 12] = v, v
+        g = rast.alloc_grads()
+        rast.project(ws, *params, dp)
+        rast.bin(ws, dev_mask(mask))
+        rast.render_into(ws, C, D, T, I)
+        rast.backward_into(ws, params, dp, D, T, I, gC, gD, g)
+        got.append({k: t.cpu().numpy() for k, t in g.items()})
+    assert rast.read_status(ws)["pairs"] == 3
+    for k in got[0]:
+        assert not got[0][k][1].any() and not got[1][k][1].any(), k
+    assert not np.isfinite(got[1]["color"][2]).any() and np.isfinite(got[0]["color"]).all()
