@@ -421,8 +421,13 @@ rtg_status rtg_unstable_mask(const rtg_plan* p, void* ws, uint8_t* mask_out, voi
 namespace {
 
 // Gaussians per binning range from which k_pair_hist collects those with an
-// active row: with 256 a wave has one group of 64, nothing to collect, and the
-// loads that then come one after the other are its time.
+// active row.  What the collecting gains comes from the mask, which only the
+// device knows; the range says how much there can be to collect.  With 256 a
+// wave has one group of 64, and loads that come one after the other are its
+// time (one full 640x480 frame 14.4 us without, 14.9 with a collecting form of
+// one group).  From 512 on masked frames gain (16 keyframes 660 to 474 us, a
+// masked 1200x680 frame 30 to 23) and a full one, where every Gaussian has a
+// row, loses little (500,000 Gaussians 25.9 to 26.7).
 constexpr int32_t kQueueFrom = 512;
 
 constexpr int64_t kMaxSortGrid = int64_t(1) << 23;   // workgroups of 256 in one launch of k_tile_sort

@@ -415,6 +415,13 @@ struct IcpCand {
 // height fit it, which takes the binary64 divisions per pixel from ten to two.
 // The partial sums of consecutive passes and the poses alternate between two
 // places, so no workgroup overwrites what another still reads.
+//
+// A level-0 pass at 1200x680 takes 17.0 us.  4.8 of them are the launch, the
+// sums of the rows and the solve (a launch that does only these takes as long).
+// Vector instructions are issued for 9 of the other 12 (5.3M wave instructions,
+// 3.2M of them binary64, by counters); the rest is latency that two waves per
+// SIMD leave open.  With three (balanced strips, other sums) a pass took 19 us.
+// The call: 245 us, 298 with the strips, 720 with a solve launch per iteration.
 template <bool TAB>
 __global__ __launch_bounds__(kIcpThreads) void k_icp_pass(IcpLevel L, IcpPrev prev, const double* __restrict__ Tm,
                                                           double dist, double sin_a, int blocks,

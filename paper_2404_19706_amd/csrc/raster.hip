@@ -42,9 +42,9 @@
 // operations, value 2 more and the exponential, blend 7 (forward), and the
 // one gradient sum g . (c - A) in place of three colour recursions (backward).
 // Measured on MI355X, forward / backward: 16 keyframes of 1200x680 with 2.6M
-// masked pixels 914 / 1050 to 632 / 661 us, 8 keyframes 632 / 930 to 510 /
-// 675 us, one masked 1200x680 frame 63 / 103 to 45 / 61 us, one full 640x480
-// frame 28 / 68 to 28 / 51 us.
+// masked pixels 914 / 1050 to 630 / 650 us, 8 keyframes 632 / 930 to 499 /
+// 650 us, one masked 1200x680 frame 63 / 103 to 44 / 59 us, one full 640x480
+// frame 28 / 68 to 27 / 49 us.
 #include <type_traits>
 
 #include "rtg_common.h"
@@ -54,7 +54,7 @@
 // (instruction-level parallelism against register pressure), and the
 // minimum number of resident waves per SIMD each kernel is compiled for
 // (occupancy; 0 = compiler's choice).  Measured on gfx950, us per launch over
-// 16 / 8 keyframes: forward groups of four (112 VGPRs, four waves) 793 / 582,
+// 16 / 8 keyframes: forward groups of four (110 VGPRs, four waves) 793 / 582,
 // of two (five waves) 912 / 589, of four held to five waves 900 / 593;
 // backward groups of two (127 VGPRs, four waves) 705 / 715, single records
 // 725 / 734.

@@ -121,8 +121,9 @@ struct WS {
     float* recp;            // 6 floats per precise slot: r_hi, r_lo, U.xx, U.yy, residual
     unsigned long long* keys;     // per pair: (depth bits << 32) | Gaussian index, grouped per tile
     unsigned long long* scratch;  // per pair: merge buffer of the long-list sort
-    unsigned long long* wcount;   // [4][kMaxWaves] per-wave work counters
-    float* lwave;                 // [3][kMaxWaves] per-wave L1 sums (colour, depth, depth count)
+    unsigned long long* wcount;   // [4][kMaxWaves] per-wave work counters: tests, blends, entries walked back, blends
+                                  // (of two renders by turns, see Hdr::blend_row)
+    float* lwave;                 // [3][kMaxWaves] per-workgroup L1 sums (colour, depth, depth count)
     uint32_t* stagec;             // [256] entries claimed per staging region
     uint32_t* bfail;              // per binning block: 1 if its staging overflowed
     uint32_t* vcnt;               // [F][ngrp] visible Gaussians per group of 64
